@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
-SOURCES = ["lmbd_api.hip", "lmbd_serve.hip", "k_nbr.hip", "k_scs.hip", "k_mbd.hip", "k_gather.hip"]
+SOURCES = ["lmbd_api.hip", "lmbd_serve.hip", "k_nbr.hip", "k_scs.hip", "k_mbd.hip", "k_mbd_rows.hip", "k_gather.hip"]
 LIB = os.path.join(HERE, "liblmbd.so")
 
 FLAGS = [

@@ -58,108 +58,13 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "lmbd_internal.h"
+#include "mbd_common.h"
 
 namespace lmbd {
 
 
-__host__ __device__ inline size_t al4(size_t x) { return (x + 3) / 4 * 4; }
-
-// Per-site arrays (LDS, or the workspace) and the small per-atom arrays (LDS).  The
-// pair sums g of the force stage take the place of sqrt(alpha~), whose last use (the
-// operands of Tbar) precedes them.
-struct MbdLds {
-    double *px, *py, *pz, *sa, *sqa, *Rt, *fs, *dfs, *ab, *g, *rb, *fg, *mu, *cf, *lz;
-};
-// sa and ab hold every frequency of the energy: 0 and the nq nodes.  cf (fitted
-// coefficients, [nq][kMaxNmax + 1] and [kMaxNmax + 1][nq]) and lz (Lanczos: alpha and beta [steps][nq], the steps
-// taken and the two bounds per node) exist only when used.  The site arrays take
-// mbd_site_doubles(nk, nq) from b, the small ones start at sm.
-__device__ inline MbdLds mbd_lds(double* b, int nk, int nq, double* sm, int n_max, bool fit) {
-    const int nw = nq + 1;
-    MbdLds L;
-    L.px = b;
-    L.py = L.px + nk;
-    L.pz = L.py + nk;
-    L.sa = L.pz + nk;
-    L.sqa = L.sa + (size_t)nk * nw;   // [nk][nq]
-    L.g = L.sqa;                      // [4 parts][nk][3], nq >= 12 (force stage only)
-    L.Rt = L.sqa + (size_t)nk * max(nq, 12);
-    L.fs = L.Rt + nk;
-    L.dfs = L.fs + nk;
-    L.ab = L.dfs + nk;
-    L.rb = L.ab + (size_t)nk * nw;    // [4 parts][nk]
-    L.fg = L.rb + 4 * (size_t)nk;     // [nk][3]
-    L.mu = sm;
-    L.cf = L.mu + (size_t)(n_max + 1) * nq;
-    L.lz = L.cf + (fit ? 2 * (size_t)(kMaxNmax + 1) * nq : 0);
-    return L;
-}
-
-// (nkmax = 0: the sparse form with the site arrays in the workspace)
 size_t mbd_lds_bytes(int nkmax, int nq, int n_max, int lz_steps, bool fit) {
     return sizeof(double) * (mbd_site_doubles((size_t)nkmax, nq) + mbd_small_doubles(nq, n_max, lz_steps, fit));
-}
-
-// The output function of SplitMix64 (Steele, Lea and Flood, OOPSLA 2014) on a 64-bit counter.
-__device__ inline uint64_t splitmix64(uint64_t z) {
-    z += 0x9E3779B97F4A7C15ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
-}
-
-// Coefficients c_0 .. c_n_max (c_0 = c_1 = 0 on return) of the least-squares polynomial
-// of ln(1 - x) on [lo, hi] over the Gauss-Legendre points x_i of [-1, 1] mapped to it:
-// the Legendre coefficients a_j = (2 j + 1) / 2 sum_i w_i ln(1 - lambda_i) P_j(x_i),
-// then sum_j a_j P_j(t), t = (x - mid) / half, in powers of x by Clenshaw's recurrence
-// b_j = a_j + (2j+1)/(j+1) t b_{j+1} - (j+1)/(j+2) b_{j+2} carried out on coefficient
-// arrays (b_0 is the polynomial).  No width (hi - lo <= 1e-12): the Taylor
-// coefficients -1/n.
-__host__ __device__ inline void log_fit(double lo, double hi, int n_max, const double* gx, const double* gw,
-                                        double (&c)[kMaxNmax + 1]) {
-#pragma unroll
-    for (int n = 0; n <= kMaxNmax; ++n) c[n] = n >= 2 ? -1.0 / n : 0.0;
-    if (!(hi - lo > 1e-12)) return;
-    const double h = 0.5 * (hi - lo), m = 0.5 * (hi + lo), ih = 1.0 / h;
-    double cl[kMaxNmax + 1];
-#pragma unroll
-    for (int j = 0; j <= kMaxNmax; ++j) cl[j] = 0.0;
-    for (int i = 0; i < kFitNodes; ++i) {
-        const double x = gx[i];
-        const double f = gw[i] * log1p(-(m + h * x));
-        double p0 = 1.0, p1 = x;
-        cl[0] += f;
-        cl[1] += f * x;
-#pragma unroll
-        for (int j = 2; j <= kMaxNmax; ++j) {
-            const double p2 = ((2 * j - 1) * x * p1 - (j - 1) * p0) / j;
-            cl[j] += f * p2;
-            p0 = p1;
-            p1 = p2;
-        }
-    }
-    // b1 = b_{j+1}, b2 = b_{j+2}; b_j overwrites b2, then the two swap roles
-    double b1[kMaxNmax + 1], b2[kMaxNmax + 1];
-#pragma unroll
-    for (int t = 0; t <= kMaxNmax; ++t) b1[t] = b2[t] = 0.0;
-#pragma unroll
-    for (int j = kMaxNmax; j >= 0; --j) {
-        if (j > n_max) continue;
-        const double aj = 0.5 * (2 * j + 1) * cl[j];
-        const double al = (2.0 * j + 1.0) / (j + 1.0) * ih, be = -(j + 1.0) / (j + 2.0);
-#pragma unroll
-        for (int t = kMaxNmax; t >= 0; --t)
-            b2[t] = (t == 0 ? aj : 0.0) + al * ((t > 0 ? b1[t - 1] : 0.0) - m * b1[t]) + be * b2[t];
-#pragma unroll
-        for (int t = 0; t <= kMaxNmax; ++t) {
-            const double x = b1[t];
-            b1[t] = b2[t];
-            b2[t] = x;
-        }
-    }
-#pragma unroll
-    for (int n = 0; n <= kMaxNmax; ++n) c[n] = n >= 2 ? b1[n] : 0.0;
 }
 
 typedef double d4_t __attribute__((ext_vector_type(4)));
@@ -283,97 +188,18 @@ __device__ __forceinline__ void mfma_gemm_nt(int M, int N, int K, const W* __res
     __syncthreads();
 }
 
-// T_LR pair coefficients: T_LR = A rhat rhat^T + B I with radial derivatives,
-// and dT_LR/dS~ = fLR (df/dS~) T.
-template <typename P>
-struct LrPair {
-    P A, B, dA, dB, dfS, fLR;
-};
-template <typename P>
-__device__ inline LrPair<P> lr_pair(P r, P S, P damp_d, P rcut, P rb) {
-    P dfdr, dfdS, dcut;
-    const P f = fermi<P>(r, S, damp_d, dfdr, dfdS);
-    const P fc = cutoff_poly<P>(r, rcut, rb, dcut);
-    const P w = fc * f;
-    const P dw = dcut * f + fc * dfdr;
-    const P ir = P(1) / r;
-    const P ir3 = ir * ir * ir;
-    LrPair<P> p;
-    p.A = P(3) * w * ir3;
-    p.B = -w * ir3;
-    p.dA = P(3) * dw * ir3 - P(9) * w * ir3 * ir;
-    p.dB = -dw * ir3 + P(3) * w * ir3 * ir;
-    p.dfS = dfdS;
-    p.fLR = fc;
-    return p;
-}
-
 // 512 threads: the eight wavefronts share the GEMM items of an atom (six
 // 48-row items per Krylov product, 21 lower-triangle items of Tbar), which
 // balances them better than four (measured 4.55 -> 4.42 ms FP64, 3.07 -> 2.62
 // ms FP32 on 1,728 C atoms; 384, 768 and 1,024 threads were slower)
 constexpr int kMbdThreads = 512;
 
-// Value of `x` in lane l (l uniform over the wavefront).
-__device__ inline double read_lane(double x, int l) {
-    const long long b = __double_as_longlong(x);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(b & 0xffffffffll), l);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-__device__ inline float read_lane(float x, int l) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
-}
-template <typename W>
-__device__ inline W lane_value(W x, int l) { return read_lane(x, l); }
-
-// Sums over the 64 lanes of nine per-lane values, returned to every lane.  A
-// transposed butterfly: at the exchanges over lane bits 5, 4, 3 and 2 a lane keeps
-// half of the (zero-padded to 16) values it carries and sends the other half, so
-// lane l ends with value 8 b5 + 4 b4 + 2 b3 + b2 (b_n: bit n of l) summed over its
-// 16 partners; two plain exchanges finish the sum and one lane per value gives it
-// out: 17 exchanges instead of 54.
-__device__ inline void wave_sum9(const double (&v)[9], double (&out)[9]) {
-    const int lane = threadIdx.x & 63;
-    double a[8], b[4], c[2];
-    bool hi = lane & 32;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        const double lo_v = v[t], hi_v = (t == 0) ? v[8] : 0.0;
-        a[t] = (hi ? hi_v : lo_v) + __shfl_xor(hi ? lo_v : hi_v, 32);
-    }
-    hi = lane & 16;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) b[t] = (hi ? a[4 + t] : a[t]) + __shfl_xor(hi ? a[t] : a[4 + t], 16);
-    hi = lane & 8;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) c[t] = (hi ? b[2 + t] : b[t]) + __shfl_xor(hi ? b[t] : b[2 + t], 8);
-    hi = lane & 4;
-    double d = (hi ? c[1] : c[0]) + __shfl_xor(hi ? c[0] : c[1], 4);
-    d += __shfl_xor(d, 2);
-    d += __shfl_xor(d, 1);
-#pragma unroll
-    for (int x = 0; x < 9; ++x)
-        out[x] = read_lane(d, ((x >> 3) & 1) << 5 | ((x >> 2) & 1) << 4 | ((x >> 1) & 1) << 3 | (x & 1) << 2);
-}
-
-// SP = false: T_LR is stored dense and every product runs on the matrix cores.
-// SP = true (two-radius regime, Sec. III.A: a site couples to the central atom up
-// to r_MBD,1 but to the others only up to r_MBD,2, so block rows other than the
-// central one are sparse): T_LR is never stored.  The coupled sites of every block
-// row and their coefficients are listed once per atom (a wavefront per row, its
-// lanes testing 64 candidates at a time); each Krylov product walks a row's list
-// with the whole wavefront (lanes over the Krylov columns), and Tbar is formed only
-// for coupled pairs, each 3x3 block as nine dot products over eight lanes.
-// The sparse form is bound by the latency of its gathers rather than by arithmetic:
-// it runs 1,024 threads (four wavefronts per SIMD at its register count) to hide it.
-constexpr int kMbdThreadsSparse = 1024;
+// The dense form: T_LR is stored and every product runs on the matrix cores (the sparse
+// forms are in k_mbd_rows.hip).
 // TB: the atoms' structures have two-body radii of their own (a separate instantiation,
-// so that the other kernels carry none of its registers)
-template <typename W, int FORM, bool TB>
-__global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax) {
-    constexpr bool SP = FORM != kMbdDense, GS = FORM == kMbdSparseGlobal;
+// so that the other kernel carries none of its registers)
+template <typename W, bool TB>
+__global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax) {
     extern __shared__ double lds[];
     const int k = a.order[blockIdx.x];
     const int tid = threadIdx.x;
@@ -387,10 +213,7 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
     const bool fit = a.fit != 0;
     constexpr bool has2b = TB;
     W* const wbase = static_cast<W*>(a.work) + a.work_off[k];
-    const int64_t lcap = GS ? mbd_list_cap(nK, SI.m2max) : (int64_t)nK * nK;   // list entries
-    const MbdGlobalLayout G = mbd_global_layout(nK, nq, n_max, a.mmax, lcap, (int64_t)sizeof(W), a.forces != 0);
-    MbdLds L = GS ? mbd_lds(reinterpret_cast<double*>(wbase + G.sites), nK, nq, lds, n_max, fit)
-                  : mbd_lds(lds, nkmax, nq, lds + mbd_site_doubles((size_t)nkmax, nq), n_max, fit);
+    MbdLds L = mbd_lds(lds, nkmax, nq, lds + mbd_site_doubles((size_t)nkmax, nq), n_max, fit);
     // c_n at node q: fitted per atom and node, or the common series
     // (fitted: two copies in LDS, [kMaxNmax + 1][nq] here and [nq][kMaxNmax + 1] for the adjoint operands,
     // whose per-element loop keeps one node's coefficients at fixed offsets)
@@ -400,22 +223,18 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
     const Site* S = a.sites + a.site_off[k];
     const double* aloc = a.alpha_loc + a.aloc_off[k];
     // sub-arrays start on multiples of 4 elements (aligned 4-vector loads)
-    const int KK = n_max * ncol, KKp = (KK + 3) / 4 * 4;
+    // Tbar's product runs over u_1 .. u_{n_max-2}: u_0 = e_k only reaches the central block
+    // row and column, which are added apart (0 columns for the approximate forces, which
+    // have no other part)
+    const int na = a.paper ? 0 : max(n_max - 2, 0);
+    const int KK = na * ncol, KKp = (KK + 3) / 4 * 4;
     const int N3p = (int)al4(N3);                            // row stride of T and of V^T (zero padded)
-    W* T = wbase;                                            // dense T_LR (the sparse form's lists in its space)
+    W* T = wbase;                                            // T_LR
     W* U = T + al4((size_t)N3 * N3p);                        // u_1 .. u_mmax
     W* V = U + al4((size_t)a.mmax * N3 * ncol);              // (D u_m)^T, the next product's operand, ncol x N3p,
     W* V2 = V + al4((size_t)ncol * N3p);                     //   in two buffers used in turn
-    W* Pm = V2 + al4((size_t)ncol * N3p);                    // D u_a side by side, a = 0 .. n_max-1
+    W* Pm = V2 + al4((size_t)ncol * N3p);                    // D u_a side by side, a = 1 .. na
     W* Qm = Pm + (size_t)N3 * KKp;                           // W D Z_a side by side
-    if constexpr (GS) {   // no dense T: the parts of the global-site layout
-        T = wbase + G.lists;
-        U = wbase + G.U;
-        V = wbase + G.V;
-        V2 = wbase + G.V2;
-        Pm = wbase + G.P;
-        Qm = wbase + G.Q;
-    }
     auto Uat = [&](int m) { return U + (size_t)(m - 1) * N3 * ncol; };
 
     // --- blend (Sec. III.B, central/local combination) and SCS radii
@@ -465,7 +284,6 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
     // per thread, consecutive threads along a block row, so that the rows are
     // written in contiguous runs (each unordered pair is evaluated from both
     // ends: the block is the same for (i, j) and (j, i)).
-    if constexpr (!SP) {
     for (int p = tid; p < nK * nK; p += blockDim.x) {
         const int i = p / nK, j = p % nK;
         double blk[9] = {};
@@ -491,197 +309,9 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
         V2[(size_t)(e / (N3p - N3)) * N3p + N3 + e % (N3p - N3)] = W(0);
     }
     __syncthreads();
-    }
-
-    // sparse form: whether the pair (i, j) couples, and its coefficients T_LR,ij = A rhat rhat^T + B I
-    auto coupled = [&](int i, int j, double v[3], double& r) -> bool {
-        if (j >= nK || j == i) return false;
-        v[0] = L.px[i] - L.px[j];
-        v[1] = L.py[i] - L.py[j];
-        v[2] = L.pz[i] - L.pz[j];
-        r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-        // (central pairs out to the two-body radius too: their MBD coefficients are 0 there)
-        return r < ((i == 0 || j == 0) ? (has2b ? fmax(SI.r_mbd1, SI.r_2b1) : SI.r_mbd1) : SI.r_mbd2);
-    };
-    auto couple = [&](int i, int j, W& A, W& B, double rh[3]) -> bool {
-        double v[3], r;
-        if (!coupled(i, j, v, r)) return false;
-        const double rcut = (i == 0 || j == 0) ? SI.r_mbd1 : SI.r_mbd2;
-        const LrPair<W> t = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut), W(a.r_buf));
-        A = t.A;
-        B = t.B;
-        rh[0] = v[0] / r;
-        rh[1] = v[1] / r;
-        rh[2] = v[2] / r;
-        return true;
-    };
-    // sparse form: the coupled sites of every block row and their coefficients, found
-    // once per atom: row i at [roff[i], roff[i + 1]) of NN entries (site index, A, B, rhat).
-    // With the site arrays in LDS they sit in the space of the dense T (unused here):
-    // (4 + 5 sizeof(W)) nK^2 + 4 (nK + 1) bytes fit in its 9 nK^2 sizeof(W); else in a part of
-    // their own, sized from the structure's largest count of sites within r_mbd2.
-    const size_t NN = (size_t)lcap;
-    W* const pA = T;
-    W* const pB = pA + NN;
-    W* const pR0 = pB + NN;
-    W* const pR1 = pR0 + NN;
-    W* const pR2 = pR1 + NN;
-    int* const pj = reinterpret_cast<int*>(pR2 + NN);
-    int* const roff = pj + NN;
-    if constexpr (SP) {
-        // counts per row (into roff[i + 1]), then their running sum over the rows
-        for (int i = wave; i < nK; i += nwave) {
-            int n = 0;
-            for (int j0 = 0; j0 < nK; j0 += 64) {
-                double v[3], r;
-                n += __popcll(__ballot(coupled(i, j0 + lane, v, r)));
-            }
-            if (lane == 0) roff[i + 1] = n;
-        }
-        __syncthreads();
-        if (wave == 0) {
-            int carry = 0;
-            for (int i0 = 0; i0 < nK; i0 += 64) {
-                const bool in = i0 + lane < nK;
-                int x = in ? roff[i0 + lane + 1] : 0;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int t = __shfl_up(x, o);
-                    if (lane >= o) x += t;
-                }
-                if (in) roff[i0 + lane + 1] = carry + x;
-                carry += __shfl(x, 63);
-            }
-            if (lane == 0) roff[0] = 0;
-        }
-        __syncthreads();
-        if (tid == 0 && (size_t)roff[nK] > NN) {   // a row outgrew the bound: refuse the call
-            atomicOr(a.err, 32);
-            atomicMin(a.err_atom, k);
-        }
-        for (int i = wave; i < nK; i += nwave) {
-            int n = roff[i];
-            for (int j0 = 0; j0 < nK; j0 += 64) {
-                W A = W(0), B = W(0);
-                double rh[3] = {0.0, 0.0, 0.0};
-                const bool in = couple(i, j0 + lane, A, B, rh);
-                const unsigned long long mask = __ballot(in);
-                const size_t e = (size_t)n + __popcll(mask & ((1ull << lane) - 1ull));
-                if (in && e < NN) {
-                    pj[e] = j0 + lane;
-                    pA[e] = A;
-                    pB[e] = B;
-                    pR0[e] = W(rh[0]);
-                    pR1[e] = W(rh[1]);
-                    pR2[e] = W(rh[2]);
-                }
-                n += __popcll(mask);
-            }
-        }
-        __syncthreads();
-    }
-    // entries of row i: [roff[i], roff[i] + row_len(i)), within the capacity
-    auto row_len = [&](int i) -> int {
-        const int e1 = roff[i + 1] < (int)NN ? roff[i + 1] : (int)NN;
-        return e1 > roff[i] ? e1 - roff[i] : 0;
-    };
-    // sparse form: Uout = D T D Uin, one block row (and 64 columns) per wavefront, lanes over
-    // the columns, four coupled sites per step; the loads use in-bounds indices (entry 0 of the
-    // row, column 0) with a zero factor instead of a branch, so that they overlap
-    auto sparse_product = [&](const W* __restrict__ Uin, W* __restrict__ Uout) {
-        for (int it = wave; it < nK * ((ncol + 63) / 64); it += nwave) {
-            const int i = it % nK, col = (it / nK) * 64 + lane, q = col / 3;
-            const int cs = col < ncol ? col : 0, qs = cs / 3;
-            const int n = row_len(i);
-            const size_t e0 = (size_t)roff[i];
-            W acc0 = W(0), acc1 = W(0), acc2 = W(0);
-            for (int s0 = 0; s0 < n; s0 += 4) {
-                // the four entries are loaded cooperatively (lane 4 f + u holds field f of entry
-                // s0 + u: A, B, rhat) and handed to every lane through scalar registers
-                const int fu = lane & 3, ff = min(lane >> 2, 4);
-                const size_t ec = e0 + (s0 + fu < n ? s0 + fu : 0);
-                const W fv = pA[(size_t)ff * NN + ec];
-                const int jv = pj[ec];
-                W x[4][3], Aj[4], Bj[4], r0[4], r1[4], r2[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const bool ok = s0 + u < n;
-                    const int j = __builtin_amdgcn_readlane(jv, u);
-                    Aj[u] = lane_value(fv, u);
-                    Bj[u] = lane_value(fv, 4 + u);
-                    r0[u] = lane_value(fv, 8 + u);
-                    r1[u] = lane_value(fv, 12 + u);
-                    r2[u] = lane_value(fv, 16 + u);
-                    const W sj = (ok && col < ncol) ? W(L.sqa[(size_t)j * nq + qs]) : W(0);
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) x[u][c] = sj * Uin[(size_t)(3 * j + c) * ncol + cs];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const W ax = Aj[u] * (r0[u] * x[u][0] + r1[u] * x[u][1] + r2[u] * x[u][2]);
-                    acc0 += ax * r0[u] + Bj[u] * x[u][0];
-                    acc1 += ax * r1[u] + Bj[u] * x[u][1];
-                    acc2 += ax * r2[u] + Bj[u] * x[u][2];
-                }
-            }
-            if (col < ncol) {
-                const W si = W(L.sqa[(size_t)i * nq + q]);
-                Uout[(size_t)(3 * i) * ncol + col] = si * acc0;
-                Uout[(size_t)(3 * i + 1) * ncol + col] = si * acc1;
-                Uout[(size_t)(3 * i + 2) * ncol + col] = si * acc2;
-            }
-        }
-        __syncthreads();
-    };
-
-    // sparse form, Lanczos vectors (column-major [nq][N3p], one column per node):
-    // Vout = D T D Vin, one block row per wavefront, lanes over the nodes, the row's
-    // coupled sites in order
-    auto sparse_product_lz = [&](const W* __restrict__ Vin, W* __restrict__ Vout) {
-        const int q = lane < nq ? lane : 0;
-        for (int i = wave; i < nK; i += nwave) {
-            const int n = row_len(i);
-            const size_t e0 = (size_t)roff[i];
-            W acc0 = W(0), acc1 = W(0), acc2 = W(0);
-            for (int t = 0; t < n; ++t) {
-                const size_t e = e0 + t;
-                const int j = pj[e];
-                const W Aj = pA[e], Bj = pB[e], r0 = pR0[e], r1 = pR1[e], r2 = pR2[e];
-                const W sj = W(L.sqa[(size_t)j * nq + q]);
-                const W* x = Vin + (size_t)q * N3p + 3 * j;
-                const W x0 = sj * x[0], x1 = sj * x[1], x2 = sj * x[2];
-                const W ax = Aj * (r0 * x0 + r1 * x1 + r2 * x2);
-                acc0 += ax * r0 + Bj * x0;
-                acc1 += ax * r1 + Bj * x1;
-                acc2 += ax * r2 + Bj * x2;
-            }
-            if (lane < nq) {
-                const W si = W(L.sqa[(size_t)i * nq + q]);
-                W* y = Vout + (size_t)q * N3p + 3 * i;
-                y[0] = si * acc0;
-                y[1] = si * acc1;
-                y[2] = si * acc2;
-            }
-        }
-        __syncthreads();
-    };
 
     // --- u_1 = D T D e_k, V = D u_1
     W* U1 = Uat(1);
-    if constexpr (SP) {
-        // u_1 = D T D e_k needs the block column of the central atom only
-        for (int e = tid; e < nK * ncol; e += blockDim.x) {
-            const int i = e / ncol, col = e % ncol, q = col / 3, c = col % 3;
-            W A = W(0), B = W(0);
-            double rh[3] = {0.0, 0.0, 0.0};
-            const bool in = couple(i, 0, A, B, rh);
-            const double s = L.sqa[(size_t)i * nq + q] * L.sqa[q];
-            for (int r = 0; r < 3; ++r)
-                U1[(size_t)(3 * i + r) * ncol + col] =
-                    in ? W(s * (double(A) * rh[r] * rh[c] + (r == c ? double(B) : 0.0))) : W(0);
-        }
-        __syncthreads();
-    } else {
     for (int e = tid; e < N3 * ncol; e += blockDim.x) {
         const int row = e / ncol, col = e % ncol;
         const int q = col / 3, c = col % 3;
@@ -691,15 +321,10 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
         V[(size_t)col * N3p + row] = W(sq * u);
     }
     __syncthreads();
-    }
     // --- u_{m+1} = D (T V), V' = D u_{m+1}  (T symmetric, so it is its own K-major
     // operand); the product's stores write both, V' into the other buffer
     for (int m = 1; m < a.mmax; ++m) {
         W* Un = Uat(m + 1);
-        if constexpr (SP) {
-            sparse_product(Uat(m), Un);
-            continue;
-        }
         const W* Vin = (m & 1) ? V : V2;
         W* Vout = (m & 1) ? V2 : V;
         mfma_gemm_nt<3, 3, W>(N3, ncol, N3, T, N3p, Vin, N3p, false, [&](int r, int col, W v) {
@@ -710,155 +335,17 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
         });   // ends with a barrier
     }
 
-    // --- spectrum bounds of G~ at every node (Lanczos) and, with a.fit, the fitted c_n
-    if (a.lz_steps > 0) {
-        const int m = a.lz_steps;
-        // three vectors per node, column-major ([nq][N3p]), in the space of V; the dense
-        // products' operand D v (rows 0 .. nq-1, zero padded) in V2
-        W* vb[3] = {V, V + (size_t)nq * N3p, V + 2 * (size_t)nq * N3p};
-        double* la = L.lz;                            // alpha_j of node q at [j nq + q]
-        double* lb = la + (size_t)m * nq;             // beta_{j+1} at [j nq + q]
-        double* lm = lb + (size_t)m * nq;             // steps taken per node
-        double* bnd = lm + nq;                        // [nq][2] bounds
-        auto wave_total = [&](double x) -> double {   // same order, same value in every lane
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-            return x;
-        };
-        // start vector, keyed on (k, base atom, lattice shift, component) in the structure's numbering
-        const uint64_t kl = (uint64_t)(k - SI.atom_offset);
-        auto start = [&](int r) -> double {
-            const Site st = S[r / 3];
-            const uint64_t h = splitmix64((kl << 32) + (uint64_t)(st.base - SI.atom_offset));
-            const uint64_t z = splitmix64(h + 4ull * (uint64_t)(uint32_t)st.shift + (uint64_t)(r % 3));
-            return (double)(z >> 11) * 0x1.0p-53 - 0.5;
-        };
-        for (int q = wave; q < nq; q += nwave) {
-            double s2 = 0.0;
-            for (int r = lane; r < N3; r += 64) {
-                const double x = start(r);
-                s2 += x * x;
-            }
-            const double inv = 1.0 / sqrt(wave_total(s2));
-            W* v1 = vb[1] + (size_t)q * N3p;
-            W* v0 = vb[0] + (size_t)q * N3p;
-            for (int r = lane; r < N3; r += 64) {
-                const W v = W(start(r) * inv);
-                v1[r] = v;
-                v0[r] = W(0);
-                if constexpr (!SP) V2[(size_t)q * N3p + r] = W(L.sqa[(size_t)(r / 3) * nq + q]) * v;
-            }
-            if (lane == 0) lm[q] = m;
-        }
-        __syncthreads();
-        int ip = 0, ic = 1, iw = 2;
-        for (int j = 0; j < m; ++j) {
-            // w = G~ v_j at every node (a node that has stopped has v_j = 0)
-            if constexpr (SP) {
-                sparse_product_lz(vb[ic], vb[iw]);
-            } else {
-                W* wv = vb[iw];
+    // --- spectrum bounds of G~ at every node (Lanczos) and, with a.fit, the fitted c_n: the
+    // vectors in the space of V, the products' operand D v (rows 0 .. nq-1, zero padded) in V2
+    if (a.lz_steps > 0)
+        lanczos_fit<W>(
+            a, k, N3, N3p, L, V, [&](int r) { return lanczos_start(SI, k, S[r / 3], r); },
+            [&](int q, int r, W v) { V2[(size_t)q * N3p + r] = W(L.sqa[(size_t)(r / 3) * nq + q]) * v; },
+            [&](const W*, W* wv) {
                 mfma_gemm_nt<1, 2, W>(N3, nq, N3, T, N3p, V2, N3p, false, [&](int r, int q, W v) {
                     wv[(size_t)q * N3p + r] = W(L.sqa[(size_t)(r / 3) * nq + q]) * v;
                 });   // ends with a barrier
-            }
-            // w -= beta_j v_{j-1}; alpha_j = <v_j, w>; w -= alpha_j v_j; beta_{j+1} = |w|;
-            // v_{j+1} = w / beta_{j+1} (zero once the node stops)
-            for (int q = wave; q < nq; q += nwave) {
-                if (lm[q] <= j) continue;
-                const W* vp = vb[ip] + (size_t)q * N3p;
-                const W* vc = vb[ic] + (size_t)q * N3p;
-                W* w = vb[iw] + (size_t)q * N3p;
-                const double bj = j > 0 ? lb[(size_t)(j - 1) * nq + q] : 0.0;
-                double s = 0.0;
-                for (int r = lane; r < N3; r += 64) {
-                    const double t = double(w[r]) - bj * double(vp[r]);
-                    w[r] = W(t);
-                    s += double(vc[r]) * t;
-                }
-                const double al = wave_total(s);
-                double s2 = 0.0;
-                for (int r = lane; r < N3; r += 64) {
-                    const double t = double(w[r]) - al * double(vc[r]);
-                    w[r] = W(t);
-                    s2 += t * t;
-                }
-                const double bn = sqrt(wave_total(s2));
-                const bool stop = j == m - 1 || !(bn > 1e-10 * (fabs(al) + bj));
-                const double inv = stop ? 0.0 : 1.0 / bn;
-                for (int r = lane; r < N3; r += 64) {
-                    const W v = W(double(w[r]) * inv);
-                    w[r] = v;
-                    if constexpr (!SP) V2[(size_t)q * N3p + r] = W(L.sqa[(size_t)(r / 3) * nq + q]) * v;
-                }
-                if (lane == 0) {
-                    la[(size_t)j * nq + q] = al;
-                    lb[(size_t)j * nq + q] = bn;
-                    if (stop) lm[q] = j + 1;
-                }
-            }
-            __syncthreads();
-            const int t = ip;
-            ip = ic;
-            ic = iw;
-            iw = t;
-        }
-        // extreme eigenvalues of each node's tridiagonal matrix: bisection on the number
-        // of eigenvalues below x (the negative pivots of T - x I = L D L^T), one lane per end
-        if (tid < 2 * nq) {
-            const int q = tid >> 1, top = tid & 1;
-            const int me = (int)lm[q];
-            double glo = 0.0, ghi = 0.0;
-            for (int j = 0; j < me; ++j) {
-                const double b0 = j > 0 ? fabs(lb[(size_t)(j - 1) * nq + q]) : 0.0;
-                const double b1 = j + 1 < me ? fabs(lb[(size_t)j * nq + q]) : 0.0;
-                const double aj = la[(size_t)j * nq + q];
-                glo = j == 0 ? aj - b0 - b1 : fmin(glo, aj - b0 - b1);
-                ghi = j == 0 ? aj + b0 + b1 : fmax(ghi, aj + b0 + b1);
-            }
-            const double pad = 1e-14 * (fabs(glo) + fabs(ghi)) + 1e-300;
-            double lo = glo - pad, hi = ghi + pad;
-            const int target = top ? me : 1;   // count(lo) < target <= count(hi)
-            for (int it = 0; it < 256; ++it) {
-                const double mid = 0.5 * (lo + hi);
-                if (!(mid > lo && mid < hi)) break;
-                int cnt = 0;
-                double d = 1.0;
-                for (int j = 0; j < me; ++j) {
-                    const double bb = j > 0 ? lb[(size_t)(j - 1) * nq + q] : 0.0;
-                    d = la[(size_t)j * nq + q] - mid - (j > 0 ? bb * bb / d : 0.0);
-                    if (fabs(d) < 1e-300) d = -1e-300;
-                    cnt += d < 0.0 ? 1 : 0;
-                }
-                if (cnt >= target)
-                    hi = mid;
-                else
-                    lo = mid;
-            }
-            bnd[tid] = hi;
-            if (a.spectrum) a.spectrum[((size_t)k * nq + q) * 2 + top] = hi;
-        }
-        __syncthreads();
-        if (fit && tid < nq) {
-            const int q = tid;
-            const double lo = bnd[2 * q], hi = bnd[2 * q + 1];
-            double c[kMaxNmax + 1];
-            if (!(hi < 1.0)) {   // polarisation catastrophe: ln(1 - x) has no fit
-                atomicOr(a.err, 16);
-                atomicMin(a.err_atom, k);
-#pragma unroll
-                for (int n = 0; n <= kMaxNmax; ++n) c[n] = 0.0;
-            } else {
-                log_fit(lo, hi, n_max, a.gl_x, a.gl_w, c);
-            }
-#pragma unroll
-            for (int n = 0; n <= kMaxNmax; ++n) {
-                L.cf[q * (kMaxNmax + 1) + n] = c[n];
-                cfn[n * nq + q] = c[n];
-            }
-        }
-        __syncthreads();
-    }
+            });
 
     // --- moments mu_n(q) = <u_a, u_b>, a + b = n: eight moments (consecutive in the
     // node, so that a row's reads are contiguous) per wavefront, eight lanes per moment
@@ -927,7 +414,7 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
     // --- dE/d alpha~_i(w_q) from the moments (row-local Krylov products)
     if (a.paper) {
         // the full n = 2 trace: 2 c_2 sum_j alpha~_j |T_ij|^2, one site per thread over
-        // its block row; the central terms of n >= 3 from u_{n-1} and u_1 (the dense form
+        // its block row; the central terms of n >= 3 from u_{n-1} and u_1 (this form
         // only: the host never runs the approximate forces with the sparse products)
         for (int i = tid; i < nK; i += blockDim.x) {
             L.ab[(size_t)i * nwe] = 0.0;
@@ -1003,11 +490,18 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
         }
         L.ab[t] = v;
     }
-    // --- operands of Tbar = sum_a (D u_a)(W D Z_a)^T, Z_a = sum_b c_{a+b+1} u_b (u_0 = e_k),
-    // k-contiguous: P[r][a ncol + col] = sqrt(alpha~_r) u_a[r][col] and
-    // Q[s][a ncol + col] = w_k W_q sqrt(alpha~_s) Z_a[s][col]
-    // one (row, column) of the Krylov blocks per thread: u_0 .. u_{n_max-1} read
-    // once, all n_max column blocks of P and Q written
+    // --- operands of Tbar = sum_a (D u_a)(W D Z_a)^T, Z_a = sum_b c_{a+b+1} u_b (u_0 = e_k).
+    // Away from the central block row and column u_0 vanishes, so the product runs over
+    // a, b = 1 .. n_max - 2 only (144 instead of 216 columns at n_max = 6 and 12 nodes),
+    // k-contiguous: P[r][(a-1) ncol + col] = sqrt(alpha~_r) u_a[r][col] and
+    // Q[s][(a-1) ncol + col] = w_k W_q sqrt(alpha~_s) sum_{b>=1} c_{a+b+1} u_b[s][col].
+    // One (row, column) of the Krylov blocks per thread: u_1 .. u_{n_max-1} read once, all
+    // na column blocks of P and Q written.  The u_0 terms of Tbar's central block column,
+    // entry (row r >= 3, x): w_k sum_q W_q sqrt(alpha~_r alpha~_k) sum_{b>=1} c_{b+1}
+    // u_b[r][3q + x] (the approximate forces: b >= 2 with c_{b+1} (b + 1); with two-body
+    // radii the n = 2 term is apart), get their summand over q from the same values, into
+    // the space of V.  Leaving u_0 out of the product: Tbar 395k -> 265k cycles per atom
+    // of 1,728 C at 6 A.
     // (two instantiations: the common series coefficients are kernel arguments at
     // fixed offsets, the fitted ones LDS entries of the column's node)
     auto build_pq = [&](auto coef) {
@@ -1016,34 +510,34 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
             const double sq = L.sqa[(size_t)(r / 3) * nq + q];
             const double scale = wk * a.wq[q] * sq;
             double u[kMaxNmax];
-            u[0] = (r == col % 3) ? 1.0 : 0.0;
 #pragma unroll
             for (int b = 1; b < kMaxNmax; ++b) u[b] = (b < n_max) ? double(Uat(b)[(size_t)r * ncol + col]) : 0.0;
             W* pr = Pm + (size_t)r * KKp + col;
             W* qr = Qm + (size_t)r * KKp + col;
+            double z0 = 0.0;
 #pragma unroll
-            for (int aa = 0; aa < kMaxNmax; ++aa) {
-                if (aa >= n_max) break;
-                double z = 0.0;
-                if (a.paper) {   // Z_0 = sum_{n>=3} c_n n u_{n-1}; Z_{n-1} = c_n n e_k
-#pragma unroll
-                    for (int b = 2; b < kMaxNmax; ++b)
-                        if (aa == 0 && b <= n_max - 1) z += coef(b + 1, q) * (b + 1) * u[b];
-                    if (aa >= 2) z = coef(aa + 1, q) * (aa + 1) * u[0];
-                } else {
-#pragma unroll
-                    for (int b = 0; b < kMaxNmax; ++b)
-                        if ((b > 0 || aa >= 1) && b <= n_max - 1 - aa) z += coef(min(aa + b + 1, kMaxNmax), q) * u[b];
+            for (int b = 1; b < kMaxNmax; ++b) {
+                if (a.paper) {
+                    if (b > 1) z0 += coef(b + 1, q) * (b + 1) * u[b];
+                } else if (!(has2b && b == 1)) {
+                    z0 += coef(b + 1, q) * u[b];
                 }
-                pr[(size_t)aa * ncol] = W(sq * u[aa]);
-                qr[(size_t)aa * ncol] = W(scale * z);
+            }
+            V[e] = W(scale * L.sqa[q] * z0);
+#pragma unroll
+            for (int aa = 1; aa < kMaxNmax - 1; ++aa) {
+                if (aa > na) break;
+                double z = 0.0;
+#pragma unroll
+                for (int b = 1; b < kMaxNmax - 1; ++b)
+                    if (b <= n_max - 1 - aa) z += coef(min(aa + b + 1, kMaxNmax), q) * u[b];
+                pr[(size_t)(aa - 1) * ncol] = W(sq * u[aa]);
+                qr[(size_t)(aa - 1) * ncol] = W(scale * z);
             }
         }
     };
-    if (fit)
-        build_pq([&](int n, int q) { return (has2b && n == 2) ? 0.0 : L.cf[q * (kMaxNmax + 1) + n]; });
-    else
-        build_pq([&](int n, int) { return (has2b && n == 2) ? 0.0 : a.coef[n]; });
+    if (fit) build_pq([&](int n, int q) { return L.cf[q * (kMaxNmax + 1) + n]; });
+    else build_pq([&](int n, int) { return a.coef[n]; });
     for (int e = tid; e < N3 * (KKp - KK); e += blockDim.x) {   // padding columns
         const int r = e / (KKp - KK), kk = KK + e % (KKp - KK);
         Pm[(size_t)r * KKp + kk] = W(0);
@@ -1053,26 +547,34 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
     // --- Tbar (overwrites T).  Tbar is symmetric (the terms a, b and b, a of
     // Gbar are transposes of each other), so only blocks on or below the
     // diagonal are formed and read.
-    if constexpr (!SP) {
-        if (a.paper && !has2b) {   // Tbar += 2 w_k sum_q c_2(q) W_q D_q^2 T D_q^2, read from T before it is overwritten
-            const double c2 = 2.0 * wk;
-            mfma_gemm_nt<3, 3, W>(N3, N3, KKp, Pm, KKp, Qm, KKp, true, [&](int r, int s, W v) {
-                const size_t e = (size_t)r * N3p + s;
-                const double t = double(T[e]);
-                double f = 0.0;
-                if (t != 0.0)
-                    for (int q = 0; q < nq; ++q)
-                        f += a.wq[q] * cfq(2, q) * L.sa[(size_t)(r / 3) * nwe + 1 + q] *
-                             L.sa[(size_t)(s / 3) * nwe + 1 + q];
-                T[e] = W(double(v) + c2 * t * f);
-            });
-        } else {
-            mfma_gemm_nt<3, 3, W>(N3, N3, KKp, Pm, KKp, Qm, KKp, true, [&](int r, int s, W v) { T[(size_t)r * N3p + s] = v; });
+    if (a.paper) {   // 2 w_k sum_q c_2(q) W_q D_q^2 T D_q^2 (with two-body radii: apart), the central column below
+        const double c2 = 2.0 * wk;
+        for (int e = tid; e < N3 * N3; e += blockDim.x) {
+            const int r = e / N3, s = e % N3;
+            if (s > r) continue;
+            const size_t at = (size_t)r * N3p + s;
+            const double t = has2b ? 0.0 : double(T[at]);
+            double f = 0.0;
+            if (t != 0.0)
+                for (int q = 0; q < nq; ++q)
+                    f += a.wq[q] * cfq(2, q) * L.sa[(size_t)(r / 3) * nwe + 1 + q] *
+                         L.sa[(size_t)(s / 3) * nwe + 1 + q];
+            T[at] = W(c2 * t * f);
         }
+        __syncthreads();
+    } else {
+        mfma_gemm_nt<3, 3, W>(N3, N3, KKp, Pm, KKp, Qm, KKp, true, [&](int r, int s, W v) { T[(size_t)r * N3p + s] = v; });
     }
+    for (int e = 9 + tid; e < 3 * N3; e += blockDim.x) {
+        W* const t = T + (size_t)(e / 3) * N3p + e % 3;
+        double c = 0.0;
+        for (int q = 0; q < nq; ++q) c += double(V[(size_t)(e / 3) * ncol + 3 * q + e % 3]);
+        *t = W(double(*t) + c);
+    }
+    __syncthreads();
 
     // --- pair contraction: dE/dp_i and dE/dR~_i (each unordered pair from both ends)
-    const int parts = SP ? 1 : max(1, min(4, (int)blockDim.x / max(nK, 1)));
+    const int parts = max(1, min(4, (int)blockDim.x / max(nK, 1)));
     // the two-body term's pair derivative C2 = kappa T2_ij, kappa = 2 w_k sum_q W_q c_2
     // alpha~_i alpha~_j (central pairs; 4 and every pair for the approximate forces),
     // contracted with dT2/dp_i and, through S~, with dT2/dR~
@@ -1095,225 +597,6 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
         g[2] += gp[2];
         Rb += a.beta * t.fLR * t.dfS * 2.0 * kap * t.A / (r * r * r);   // <C2, T_dip> = 2 kappa A / r^3
     };
-    if constexpr (GS) {
-        // Each unordered coupled pair once (the neighbourhoods of this form are large and
-        // the contraction is bound by the gathers of P and Q rows): pass 1, one block row
-        // i per wavefront over its partners j < i (a prefix of the sorted row), forms
-        // Tbar_ij = P_i Q_j^T, C = Tbar_ij + Tbar_ij^T and the pair's terms (its gradient
-        // with respect to r_i and its R~ term) into the entry's slot of a pair buffer.
-        // Pass 2 sums every row over its partners in list order, reading the partner's
-        // slot (found by binary search in the partner's sorted row) with the gradient's
-        // sign turned for j > i: the gradient of a pair term is odd in rhat, the R~ term
-        // even.  The sums have a fixed order, as in the other forms.  The buffer (four
-        // values of the arithmetic type per entry) takes the place of the entries' T_LR
-        // coefficients, which the products before have used for the last time.
-        W* const pbuf = pA;
-        constexpr int VW = 16 / sizeof(W);
-        typedef W VV __attribute__((ext_vector_type(VW)));
-        const int pu = lane >> 3, pt = lane & 7;
-        for (int i = wave; i < nK; i += nwave) {
-            const int n = row_len(i);
-            const size_t e0 = (size_t)roff[i];
-            int nlo = 0;   // partners below i
-            for (int s0 = 0; s0 < n; s0 += 64) nlo += __popcll(__ballot(s0 + lane < n && pj[e0 + s0 + lane] < i));
-            // eight pairs per step, eight lanes per pair (as in the LDS form)
-            for (int s0 = 0; s0 < nlo; s0 += 8) {
-                const bool okp = s0 + pu < nlo;
-                const int j = pj[e0 + (okp ? s0 + pu : s0)];
-                double sb[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-                for (int kb = 0; kb < KKp; kb += 8 * VW) {
-                    const int kk = kb + VW * pt;
-                    const int ks = kk < KKp ? kk : 0;
-                    const double z = kk < KKp ? 1.0 : 0.0;
-                    VV pv[3], qv[3];
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        pv[c] = *reinterpret_cast<const VV*>(Pm + (size_t)(3 * i + c) * KKp + ks);
-                        qv[c] = *reinterpret_cast<const VV*>(Qm + (size_t)(3 * j + c) * KKp + ks);
-                    }
-#pragma unroll
-                    for (int x = 0; x < 3; ++x)
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-                            double d = 0.0;
-#pragma unroll
-                            for (int v = 0; v < VW; ++v) d += double(pv[x][v]) * double(qv[c][v]);
-                            sb[3 * x + c] += z * d;
-                        }
-                }
-#pragma unroll
-                for (int x = 0; x < 9; ++x) {
-                    sb[x] += __shfl_xor(sb[x], 1);
-                    sb[x] += __shfl_xor(sb[x], 2);
-                    sb[x] += __shfl_xor(sb[x], 4);
-                }
-                if (okp && pt == 0) {
-                    double C[9];
-                    for (int x = 0; x < 3; ++x)
-                        for (int c = 0; c < 3; ++c) C[3 * x + c] = sb[3 * x + c] + sb[3 * c + x];
-                    const double v[3] = {L.px[i] - L.px[j], L.py[i] - L.py[j], L.pz[i] - L.pz[j]};
-                    const double r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-                    const double rcut = (i == 0 || j == 0) ? SI.r_mbd1 : SI.r_mbd2;
-                    const double rh[3] = {v[0] / r, v[1] / r, v[2] / r};
-                    const LrPair<W> lp = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut),
-                                                    W(a.r_buf));
-                    double gp[3];
-                    radial_tensor_grad(rh, r, double(lp.A), double(lp.dA), double(lp.dB), C, gp);
-                    double rCr = 0.0;
-                    for (int x = 0; x < 3; ++x)
-                        for (int c = 0; c < 3; ++c) rCr += rh[x] * C[3 * x + c] * rh[c];
-                    const double ct = (3.0 * rCr - (C[0] + C[4] + C[8])) / (r * r * r);
-                    W* slot = pbuf + (e0 + s0 + pu) * 4;
-                    slot[0] = W(gp[0]);
-                    slot[1] = W(gp[1]);
-                    slot[2] = W(gp[2]);
-                    slot[3] = W(a.beta * double(lp.fLR) * double(lp.dfS) * ct);
-                }
-            }
-        }
-        __syncthreads();   // the pair buffer is complete
-        for (int i = wave; i < nK; i += nwave) {
-            double g[3] = {0.0, 0.0, 0.0};
-            double Rb = 0.0;
-            const int n = row_len(i);
-            const size_t e0 = (size_t)roff[i];
-            for (int s0 = 0; s0 < n; s0 += 64) {
-                // the slot of entry s0 + lane (every lane), then the sums in the order of
-                // eight pairs per step, pair u of a step on lane 8u
-                long long src = -1;
-                bool neg = false;
-                if (s0 + lane < n) {
-                    const int j = pj[e0 + s0 + lane];
-                    if (j < i) {
-                        src = (long long)(e0 + s0 + lane);
-                    } else {
-                        int lo = roff[j], hi = roff[j] + row_len(j);
-                        const int end = hi;
-                        while (lo < hi) {
-                            const int mid = (lo + hi) >> 1;
-                            if (pj[mid] < i) lo = mid + 1;
-                            else hi = mid;
-                        }
-                        if (lo < end && pj[lo] == i) {
-                            src = lo;
-                            neg = true;
-                        } else {   // the coupling relation is symmetric: never taken
-                            atomicOr(a.err, 32);
-                            atomicMin(a.err_atom, k);
-                        }
-                    }
-                }
-                for (int t = 0; t < 8; ++t) {
-                    const int from = 8 * t + pu;
-                    const long long sr = __shfl(src, from);
-                    const bool ng = __shfl((int)neg, from) != 0;
-                    if (pt == 0 && s0 + from < n && sr >= 0) {
-                        const W* slot = pbuf + (size_t)sr * 4;
-                        const double sg = ng ? -1.0 : 1.0;
-                        g[0] += sg * double(slot[0]);
-                        g[1] += sg * double(slot[1]);
-                        g[2] += sg * double(slot[2]);
-                        Rb += double(slot[3]);
-                    }
-                }
-            }
-            {   // the lanes' partial sums, in a fixed order
-                const double part[9] = {g[0], g[1], g[2], Rb, 0.0, 0.0, 0.0, 0.0, 0.0};
-                double tot[9];
-                wave_sum9(part, tot);
-                if (lane == 0) {
-                    L.g[(size_t)i * 3 + 0] = tot[0];
-                    L.g[(size_t)i * 3 + 1] = tot[1];
-                    L.g[(size_t)i * 3 + 2] = tot[2];
-                    L.rb[i] = tot[3];
-                }
-            }
-        }
-    } else if constexpr (SP) {
-        // one block row per wavefront; Tbar_IJ (I > J) of a coupled pair from P and Q
-        for (int i = wave; i < nK; i += nwave) {
-            double g[3] = {0.0, 0.0, 0.0};
-            double Rb = 0.0;
-            const int n = row_len(i);
-            // eight coupled pairs per step, eight lanes per pair: lane 8u + t sums columns
-            // t, t + 8, ... (16 bytes each) of pair u's nine dot products; the eight lanes of
-            // a pair then combine their sums and the pair's first lane takes its tail
-            constexpr int VW = 16 / sizeof(W);
-            typedef W VV __attribute__((ext_vector_type(VW)));
-            const int pu = lane >> 3, pt = lane & 7;
-            for (int s0 = 0; s0 < n; s0 += 8) {
-                const bool okp = s0 + pu < n;
-                const int j = pj[(size_t)roff[i] + (okp ? s0 + pu : s0)];
-                const int I = max(i, j), J = min(i, j);
-                double sb[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-                for (int kb = 0; kb < KKp; kb += 8 * VW) {
-                    const int kk = kb + VW * pt;
-                    const int ks = kk < KKp ? kk : 0;
-                    const double z = kk < KKp ? 1.0 : 0.0;
-                    VV pv[3], qv[3];
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        pv[c] = *reinterpret_cast<const VV*>(Pm + (size_t)(3 * I + c) * KKp + ks);
-                        qv[c] = *reinterpret_cast<const VV*>(Qm + (size_t)(3 * J + c) * KKp + ks);
-                    }
-#pragma unroll
-                    for (int x = 0; x < 3; ++x)
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-                            double d = 0.0;
-#pragma unroll
-                            for (int v = 0; v < VW; ++v) d += double(pv[x][v]) * double(qv[c][v]);
-                            sb[3 * x + c] += z * d;
-                        }
-                }
-#pragma unroll
-                for (int x = 0; x < 9; ++x) {
-                    sb[x] += __shfl_xor(sb[x], 1);
-                    sb[x] += __shfl_xor(sb[x], 2);
-                    sb[x] += __shfl_xor(sb[x], 4);
-                }
-                double myC[9];
-                for (int x = 0; x < 3; ++x)
-                    for (int c = 0; c < 3; ++c) myC[3 * x + c] = sb[3 * x + c] + sb[3 * c + x];
-                const int myj = (okp && pt == 0) ? j : -1;
-                if (myj >= 0) {
-                    const int j = myj;
-                    const double* C = myC;
-                    const double v[3] = {L.px[i] - L.px[j], L.py[i] - L.py[j], L.pz[i] - L.pz[j]};
-                    const double r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-                    const double rcut = (i == 0 || j == 0) ? SI.r_mbd1 : SI.r_mbd2;
-                    const double rh[3] = {v[0] / r, v[1] / r, v[2] / r};
-                    const LrPair<W> lp = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut),
-                                                    W(a.r_buf));
-                    double gp[3];
-                    radial_tensor_grad(rh, r, double(lp.A), double(lp.dA), double(lp.dB), C, gp);
-                    g[0] += gp[0];
-                    g[1] += gp[1];
-                    g[2] += gp[2];
-                    double rCr = 0.0;
-                    for (int x = 0; x < 3; ++x)
-                        for (int c = 0; c < 3; ++c) rCr += rh[x] * C[3 * x + c] * rh[c];
-                    const double ct = (3.0 * rCr - (C[0] + C[4] + C[8])) / (r * r * r);
-                    Rb += a.beta * double(lp.fLR) * double(lp.dfS) * ct;
-                }
-            }
-            {   // the lanes' partial sums, in a fixed order
-                const double part[9] = {g[0], g[1], g[2], Rb, 0.0, 0.0, 0.0, 0.0, 0.0};
-                double tot[9];
-                wave_sum9(part, tot);
-                g[0] = tot[0];
-                g[1] = tot[1];
-                g[2] = tot[2];
-                Rb = tot[3];
-            }
-            if (lane == 0) {
-                L.g[(size_t)i * 3 + 0] = g[0];
-                L.g[(size_t)i * 3 + 1] = g[1];
-                L.g[(size_t)i * 3 + 2] = g[2];
-                L.rb[i] = Rb;
-            }
-        }
-    } else
     for (int t = tid; t < nK * parts; t += blockDim.x) {
         const int i = t % nK, part = t / nK;
         double g[3] = {0.0, 0.0, 0.0};
@@ -1431,47 +714,35 @@ __global__ void __launch_bounds__(FORM != kMbdDense ? kMbdThreadsSparse : kMbdTh
     __syncthreads();
     double* out = a.cf0 + a.site_off[k] * 3;
     const double fconv = -1.0 / kBohr;  // force = -dE/dx per Angstrom
-    if (tid == 0) {
+    if (wave == 0) {
         // moving the central atom changes every r_ik of the blend
-        double c0 = 0.0, c1 = 0.0, c2 = 0.0;
-        for (int i = 1; i < nK; ++i) {
-            c0 += L.fg[(size_t)i * 3 + 0];
-            c1 += L.fg[(size_t)i * 3 + 1];
-            c2 += L.fg[(size_t)i * 3 + 2];
-        }
-        out[0] = fconv * (L.g[0] - c0);
-        out[1] = fconv * (L.g[1] - c1);
-        out[2] = fconv * (L.g[2] - c2);
+        double c[3] = {0.0, 0.0, 0.0};
+        for (int i = 1 + lane; i < nK; i += 64)
+            for (int d = 0; d < 3; ++d) c[d] += L.fg[(size_t)i * 3 + d];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1)
+            for (int d = 0; d < 3; ++d) c[d] += __shfl_xor(c[d], o);
+        if (lane < 3) out[lane] = fconv * (L.g[lane] - (lane == 0 ? c[0] : lane == 1 ? c[1] : c[2]));
     }
     for (int s = 1 + tid; s < nall; s += blockDim.x) {
         const bool in = s < nK;
-        out[3 * s + 0] = in ? fconv * L.g[(size_t)s * 3 + 0] : 0.0;
-        out[3 * s + 1] = in ? fconv * L.g[(size_t)s * 3 + 1] : 0.0;
-        out[3 * s + 2] = in ? fconv * L.g[(size_t)s * 3 + 2] : 0.0;
+        double* const o = out + 3 * (size_t)s;
+        o[0] = in ? fconv * L.g[(size_t)s * 3 + 0] : 0.0;
+        o[1] = in ? fconv * L.g[(size_t)s * 3 + 1] : 0.0;
+        o[2] = in ? fconv * L.g[(size_t)s * 3 + 2] : 0.0;
     }
     for (int e = tid; e < (nall - nK) * nw; e += blockDim.x) cap[(size_t)nK * nw + e] = 0.0;
 }
 
-template <typename W, bool TB>
-static void launch_mbd_t(hipStream_t st, const MbdArgs& a, int nk_lds, size_t lds, int form) {
-    const dim3 grid(a.n), blk(form == kMbdDense ? kMbdThreads : kMbdThreadsSparse);
-    if (form == kMbdDense)
-        hipLaunchKernelGGL((k_mbd<W, kMbdDense, TB>), grid, blk, lds, st, a, nk_lds);
-    else if (form == kMbdSparse)
-        hipLaunchKernelGGL((k_mbd<W, kMbdSparse, TB>), grid, blk, lds, st, a, nk_lds);
-    else
-        hipLaunchKernelGGL((k_mbd<W, kMbdSparseGlobal, TB>), grid, blk, lds, st, a, nk_lds);
-}
-
-hipError_t launch_mbd(hipStream_t st, const MbdArgs& a, int nkmax, bool mixed, int form, bool two_body) {
-    const int nk_lds = form == kMbdSparseGlobal ? 0 : nkmax;   // per-site arrays in LDS or not
-    const size_t lds = mbd_lds_bytes(nk_lds, a.nq, a.n_max, a.lz_steps, a.fit != 0);
+hipError_t launch_mbd_dense(hipStream_t st, const MbdArgs& a, int nkmax, bool mixed, bool two_body) {
+    const size_t lds = mbd_lds_bytes(nkmax, a.nq, a.n_max, a.lz_steps, a.fit != 0);
+    const dim3 grid(a.n), blk(kMbdThreads);
     if (mixed) {
-        if (two_body) launch_mbd_t<float, true>(st, a, nk_lds, lds, form);
-        else launch_mbd_t<float, false>(st, a, nk_lds, lds, form);
+        if (two_body) hipLaunchKernelGGL((k_mbd<float, true>), grid, blk, lds, st, a, nkmax);
+        else hipLaunchKernelGGL((k_mbd<float, false>), grid, blk, lds, st, a, nkmax);
     } else {
-        if (two_body) launch_mbd_t<double, true>(st, a, nk_lds, lds, form);
-        else launch_mbd_t<double, false>(st, a, nk_lds, lds, form);
+        if (two_body) hipLaunchKernelGGL((k_mbd<double, true>), grid, blk, lds, st, a, nkmax);
+        else hipLaunchKernelGGL((k_mbd<double, false>), grid, blk, lds, st, a, nkmax);
     }
     return hipGetLastError();
 }

@@ -1,0 +1,923 @@
+// Local MBD energy and its adjoint in the two-radius regime (Sec. III.A: a site couples to
+// the central atom up to r_MBD,1 but to the others only up to r_MBD,2, so the block rows
+// of T_LR other than the central one are sparse).  The quantities are those of the dense
+// form (k_mbd.hip); here T_LR is kept as lists of coupled sites and one atom is spread
+// over many workgroups, one launch per step:
+//   k_rows_setup     site order, blend, SCS radii                     one workgroup per atom
+//   k_rows_lists     coupled-site lists, u_1                          a row per wavefront
+//   k_rows_product   u_{m+1} = D T D u_m                              block rows per lane group
+//   k_rows_energy    spectrum bounds, moments, energy                 one workgroup per atom
+//   k_rows_operands  polarisability adjoints, operands of Tbar        elementwise
+//   k_rows_pairs     Tbar and gradient of every coupled pair          a row per wavefront
+//   k_rows_sums      pair terms summed per site                       a row per wavefront
+//   k_rows_final     blend adjoint, outputs                           one workgroup per atom
+// All of it is bound by gathers of the partners' rows.  What makes them cheap is where they
+// hit: the sites are ordered along a space-filling curve, so that the rows at work share
+// most of their partners, and the workgroups of one atom are dealt to one XCD one atom
+// after the other, so that this atom's Krylov block (2.1 MB of FP64 for 2,450 sites) and
+// not those of 32 atoms is what the XCD's L2 has to hold.
+//
+// Storage per atom (RowsLayout): the Krylov blocks scaled, P = [D u_1 .. D u_mmax] side by
+// side, which is the products' operand and Tbar's left operand at once; moments and
+// adjoints divide by alpha~ where they need u itself.
+#include <algorithm>
+#include <type_traits>
+
+#include "mbd_common.h"
+
+namespace lmbd {
+
+constexpr int kRowsThreads = 256;    // row kernels: four wavefronts
+constexpr int kRowsWaves = kRowsThreads / 64;
+constexpr int kAtomThreads = 1024;   // one-workgroup-per-atom kernels
+constexpr int kBox = 16;             // slots per bounding box
+constexpr int kRowsPerWave = 3;      // rows of a wavefront in the list, pair and sum kernels
+
+// What every kernel of this file derives from its atom.
+template <typename W>
+struct RowsAtom {
+    typedef W W4 __attribute__((ext_vector_type(4)));
+    int k, nK, n1, nall, N3, N3p, nq, nwe, nw, ncol, ldp, na, ldq, stride, nbox;
+    const StructInfo* SI;
+    const Site* S;
+    MbdLds L;             // site arrays, in the workspace
+    int32_t* slot_site;   // site of each slot
+    uint32_t* keys;       // curve keys per site (setup only)
+    double* boxes;        // bounding boxes of kBox slots
+    W4* rec;              // list entries: s = sqrt(A) rhat and B (T_LR = s s^T + B I; A >= 0)
+    int32_t* pj;          // list entries: slot, ascending in each row
+    int32_t* len;         // entries per row
+    W *P, *V, *Q;
+    __device__ size_t row0(int i) const { return i == 0 ? 0 : (size_t)nK + (size_t)(i - 1) * stride; }
+};
+
+// The atom and part of workgroup b when every atom has `parts` workgroups: an atom's
+// workgroups all on one XCD (workgroups go to the eight XCDs in turn), one after the other.
+__device__ inline void rows_place(int b, int parts, int& slot, int& part) {
+    const int xcd = b & 7, loc = b >> 3;
+    slot = (loc / parts) * 8 + xcd;
+    part = loc % parts;
+}
+
+template <typename W>
+__device__ inline RowsAtom<W> rows_atom(const MbdArgs& a, int k, double* small) {
+    RowsAtom<W> R;
+    const Counts cnt = a.counts[k];
+    R.k = k;
+    R.nK = cnt.nK;
+    R.n1 = cnt.n1;
+    R.nall = cnt.n_all;
+    R.N3 = 3 * R.nK;
+    R.N3p = (R.N3 + 3) / 4 * 4;
+    R.nq = a.nq;
+    R.nwe = a.nq + 1;
+    R.nw = a.nw;
+    R.ncol = a.ncol;
+    R.ldp = a.mmax * a.ncol;
+    R.na = a.forces ? max(a.n_max - 2, 0) : 0;
+    R.ldq = R.na * a.ncol;
+    R.SI = &a.sinfo[a.atom_struct[k]];
+    R.S = a.sites + a.site_off[k];
+    R.stride = rows_stride(R.nK, R.SI->m2max);
+    const RowsLayout G = rows_layout(R.nK, R.SI->m2max, R.nq, a.n_max, a.mmax, (int64_t)sizeof(W), a.forces != 0);
+    W* const w = static_cast<W*>(a.work) + a.work_off[k];
+    R.L = mbd_lds(reinterpret_cast<double*>(w + G.sites), R.nK, R.nq, small, a.n_max, a.fit != 0);
+    // slots, keys and boxes take the parts of L.rb beyond the first
+    R.slot_site = reinterpret_cast<int32_t*>(R.L.rb + R.nK);
+    R.keys = reinterpret_cast<uint32_t*>(R.slot_site + R.nK);
+    R.boxes = R.L.rb + 2 * (size_t)R.nK;
+    R.nbox = (R.nK + kBox - 1) / kBox;
+    const int64_t cap = rows_cap(R.nK, R.SI->m2max);
+    R.rec = reinterpret_cast<typename RowsAtom<W>::W4*>(w + G.lists);
+    R.pj = reinterpret_cast<int32_t*>(R.rec + cap);
+    R.len = R.pj + cap;
+    R.P = w + G.P;
+    R.V = w + G.V;
+    R.Q = w + G.Q;
+    return R;
+}
+
+// whether the pair (i, j) couples (central pairs out to the two-body radius too: their MBD
+// coefficients are 0 there)
+template <typename W, bool TB>
+__device__ inline bool rows_coupled(const RowsAtom<W>& R, int i, int j, double v[3], double& r) {
+    if (j >= R.nK || j == i) return false;
+    v[0] = R.L.px[i] - R.L.px[j];
+    v[1] = R.L.py[i] - R.L.py[j];
+    v[2] = R.L.pz[i] - R.L.pz[j];
+    r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+    const StructInfo& SI = *R.SI;
+    return r < ((i == 0 || j == 0) ? (TB ? fmax(SI.r_mbd1, SI.r_2b1) : SI.r_mbd1) : SI.r_mbd2);
+}
+
+// ---------------------------------------------------------------------------
+// Slots along the curve, blended polarisabilities, SCS radii, bounding boxes.
+// ---------------------------------------------------------------------------
+template <typename W>
+__global__ void __launch_bounds__(kAtomThreads) k_rows_setup(MbdArgs a) {
+    const int k = a.order[blockIdx.x], tid = threadIdx.x;
+    const RowsAtom<W> R = rows_atom<W>(a, k, nullptr);
+    const MbdLds& L = R.L;
+    const StructInfo& SI = *R.SI;
+    const int nK = R.nK, n1 = R.n1, nw = a.nw, nq = a.nq, nwe = R.nwe;
+    const double rs = SI.r_scs;
+    const double* aloc = a.alpha_loc + a.aloc_off[k];
+    // Morton keys of a grid over the ball; the central atom takes slot 0, the others follow
+    // by (key, site): a fixed order, found by counting (the neighbourhoods are small)
+    auto spread = [](uint32_t x) -> uint32_t {   // bits of x (10) to every third bit
+        x &= 0x3ffu;
+        x = (x | (x << 16)) & 0x030000ffu;
+        x = (x | (x << 8)) & 0x0300f00fu;
+        x = (x | (x << 4)) & 0x030c30c3u;
+        return (x | (x << 2)) & 0x09249249u;
+    };
+    const double h = fmax(2.0, SI.r_nbr / 511.0);   // bohr per step of the grid
+    auto step = [&](double x) -> uint32_t { return (uint32_t)min(max((int)((x + SI.r_nbr) / h), 0), 1023); };
+    for (int s = tid; s < nK; s += blockDim.x)
+        R.keys[s] = spread(step(R.S[s].x)) | (spread(step(R.S[s].y)) << 1) | (spread(step(R.S[s].z)) << 2);
+    if (tid == 0) R.slot_site[0] = 0;
+    __syncthreads();
+    for (int s = 1 + tid; s < nK; s += blockDim.x) {
+        const uint32_t ks = R.keys[s];
+        int rank = 1;
+        for (int t = 1; t < nK; ++t) {
+            const uint32_t kt = R.keys[t];
+            rank += (kt < ks || (kt == ks && t < s)) ? 1 : 0;
+        }
+        R.slot_site[rank] = s;
+    }
+    __syncthreads();
+    for (int s = tid; s < nK; s += blockDim.x) {
+        const int si = R.slot_site[s];
+        const Site st = R.S[si];
+        L.px[s] = st.x;
+        L.py[s] = st.y;
+        L.pz[s] = st.z;
+        const double r = sqrt(st.x * st.x + st.y * st.y + st.z * st.z);
+        const double* cen = a.alpha_loc + a.aloc_off[st.base];  // row 0 = central value
+        double fsv = 1.0, dfsv = 0.0;
+        if (s == 0) {
+            fsv = 0.0;
+        } else if (si < n1) {
+            const double x = r / rs;
+            fsv = 3.0 * x * x - 2.0 * x * x * x;
+            dfsv = (6.0 * x - 6.0 * x * x) / rs;
+        }
+        L.fs[s] = fsv;
+        L.dfs[s] = dfsv;
+        const double* al = aloc + (size_t)si * nw;
+        if (a.lorentz) {
+            const double a0 = (s == 0) ? aloc[0] : (si < n1) ? (1.0 - fsv) * al[0] + fsv * cen[0] : cen[0];
+            const double ar = (s == 0) ? aloc[1] : (si < n1) ? (1.0 - fsv) * al[1] + fsv * cen[1] : cen[1];
+            if (!(ar > 0.0 && a0 >= ar)) {   // no real characteristic frequency
+                atomicOr(a.err, 8);
+                atomicMin(a.err_atom, k);
+            }
+            L.sa[(size_t)s * nwe] = a0;
+            for (int q = 0; q < nq; ++q) {
+                const double v = a0 * ar / (a.rho[q] * a0 + (1.0 - a.rho[q]) * ar);
+                L.sa[(size_t)s * nwe + 1 + q] = v;
+                L.sqa[(size_t)s * nq + q] = sqrt(v);
+            }
+        } else {
+            for (int w = 0; w < nw; ++w) {
+                const double lo = (si < n1) ? al[w] : 0.0;
+                const double v = (s == 0) ? lo : (1.0 - fsv) * lo + fsv * cen[w];
+                L.sa[(size_t)s * nwe + w] = v;
+                if (w > 0) L.sqa[(size_t)s * nq + (w - 1)] = sqrt(v);
+            }
+        }
+        L.Rt[s] = a.r0v[st.base] * cbrt(L.sa[(size_t)s * nwe] / a.a0v[st.base]);
+    }
+    if (nK <= 64) return;   // the lists test every pair: no boxes
+    __syncthreads();
+    for (int b = tid; b < R.nbox; b += blockDim.x) {
+        double lo[3], hi[3];
+        for (int s = kBox * b; s < min(kBox * (b + 1), nK); ++s) {
+            const double x[3] = {L.px[s], L.py[s], L.pz[s]};
+            for (int d = 0; d < 3; ++d) {
+                lo[d] = s == kBox * b ? x[d] : fmin(lo[d], x[d]);
+                hi[d] = s == kBox * b ? x[d] : fmax(hi[d], x[d]);
+            }
+        }
+        for (int d = 0; d < 3; ++d) {
+            R.boxes[6 * b + d] = lo[d];
+            R.boxes[6 * b + 3 + d] = hi[d];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Coupled sites of every block row and their coefficients, ascending in the slot, and the
+// row of D u_1 (u_1 = D T D e_k needs the central block column only).  A wavefront per
+// row, its lanes testing four boxes of 16 slots at a time: the first box (the central
+// atom) and those that reach within r_mbd2 (all of them for the central row).  Row i has
+// space for every site within r_mbd2 of the structure's fullest atom, so the rows need no
+// counting pass.
+// ---------------------------------------------------------------------------
+template <typename W, bool TB>
+__global__ void __launch_bounds__(kRowsThreads) k_rows_lists(MbdArgs a, int parts) {
+    int at, part;
+    rows_place(blockIdx.x, parts, at, part);
+    if (at >= a.n) return;
+    typedef typename RowsAtom<W>::W4 W4;
+    const RowsAtom<W> R = rows_atom<W>(a, a.order[at], nullptr);
+    const MbdLds& L = R.L;
+    const StructInfo& SI = *R.SI;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nK = R.nK, nq = a.nq, ncol = a.ncol;
+    const double rcull = SI.r_mbd2 * SI.r_mbd2 * (1.0 + 1e-9);
+    const int i0 = (part * kRowsWaves + wave) * kRowsPerWave;
+    for (int i = i0; i < min(i0 + kRowsPerWave, nK); ++i) {
+        const size_t e0 = R.row0(i);
+        const int cap = i == 0 ? nK : R.stride;
+        int n = 0;
+        bool central = false;            // the row's first entry is the central atom
+        W4 r0 = {W(0), W(0), W(0), W(0)};
+        for (int b0 = 0; b0 < R.nbox; b0 += 64) {
+            const int b = b0 + lane;
+            bool near = b < R.nbox;
+            if (near && i != 0 && b != 0 && nK > 64) {
+                const double* bx = R.boxes + 6 * b;
+                const double dx = fmax(0.0, fmax(bx[0] - L.px[i], L.px[i] - bx[3]));
+                const double dy = fmax(0.0, fmax(bx[1] - L.py[i], L.py[i] - bx[4]));
+                const double dz = fmax(0.0, fmax(bx[2] - L.pz[i], L.pz[i] - bx[5]));
+                near = dx * dx + dy * dy + dz * dz < rcull;
+            }
+            unsigned long long m = __ballot(near);
+            while (m) {
+                int box = 0;
+                bool have = false;
+#pragma unroll
+                for (int u = 0; u < 64 / kBox; ++u) {   // the next four near boxes
+                    const int bit = m ? __ffsll((long long)m) - 1 : -1;
+                    m &= m - 1;
+                    if (lane / kBox == u) {
+                        have = bit >= 0;
+                        box = b0 + max(bit, 0);
+                    }
+                }
+                const int j = have ? kBox * box + lane % kBox : nK;
+                double v[3], r;
+                W4 e = {W(0), W(0), W(0), W(0)};
+                const bool in = rows_coupled<W, TB>(R, i, j, v, r);
+                if (in) {
+                    const double rcut = (i == 0 || j == 0) ? SI.r_mbd1 : SI.r_mbd2;
+                    const LrPair<W> t = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut),
+                                                   W(a.r_buf));
+                    const double sA = sqrt(fmax(double(t.A), 0.0)) / r;
+                    e = W4{W(sA * v[0]), W(sA * v[1]), W(sA * v[2]), t.B};
+                }
+                const unsigned long long mask = __ballot(in);
+                const int at_e = n + __popcll(mask & ((1ull << lane) - 1ull));
+                if (in && at_e < cap) {
+                    R.pj[e0 + at_e] = j;
+                    R.rec[e0 + at_e] = e;
+                }
+                if (b0 == 0 && n == 0 && i != 0) {   // lane 0 of the first step tests the central atom
+                    const bool first = (mask & 1ull) != 0 && __shfl(j, 0) == 0;
+                    if (first) {
+                        central = true;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) r0[c] = __shfl(e[c], 0);
+                    }
+                }
+                n += __popcll(mask);
+            }
+        }
+        if (n > cap && lane == 0) {   // the row outgrew its bound: refuse the call
+            atomicOr(a.err, 32);
+            atomicMin(a.err_atom, R.k);
+        }
+        if (lane == 0) R.len[i] = min(n, cap);
+        for (int col = lane; col < ncol; col += 64) {
+            const int q = col / 3, c = col % 3;
+            const double si = L.sqa[(size_t)i * nq + q];
+            const double s = central ? si * si * L.sqa[q] : 0.0;
+            for (int x = 0; x < 3; ++x)
+                R.P[(size_t)(3 * i + x) * R.ldp + col] =
+                    W(s * (double(r0[x]) * double(c == 0 ? r0[0] : c == 1 ? r0[1] : r0[2]) + (x == c ? double(r0[3]) : 0.0)));
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// D u_{m+1} = D^2 T (D u_m).  A wavefront holds ng groups of nl lanes, a lane VW
+// consecutive columns (16-byte loads: 18 lanes and three groups for 36 FP64 columns, nine
+// and seven for FP32); each group walks a block row of its own, the rows side by side on
+// the curve.  The central row is longer than the others: its entries are dealt to the
+// groups of one wavefront and the parts summed in order.
+// ---------------------------------------------------------------------------
+template <typename W, int VW>
+__global__ void __launch_bounds__(kRowsThreads) k_rows_product(MbdArgs a, int parts, int m) {
+    int at, part;
+    rows_place(blockIdx.x, parts, at, part);
+    if (at >= a.n) return;
+    typedef typename RowsAtom<W>::W4 W4;
+    typedef W VV __attribute__((ext_vector_type(VW)));
+    const RowsAtom<W> R = rows_atom<W>(a, a.order[at], nullptr);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nK = R.nK, nq = a.nq, ncol = a.ncol;
+    const size_t ldp = R.ldp;
+    const int nlt = ncol / VW;                           // lanes of all columns
+    const int nl = min(nlt, 64), ng = 64 / nl;
+    const int g = lane / nl;
+    const int nrow = 1 + (nK - 1 + ng - 1) / ng;         // items per column chunk: the central row, then ng rows each
+    const int it = part * kRowsWaves + wave;
+    if (it >= nrow * ((nlt + 63) / 64)) return;
+    const int rit = it % nrow;
+    const int cl = (it / nrow) * 64 + lane - g * nl;
+    const bool okc = g < ng && cl < nlt;
+    const int col = okc ? VW * cl : 0;
+    const bool split = rit == 0;                         // uniform
+    const int i = split ? 0 : 1 + (rit - 1) * ng + g;
+    const bool okr = okc && i < nK;
+    const int n = okr ? R.len[i] : 0;
+    const size_t e0 = okr ? R.row0(i) : 0;
+    const int first = split ? g : 0, inc = split ? ng : 1;
+    VV acc0 = VV(W(0)), acc1 = VV(W(0)), acc2 = VV(W(0));
+    const W* const vc = R.P + (size_t)(m - 1) * ncol + col;
+    // two entries per step; an entry past the row's end reads its first entry with a zero
+    // factor, so that the loads of a step overlap
+    for (int s = first; s < n; s += 2 * inc) {
+        const size_t ea = e0 + s, eb = e0 + (s + inc < n ? s + inc : s);
+        const W4 ra = R.rec[ea];
+        W4 rb = R.rec[eb];
+        const int ja = R.pj[ea], jb = R.pj[eb];
+        const W* va = vc + (size_t)(3 * ja) * ldp;
+        const W* vb = vc + (size_t)(3 * jb) * ldp;
+        const VV a0 = *reinterpret_cast<const VV*>(va), a1 = *reinterpret_cast<const VV*>(va + ldp),
+                 a2 = *reinterpret_cast<const VV*>(va + 2 * ldp);
+        const VV b0 = *reinterpret_cast<const VV*>(vb), b1 = *reinterpret_cast<const VV*>(vb + ldp),
+                 b2 = *reinterpret_cast<const VV*>(vb + 2 * ldp);
+        if (s + inc >= n) rb = W4{W(0), W(0), W(0), W(0)};
+        const VV da = ra[0] * a0 + ra[1] * a1 + ra[2] * a2;
+        acc0 += ra[0] * da + ra[3] * a0;
+        acc1 += ra[1] * da + ra[3] * a1;
+        acc2 += ra[2] * da + ra[3] * a2;
+        const VV db = rb[0] * b0 + rb[1] * b1 + rb[2] * b2;
+        acc0 += rb[0] * db + rb[3] * b0;
+        acc1 += rb[1] * db + rb[3] * b1;
+        acc2 += rb[2] * db + rb[3] * b2;
+    }
+    if (split) {   // the groups' parts, in order
+        VV t0 = acc0, t1 = acc1, t2 = acc2;
+        for (int gg = 1; gg < ng; ++gg)
+#pragma unroll
+            for (int v = 0; v < VW; ++v) {
+                const int from = (lane + gg * nl) & 63;
+                const W x0 = __shfl(acc0[v], from), x1 = __shfl(acc1[v], from), x2 = __shfl(acc2[v], from);
+                t0[v] += x0;
+                t1[v] += x1;
+                t2[v] += x2;
+            }
+        acc0 = t0;
+        acc1 = t1;
+        acc2 = t2;
+    }
+    if (okr && (!split || g == 0)) {
+        VV al;
+#pragma unroll
+        for (int v = 0; v < VW; ++v) al[v] = W(R.L.sa[(size_t)i * R.nwe + 1 + (col + v) / 3]);
+        W* const vo = R.P + (size_t)(3 * i) * ldp + (size_t)m * ncol + col;
+        *reinterpret_cast<VV*>(vo) = al * acc0;
+        *reinterpret_cast<VV*>(vo + ldp) = al * acc1;
+        *reinterpret_cast<VV*>(vo + 2 * ldp) = al * acc2;
+    }
+}
+
+// T2 of the pair (i, j) at the two-body radii
+template <typename W>
+__device__ inline bool rows_t2(const MbdArgs& a, const RowsAtom<W>& R, int i, int j, double& r, double rh[3],
+                               LrPair<double>& t) {
+    const MbdLds& L = R.L;
+    const double v[3] = {L.px[i] - L.px[j], L.py[i] - L.py[j], L.pz[i] - L.pz[j]};
+    r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+    const double rc = (i == 0 || j == 0) ? R.SI->r_2b1 : R.SI->r_2b2;
+    if (i == j || !(r < rc)) return false;
+    t = lr_pair<double>(r, a.beta * (L.Rt[i] + L.Rt[j]), a.damp_d, rc, a.r_buf);
+    rh[0] = v[0] / r;
+    rh[1] = v[1] / r;
+    rh[2] = v[2] / r;
+    return true;
+}
+
+// <u_a, u_b> of site i at node q, times alpha~_i(q)
+template <typename W>
+__device__ inline double rows_dot(const RowsAtom<W>& R, int i, int q, int x, int y) {
+    const W* p = R.P + (size_t)(3 * i) * R.ldp + 3 * q;
+    const size_t ox = (size_t)(x - 1) * R.ncol, oy = (size_t)(y - 1) * R.ncol;
+    double d = 0.0;
+    for (int r = 0; r < 3; ++r, p += R.ldp)
+        for (int c = 0; c < 3; ++c) d += double(p[ox + c]) * double(p[oy + c]);
+    return d;
+}
+
+// dE/d alpha~_i(w_q) from the moments (row-local Krylov products); mu: the moments (the
+// central site only)
+template <typename W, bool TB, class CF>
+__device__ inline double rows_alpha_adjoint(const MbdArgs& a, const RowsAtom<W>& R, double wk, int i, int q,
+                                            const double* mu, CF cfq) {
+    const double al = R.L.sa[(size_t)i * R.nwe + 1 + q];
+    double s = 0.0;
+    for (int n = 2; n <= a.n_max; ++n) {
+        const double sn = (i == 0) ? mu[n * R.nq + q] : 0.0;
+        if (n == 2 && TB) {   // alpha~_k alpha~_i t2_i (the central term is mu_2 itself)
+            s += cfq(n, q) * (i > 0 ? R.L.sa[1 + q] * al * R.L.fg[i] : sn);
+            continue;
+        }
+        // sum over x = 1 .. n-1 of the row block of u_x u_{n-x}^T: the terms x and n - x
+        // are equal, so each unordered pair is formed once
+        double pr = 0.0;
+        for (int x = 1; 2 * x <= n; ++x) {
+            const double d = rows_dot(R, i, q, x, n - x);
+            pr += (2 * x == n) ? d : 2.0 * d;
+        }
+        s += cfq(n, q) * (sn + pr / al);
+    }
+    return wk * a.wq[q] * s / al;
+}
+
+// Adjoints of the polarisabilities (sites other than the central one), Q = W D Z and the
+// u_0 terms of Tbar's central block column (into V: nine values per site, see k_mbd.hip),
+// by threads t = first, first + step, ..
+template <typename W, bool TB, class CF>
+__device__ inline void rows_operands(const MbdArgs& a, const RowsAtom<W>& R, double wk, int first, int step, CF cfq) {
+    const MbdLds& L = R.L;
+    const int nq = R.nq, ncol = R.ncol, n_max = a.n_max;
+    for (int t = first; t < R.nK * R.nwe; t += step) {
+        const int i = t / R.nwe, w = t % R.nwe;
+        if (i == 0 && w > 0) continue;   // with the moments, in k_rows_energy
+        L.ab[t] = w == 0 ? 0.0 : rows_alpha_adjoint<W, TB>(a, R, wk, i, w - 1, nullptr, cfq);
+    }
+    if (R.na > 0)
+        for (int t = first; t < R.N3 * ncol; t += step) {
+            const int r = t / ncol, col = t % ncol, q = col / 3;
+            const double scale = wk * a.wq[q];
+            const W* pr = R.P + (size_t)r * R.ldp + col;
+            W* qr = R.Q + (size_t)r * R.ldq + col;
+            double u[kMaxNmax - 1];
+#pragma unroll
+            for (int b = 1; b < kMaxNmax - 1; ++b) u[b] = b <= R.na ? double(pr[(size_t)(b - 1) * ncol]) : 0.0;
+#pragma unroll
+            for (int x = 1; x < kMaxNmax - 1; ++x) {
+                if (x > R.na) break;
+                double z = 0.0;
+#pragma unroll
+                for (int b = 1; b < kMaxNmax - 1; ++b)
+                    if (b <= n_max - 1 - x) z += cfq(min(x + b + 1, kMaxNmax), q) * u[b];
+                qr[(size_t)(x - 1) * ncol] = W(scale * z);
+            }
+        }
+    for (int t = 9 + first; t < 3 * R.N3; t += step) {
+        const W* p = R.P + (size_t)(t / 3) * R.ldp + t % 3;
+        double s = 0.0;
+        for (int q = 0; q < nq; ++q) {
+            double z = 0.0;
+            for (int b = 1; b <= n_max - 1; ++b)
+                z += ((TB && b == 1) ? 0.0 : cfq(b + 1, q)) * double(p[(size_t)(b - 1) * ncol + 3 * q]);
+            s += a.wq[q] * L.sqa[q] * z;
+        }
+        R.V[t] = W(wk * s);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Spectrum bounds and fitted coefficients, moments, energy, and the central site's
+// adjoints; with fitted coefficients or two-body radii (whose state stays in this
+// workgroup) also the operands.
+// ---------------------------------------------------------------------------
+template <typename W, bool TB>
+__global__ void __launch_bounds__(kAtomThreads) k_rows_energy(MbdArgs a) {
+    extern __shared__ double lds[];
+    const int k = a.order[blockIdx.x], tid = threadIdx.x;
+    const RowsAtom<W> R = rows_atom<W>(a, k, lds);
+    const MbdLds& L = R.L;
+    const int nK = R.nK, nq = a.nq, n_max = a.n_max, nwe = R.nwe;
+    const int lane = tid & 63, wave = tid >> 6, nwave = blockDim.x >> 6;
+    const bool fit = a.fit != 0;
+    double* const cfn = L.cf + (size_t)(kMaxNmax + 1) * nq;
+    auto cfq = [&](int n, int q) -> double { return fit ? cfn[n * nq + q] : a.coef[n]; };
+    if (a.lz_steps > 0)
+        lanczos_fit<W>(
+            a, k, R.N3, R.N3p, L, R.V,
+            [&](int r) { return lanczos_start(*R.SI, k, R.S[R.slot_site[r / 3]], r); }, [](int, int, W) {},
+            [&](const W* Vin, W* Vout) {
+                // one block row per wavefront, lanes over the nodes, the row's sites in order
+                const int q = lane < nq ? lane : 0;
+                for (int i = wave; i < nK; i += nwave) {
+                    const int n = R.len[i];
+                    const size_t e0 = R.row0(i);
+                    W acc0 = W(0), acc1 = W(0), acc2 = W(0);
+                    for (int t = 0; t < n; ++t) {
+                        const int j = R.pj[e0 + t];
+                        const typename RowsAtom<W>::W4 rc = R.rec[e0 + t];
+                        const W sj = W(L.sqa[(size_t)j * nq + q]);
+                        const W* x = Vin + (size_t)q * R.N3p + 3 * j;
+                        const W x0 = sj * x[0], x1 = sj * x[1], x2 = sj * x[2];
+                        const W ax = rc[0] * x0 + rc[1] * x1 + rc[2] * x2;
+                        acc0 += ax * rc[0] + rc[3] * x0;
+                        acc1 += ax * rc[1] + rc[3] * x1;
+                        acc2 += ax * rc[2] + rc[3] * x2;
+                    }
+                    if (lane < nq) {
+                        const W si = W(L.sqa[(size_t)i * nq + q]);
+                        W* y = Vout + (size_t)q * R.N3p + 3 * i;
+                        y[0] = si * acc0;
+                        y[1] = si * acc1;
+                        y[2] = si * acc2;
+                    }
+                }
+                __syncthreads();
+            });
+    // moments mu_n(q) = <u_x, u_y>, x + y = n: eight moments (consecutive in the node) per
+    // wavefront, eight lanes per moment over the sites, the wavefronts in `rs` ranges of
+    // sites; combined by lane exchanges and over the ranges in a fixed order
+    const int nmom = (n_max - 1) * nq;
+    const int sets = (nmom + 7) / 8, rs = max(1, nwave / sets);
+    double* const parts = lds + mbd_small_doubles(nq, n_max, a.lz_steps, fit);   // [rs][(n_max + 1) nq]
+    for (int w0 = wave; w0 < sets * rs; w0 += nwave) {
+        const int range = w0 / sets;
+        const int t = 8 * (w0 % sets) + (lane & 7), part = lane >> 3;
+        double s = 0.0;
+        if (t < nmom) {
+            const int n = 2 + t / nq, q = t % nq;
+            const int ia = n / 2, ib = n - ia;
+            for (int i = part + 8 * range; i < nK; i += 8 * rs)
+                s += rows_dot(R, i, q, ia, ib) / L.sa[(size_t)i * nwe + 1 + q];
+        }
+        s += __shfl_xor(s, 8);
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        if (t < nmom && part == 0) parts[(size_t)range * (n_max + 1) * nq + 2 * nq + t] = s;
+    }
+    __syncthreads();
+    for (int t = 2 * nq + tid; t < (n_max + 1) * nq; t += blockDim.x) {
+        double s = 0.0;
+        for (int range = 0; range < rs; ++range) s += parts[(size_t)range * (n_max + 1) * nq + t];
+        L.mu[t] = s;
+    }
+    __syncthreads();
+    if constexpr (TB) {
+        // two-body radii: t2_j = |T2_kj|^2 (into the space of the blend gradients), then
+        // mu_2 = alpha~_k sum_j alpha~_j t2_j per node, in site order over the lanes of one
+        // wavefront per node
+        for (int j = tid; j < nK; j += blockDim.x) {
+            double r, rh[3];
+            LrPair<double> t;
+            L.fg[j] = rows_t2(a, R, 0, j, r, rh, t) ? (t.A + t.B) * (t.A + t.B) + 2.0 * t.B * t.B : 0.0;
+        }
+        __syncthreads();
+        for (int q = wave; q < nq; q += nwave) {
+            double x = 0.0;
+            for (int j = lane; j < nK; j += 64) x += L.sa[(size_t)j * nwe + 1 + q] * L.fg[j];
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
+            if (lane == 0) L.mu[2 * nq + q] = L.sa[1 + q] * x;
+        }
+        __syncthreads();
+    }
+    const double wk = a.e_weight ? a.e_weight[k] : 1.0;
+    if (tid == 0) {
+        double e = 0.0;
+        for (int q = 0; q < nq; ++q) {
+            double eq = 0.0;
+            for (int n = 2; n <= n_max; ++n) eq += cfq(n, q) * L.mu[n * nq + q];
+            e += a.wq[q] * eq;
+        }
+        a.e_atom[k] = e;
+    }
+    if (!a.forces) return;
+    if (tid < nq) L.ab[1 + tid] = rows_alpha_adjoint<W, TB>(a, R, wk, 0, tid, L.mu, cfq);
+    if (!(fit || TB)) return;   // k_rows_operands follows
+    if (fit) rows_operands<W, TB>(a, R, wk, tid, blockDim.x, [&](int n, int q) { return L.cf[q * (kMaxNmax + 1) + n]; });
+    else rows_operands<W, TB>(a, R, wk, tid, blockDim.x, [&](int n, int) { return a.coef[n]; });
+    if constexpr (TB) {
+        // the two-body term's pair derivative C2 = kappa T2_kj, kappa = 2 w_k sum_q W_q c_2
+        // alpha~_k alpha~_j, contracted with dT2/dp and, through S~, with dT2/dR~: the central
+        // pairs from both ends; the gradient waits in the space of the blend gradients, the
+        // radius term goes straight into the adjoint of alpha~(0)
+        __syncthreads();
+        for (int i = tid; i < nK; i += blockDim.x) {
+            double g[3] = {0.0, 0.0, 0.0}, Rb = 0.0;
+            auto add = [&](int j) {
+                double r, rh[3];
+                LrPair<double> t;
+                if (!rows_t2(a, R, i, j, r, rh, t)) return;
+                double kap = 0.0;
+                for (int q = 0; q < nq; ++q)
+                    kap += a.wq[q] * cfq(2, q) * L.sa[(size_t)i * nwe + 1 + q] * L.sa[(size_t)j * nwe + 1 + q];
+                kap *= 2.0 * wk;
+                double C[9];
+                for (int x = 0; x < 3; ++x)
+                    for (int c = 0; c < 3; ++c) C[3 * x + c] = kap * (t.A * rh[x] * rh[c] + (x == c ? t.B : 0.0));
+                double gp[3];
+                radial_tensor_grad(rh, r, t.A, t.dA, t.dB, C, gp);
+                for (int d = 0; d < 3; ++d) g[d] += gp[d];
+                Rb += a.beta * t.fLR * t.dfS * 2.0 * kap * t.A / (r * r * r);   // <C2, T_dip> = 2 kappa A / r^3
+            };
+            if (i == 0)
+                for (int j = 1; j < nK; ++j) add(j);
+            else
+                add(0);
+            for (int d = 0; d < 3; ++d) L.fg[(size_t)i * 3 + d] = g[d];
+            L.ab[(size_t)i * nwe] = Rb * L.Rt[i] / (3.0 * L.sa[(size_t)i * nwe]);
+        }
+    }
+}
+
+template <typename W>
+__global__ void __launch_bounds__(kRowsThreads) k_rows_operands(MbdArgs a, int parts) {
+    int at, part;
+    rows_place(blockIdx.x, parts, at, part);
+    if (at >= a.n) return;
+    const int k = a.order[at];
+    const RowsAtom<W> R = rows_atom<W>(a, k, nullptr);
+    const double wk = a.e_weight ? a.e_weight[k] : 1.0;
+    rows_operands<W, false>(a, R, wk, part * kRowsThreads + threadIdx.x, parts * kRowsThreads,
+                            [&](int n, int) { return a.coef[n]; });
+}
+
+// ---------------------------------------------------------------------------
+// Each unordered coupled pair once: from row i over its partners j < i (a prefix of the
+// row), Tbar_ij = P_i Q_j^T (and the u_0 terms for j = 0), C = Tbar_ij + Tbar_ij^T, and
+// the pair's terms (its gradient with respect to r_i and its R~ term) into the entry's
+// slot of a buffer, in the place of its T_LR coefficients (used for the last time by the
+// products).  A wavefront per row: eight pairs at a time, eight lanes per pair (16 bytes
+// of a row each, P_i from LDS); the pairs' C wait in LDS so that the evaluation of the
+// radial parts, far longer than a pair's sums, runs with a pair on every lane.
+// ---------------------------------------------------------------------------
+template <typename W, int VW>
+__global__ void __launch_bounds__(kRowsThreads) k_rows_pairs(MbdArgs a, int parts) {
+    extern __shared__ double lds[];
+    int at, part;
+    rows_place(blockIdx.x, parts, at, part);
+    if (at >= a.n) return;
+    typedef W VV __attribute__((ext_vector_type(VW)));
+    const RowsAtom<W> R = rows_atom<W>(a, a.order[at], nullptr);
+    const MbdLds& L = R.L;
+    const StructInfo& SI = *R.SI;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nK = R.nK, KK = R.ldq;
+    double* const cb = lds + (size_t)wave * 64 * 7;      // six values of C per pair, padded to seven
+    W* const pi = reinterpret_cast<W*>(lds + kRowsWaves * 64 * 7) + (size_t)wave * ((3 * KK + 3) / 4 * 4);
+    const int pu = lane >> 3, pt = lane & 7;
+    const int i0 = (part * kRowsWaves + wave) * kRowsPerWave;
+    for (int i = i0; i < min(i0 + kRowsPerWave, nK); ++i) {
+        const int n = R.len[i];
+        const size_t e0 = R.row0(i);
+        int nlo = 0;   // partners below i
+        for (int s0 = 0; s0 < n; s0 += 64) nlo += __popcll(__ballot(s0 + lane < n && R.pj[e0 + s0 + lane] < i));
+        if (nlo == 0) continue;   // uniform
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        for (int e = VW * lane; e < 3 * KK; e += VW * 64)
+            *reinterpret_cast<VV*>(pi + e) = *reinterpret_cast<const VV*>(R.P + (size_t)(3 * i + e / KK) * R.ldp + e % KK);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        for (int c0 = 0; c0 < nlo; c0 += 64) {
+            const int m = min(64, nlo - c0);
+            const int jl = R.pj[e0 + c0 + min(lane, m - 1)];   // the partner of this lane's pair
+            for (int s0 = 0; s0 < m; s0 += 8) {
+                const int j = __shfl(jl, min(s0 + pu, m - 1));
+                const W* qj = R.Q + (size_t)(3 * j) * R.ldq;
+                double sb[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+                for (int kk = VW * pt; kk < KK; kk += 8 * VW) {
+                    VV pv[3], qv[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        pv[c] = *reinterpret_cast<const VV*>(pi + c * KK + kk);
+                        qv[c] = *reinterpret_cast<const VV*>(qj + (size_t)c * R.ldq + kk);
+                    }
+#pragma unroll
+                    for (int x = 0; x < 3; ++x)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+#pragma unroll
+                            for (int v = 0; v < VW; ++v) sb[3 * x + c] += double(pv[x][v]) * double(qv[c][v]);
+                        }
+                }
+#pragma unroll
+                for (int x = 0; x < 9; ++x) {
+                    sb[x] += __shfl_xor(sb[x], 1);
+                    sb[x] += __shfl_xor(sb[x], 2);
+                    sb[x] += __shfl_xor(sb[x], 4);
+                }
+                if (pt == 0 && s0 + pu < m) {
+                    if (j == 0) {   // the central column's u_0 terms
+#pragma unroll
+                        for (int x = 0; x < 9; ++x) sb[x] += double(R.V[(size_t)9 * i + x]);
+                    }
+                    double* c = cb + 7 * (s0 + pu);
+                    c[0] = 2.0 * sb[0];
+                    c[1] = sb[1] + sb[3];
+                    c[2] = sb[2] + sb[6];
+                    c[3] = 2.0 * sb[4];
+                    c[4] = sb[5] + sb[7];
+                    c[5] = 2.0 * sb[8];
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            if (lane < m) {
+                const double* c = cb + 7 * lane;
+                const double C[9] = {c[0], c[1], c[2], c[1], c[3], c[4], c[2], c[4], c[5]};
+                const int j = jl;
+                const double v[3] = {L.px[i] - L.px[j], L.py[i] - L.py[j], L.pz[i] - L.pz[j]};
+                const double r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+                const double rcut = (i == 0 || j == 0) ? SI.r_mbd1 : SI.r_mbd2;
+                const double rh[3] = {v[0] / r, v[1] / r, v[2] / r};
+                const LrPair<W> lp = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut), W(a.r_buf));
+                double gp[3];
+                radial_tensor_grad(rh, r, double(lp.A), double(lp.dA), double(lp.dB), C, gp);
+                double rCr = 0.0;
+                for (int x = 0; x < 3; ++x)
+                    for (int y = 0; y < 3; ++y) rCr += rh[x] * C[3 * x + y] * rh[y];
+                const double ct = (3.0 * rCr - (C[0] + C[4] + C[8])) / (r * r * r);
+                R.rec[e0 + c0 + lane] = typename RowsAtom<W>::W4{
+                    W(gp[0]), W(gp[1]), W(gp[2]), W(a.beta * double(lp.fLR) * double(lp.dfS) * ct)};
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Every row's pair terms summed over its partners: partner j < i from the row's own slots,
+// j > i from the slot in j's row (found by binary search in the sorted row) with the
+// gradient's sign turned: it is odd in rhat, the R~ term even.  Lane l takes the partners
+// l, l + 64, ..; the lanes are combined in a fixed order.
+// ---------------------------------------------------------------------------
+template <typename W>
+__global__ void __launch_bounds__(kRowsThreads) k_rows_sums(MbdArgs a, int parts) {
+    int at, part;
+    rows_place(blockIdx.x, parts, at, part);
+    if (at >= a.n) return;
+    const RowsAtom<W> R = rows_atom<W>(a, a.order[at], nullptr);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i0 = (part * kRowsWaves + wave) * kRowsPerWave;
+    for (int i = i0; i < min(i0 + kRowsPerWave, R.nK); ++i) {
+        double g[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        const int n = R.len[i];
+        const size_t e0 = R.row0(i);
+        for (int s = lane; s < n; s += 64) {
+            const int j = R.pj[e0 + s];
+            size_t src = e0 + s;
+            double sg = 1.0;
+            if (j > i) {
+                const size_t b = R.row0(j);
+                const int end = R.len[j];
+                int lo = 0, hi = end;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (R.pj[b + mid] < i) lo = mid + 1;
+                    else hi = mid;
+                }
+                if (!(lo < end && R.pj[b + lo] == i)) {   // the coupling relation is symmetric: never taken
+                    atomicOr(a.err, 32);
+                    atomicMin(a.err_atom, R.k);
+                    continue;
+                }
+                src = b + lo;
+                sg = -1.0;
+            }
+            const typename RowsAtom<W>::W4 t = R.rec[src];
+            g[0] += sg * double(t[0]);
+            g[1] += sg * double(t[1]);
+            g[2] += sg * double(t[2]);
+            g[3] += double(t[3]);
+        }
+        double tot[9];
+        wave_sum9(g, tot);
+        if (lane == 0) {
+            R.L.g[(size_t)i * 3 + 0] = tot[0];
+            R.L.g[(size_t)i * 3 + 1] = tot[1];
+            R.L.g[(size_t)i * 3 + 2] = tot[2];
+            R.L.rb[i] = tot[3];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// R~ adjoint into alpha~(0), two-point model, blend adjoint, f_SCS gradients; outputs per site.
+// ---------------------------------------------------------------------------
+template <typename W, bool TB>
+__global__ void __launch_bounds__(kAtomThreads) k_rows_final(MbdArgs a) {
+    const int k = a.order[blockIdx.x], tid = threadIdx.x, lane = tid & 63;
+    const RowsAtom<W> R = rows_atom<W>(a, k, nullptr);
+    const MbdLds& L = R.L;
+    const int nK = R.nK, n1 = R.n1, nall = R.nall, nw = a.nw, nq = a.nq, nwe = R.nwe;
+    const double* aloc = a.alpha_loc + a.aloc_off[k];
+    double* abl = a.abar_loc + a.aloc_off[k];
+    double* cap = a.ca + a.site_off[k] * nw;
+    double* out = a.cf0 + a.site_off[k] * 3;
+    const double fconv = -1.0 / kBohr;  // force = -dE/dx per Angstrom
+    for (int i = tid; i < nK; i += blockDim.x) {
+        double g[3];
+        for (int d = 0; d < 3; ++d) g[d] = L.g[(size_t)i * 3 + d] + (TB ? L.fg[(size_t)i * 3 + d] : 0.0);
+        const double a0 = L.sa[(size_t)i * nwe];
+        // R~_i = R0 (alpha~_i(0)/alpha0)^(1/3): dR~/d alpha~(0) = R~ / (3 alpha~(0))
+        double b0 = L.ab[(size_t)i * nwe] + L.rb[i] * L.Rt[i] / (3.0 * a0), br = 0.0;
+        const int si = R.slot_site[i];
+        const Site st = R.S[si];
+        const double* cen = a.alpha_loc + a.aloc_off[st.base];
+        const double* al = aloc + (size_t)si * nw;
+        const double fsv = L.fs[i];
+        if (a.lorentz) {
+            // back through the two-point model onto alpha~_i(0) and alpha~_i(w_ref)
+            const double ar = (i == 0) ? aloc[1] : (si < n1) ? (1.0 - fsv) * al[1] + fsv * cen[1] : cen[1];
+            for (int q = 0; q < nq; ++q) {
+                const double v = L.sa[(size_t)i * nwe + 1 + q], x = L.ab[(size_t)i * nwe + 1 + q];
+                b0 += x * (1.0 - a.rho[q]) * (v / a0) * (v / a0);
+                br += x * a.rho[q] * (v / ar) * (v / ar);
+            }
+        }
+        double gf = 0.0;  // sum_w abar_i(w) (alpha~_I,i(w) - alpha~_K,i(w))
+        for (int w = 0; w < nw; ++w) {
+            const double ai = w == 0 ? b0 : a.lorentz ? br : L.ab[(size_t)i * nwe + w];
+            if (i == 0) {
+                abl[w] = ai;
+                cap[w] = 0.0;
+            } else if (si < n1) {
+                abl[(size_t)si * nw + w] = (1.0 - fsv) * ai;
+                cap[(size_t)si * nw + w] = fsv * ai;
+                gf += ai * (cen[w] - al[w]);
+            } else {
+                cap[(size_t)si * nw + w] = ai;
+            }
+        }
+        // f_SCS(r_ik), r_ik = |p_i| (the central atom sits at the origin)
+        double fg[3] = {0.0, 0.0, 0.0};
+        if (i > 0 && si < n1) {
+            const double p[3] = {L.px[i], L.py[i], L.pz[i]};
+            const double c = L.dfs[i] * gf / sqrt(p[0] * p[0] + p[1] * p[1] + p[2] * p[2]);
+            for (int d = 0; d < 3; ++d) fg[d] = c * p[d];
+        }
+        for (int d = 0; d < 3; ++d) {
+            L.fg[(size_t)i * 3 + d] = fg[d];
+            if (i > 0) out[3 * (size_t)si + d] = fconv * (g[d] + fg[d]);
+            else L.g[d] = g[d];
+        }
+    }
+    // local polarisabilities of K1 sites outside K carry no energy adjoint
+    for (int e = tid; e < (n1 > nK ? (n1 - nK) * nw : 0); e += blockDim.x) abl[(size_t)nK * nw + e] = 0.0;
+    __syncthreads();
+    if (tid < 64) {
+        // moving the central atom changes every r_ik of the blend
+        double c[3] = {0.0, 0.0, 0.0};
+        for (int i = 1 + lane; i < nK; i += 64)
+            for (int d = 0; d < 3; ++d) c[d] += L.fg[(size_t)i * 3 + d];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1)
+            for (int d = 0; d < 3; ++d) c[d] += __shfl_xor(c[d], o);
+        if (lane < 3) out[lane] = fconv * (L.g[lane] - (lane == 0 ? c[0] : lane == 1 ? c[1] : c[2]));
+    }
+    for (int e = 3 * nK + tid; e < 3 * nall; e += blockDim.x) out[e] = 0.0;
+    for (int e = tid; e < (nall - nK) * nw; e += blockDim.x) cap[(size_t)nK * nw + e] = 0.0;
+}
+
+// dynamic LDS of the two kernels that use any
+static size_t rows_energy_lds(const MbdArgs& a) {
+    const size_t sets = ((size_t)(a.n_max - 1) * a.nq + 7) / 8;
+    const size_t rs = std::max<size_t>(1, kAtomThreads / 64 / sets);
+    return sizeof(double) * (mbd_small_doubles(a.nq, a.n_max, a.lz_steps, a.fit != 0) + rs * (a.n_max + 1) * a.nq);
+}
+static size_t rows_pairs_lds(const MbdArgs& a, size_t wsz) {
+    const size_t KK = (size_t)std::max(a.n_max - 2, 0) * a.ncol;
+    return kRowsWaves * (sizeof(double) * 64 * 7 + wsz * ((3 * KK + 3) / 4 * 4));
+}
+
+template <typename W, bool TB>
+static hipError_t launch_rows_t(hipStream_t st, const MbdArgs& a, int nkmax) {
+    constexpr int VW = 16 / sizeof(W);
+    const bool vec = a.ncol % VW == 0;
+    const unsigned atoms8 = 8u * (unsigned)((a.n + 7) / 8);
+    const dim3 per_atom(a.n);
+    auto parts_of = [](int items) { return (items + kRowsWaves - 1) / kRowsWaves; };
+    const int rows = parts_of((nkmax + kRowsPerWave - 1) / kRowsPerWave);   // workgroups per atom, rows over wavefronts
+    const int nlt = a.ncol / (vec ? VW : 1), ng = 64 / std::min(nlt, 64);
+    const int prod = parts_of((1 + (nkmax - 1 + ng - 1) / ng) * ((nlt + 63) / 64));
+    hipLaunchKernelGGL((k_rows_setup<W>), per_atom, dim3(kAtomThreads), 0, st, a);
+    hipLaunchKernelGGL((k_rows_lists<W, TB>), dim3(atoms8 * rows), dim3(kRowsThreads), 0, st, a, rows);
+    for (int m = 1; m < a.mmax; ++m) {
+        if (vec) hipLaunchKernelGGL((k_rows_product<W, VW>), dim3(atoms8 * prod), dim3(kRowsThreads), 0, st, a, prod, m);
+        else hipLaunchKernelGGL((k_rows_product<W, 1>), dim3(atoms8 * prod), dim3(kRowsThreads), 0, st, a, prod, m);
+    }
+    hipLaunchKernelGGL((k_rows_energy<W, TB>), per_atom, dim3(kAtomThreads), rows_energy_lds(a), st, a);
+    if (a.forces) {
+        if (!(a.fit || TB)) {
+            const int ops = std::max(1, (nkmax + 63) / 64);
+            hipLaunchKernelGGL((k_rows_operands<W>), dim3(atoms8 * ops), dim3(kRowsThreads), 0, st, a, ops);
+        }
+        const size_t lds = rows_pairs_lds(a, sizeof(W));
+        if (vec) hipLaunchKernelGGL((k_rows_pairs<W, VW>), dim3(atoms8 * rows), dim3(kRowsThreads), lds, st, a, rows);
+        else hipLaunchKernelGGL((k_rows_pairs<W, 1>), dim3(atoms8 * rows), dim3(kRowsThreads), lds, st, a, rows);
+        hipLaunchKernelGGL((k_rows_sums<W>), dim3(atoms8 * rows), dim3(kRowsThreads), 0, st, a, rows);
+        hipLaunchKernelGGL((k_rows_final<W, TB>), per_atom, dim3(kAtomThreads), 0, st, a);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_mbd_rows(hipStream_t st, const MbdArgs& a, int nkmax, bool mixed, bool two_body) {
+    if (mixed) return two_body ? launch_rows_t<float, true>(st, a, nkmax) : launch_rows_t<float, false>(st, a, nkmax);
+    return two_body ? launch_rows_t<double, true>(st, a, nkmax) : launch_rows_t<double, false>(st, a, nkmax);
+}
+
+}  // namespace lmbd

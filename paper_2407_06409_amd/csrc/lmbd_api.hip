@@ -380,7 +380,7 @@ void build_plan(const std::vector<Counts>& cnt, const std::vector<char>& gs, con
         P.coef_off[k] = co;
         po += (int64_t)c.n1 * (c.n12 - c.n1) + (int64_t)c.n1 * (c.n1 - 1) / 2;
         if (mixed) co += (int64_t)nw * c.n1 * (c.n1 + 1);
-        const int64_t N1 = 3 * (int64_t)c.n1, N3 = 3 * (int64_t)c.nK;
+        const int64_t N1 = 3 * (int64_t)c.n1;
         P.hash_cap[k] = (int32_t)next_pow2(2 * (int64_t)c.n_all);
         P.fac_ld[k] = (int32_t)((N1 + 3) / 4 * 4);
         so += c.n_all;
@@ -388,13 +388,10 @@ void build_plan(const std::vector<Counts>& cnt, const std::vector<char>& gs, con
         fo += (int64_t)nw * (N1 + 3) * P.fac_ld[k];   // B~ and, appended, the three rows of d^T
         xo += (int64_t)nw * N1 * 3;
         ao += (int64_t)c.n1 * nw;
-        auto al4 = [](int64_t x) { return (x + 3) / 4 * 4; };  // as the MBD kernel lays out its workspace
         if (gs[k])
-            wo += mbd_global_layout(c.nK, ncol / 3, n_max, mmax, mbd_list_cap(c.nK, m2max[k]), mixed ? 4 : 8, forces)
-                      .total;
+            wo += mbd_global_elements(c.nK, ncol / 3, n_max, mmax, mbd_list_cap(c.nK, m2max[k]), mixed ? 4 : 8, forces);
         else
-            wo += al4(N3 * al4(N3)) + al4((int64_t)mmax * N3 * ncol) + 2 * al4(ncol * al4(N3)) +
-                  (forces ? 2 * N3 * al4((int64_t)n_max * ncol) : 0);
+            wo += mbd_dense_elements(c.nK, ncol / 3, n_max, mmax, forces);
         if (!gs[k]) P.nkmax_lds = std::max(P.nkmax_lds, c.nK);
         P.n1max = std::max(P.n1max, c.n1);
         P.nkmax = std::max(P.nkmax, c.nK);
@@ -1089,24 +1086,35 @@ lmbd_status lmbd_compute_batch(lmbd_context* ctx, const lmbd_params* params, int
     Plan P;
     build_plan(cnt, gsites, m2max, nw, ncol, n_max, forces, mixed, P);
     // MBD kernel form per structure, not per call, so that a structure's results do not
-    // depend on what it shares a call with: dense-form atoms first, then sparse-form atoms
-    // with the site arrays in LDS, then those with them in the workspace, each part still
-    // largest first
+    // depend on what it shares a call with: dense-form atoms first, then sparse-form atoms,
+    // each part still largest first.  Neighbourhoods beyond the dense form's LDS are always
+    // sparse; others by their radii, as long as the sparse layout fits the space reserved
+    // (it does but for neighbourhoods of a few sites with few nodes, where the dense form is
+    // no slower)
     std::vector<int> form(n_structs);
     for (int s = 0; s < n_structs; ++s) {
         const bool sparse = params->force_model == LMBD_FORCES_EXACT &&   // the approximate forces use dense products
                             (ctx->mbd_product == LMBD_MBD_SPARSE ||
                              (ctx->mbd_product == LMBD_MBD_AUTO && structs[s].r_mbd2 <= kSparseMbdRatio * structs[s].r_nbr));
-        form[s] = gsites[sbegin[s]] ? kMbdSparseGlobal : sparse ? kMbdSparse : kMbdDense;
-        if (form[s] == kMbdSparseGlobal && (params->force_model != LMBD_FORCES_EXACT || ctx->mbd_product == LMBD_MBD_DENSE))
+        bool fits = true;
+        for (int64_t k = sbegin[s]; k < sbegin[s + 1] && sparse; ++k) {   // (the tighter space of an energy call)
+            const int me = std::max(1, (n_max + 1) / 2);
+            fits = fits && rows_layout(cnt[k].nK, m2max[k], nq, n_max, me, (int64_t)wsz, false).total <=
+                               mbd_dense_elements(cnt[k].nK, nq, n_max, me, false);
+        }
+        form[s] = gsites[sbegin[s]] || (sparse && fits) ? kMbdRows : kMbdDense;
+        if (gsites[sbegin[s]] && (params->force_model != LMBD_FORCES_EXACT || ctx->mbd_product == LMBD_MBD_DENSE))
             return fail(ctx, LMBD_E_UNSUPPORTED, "neighbourhood too large for the dense MBD products (nK up to " +
                                                      std::to_string(kMaxNK) + "; larger ones need the sparse form)");
     }
     // launch groups: MBD form, then whether the structure has two-body radii of its own
     auto group = [&](int32_t k) { return 2 * form[atom_struct[k]] + sinfo[atom_struct[k]].two_body; };
     std::stable_sort(P.order.begin(), P.order.end(), [&](int32_t x, int32_t y) { return group(x) < group(y); });
-    int n_group[6] = {0, 0, 0, 0, 0, 0};
-    for (int k = 0; k < N; ++k) n_group[group(k)]++;
+    int n_group[4] = {0, 0, 0, 0}, nk_group[4] = {0, 0, 0, 0};
+    for (int k = 0; k < N; ++k) {
+        n_group[group(k)]++;
+        nk_group[group(k)] = std::max(nk_group[group(k)], cnt[k].nK);
+    }
     if (P.n1max > kMaxN1 || P.nkmax_lds > kMaxNK || P.nallmax > kMaxSites)
         return fail(ctx, LMBD_E_UNSUPPORTED,
                     "neighbourhood too large (n1 " + std::to_string(P.n1max) + ", nK " + std::to_string(P.nkmax) +
@@ -1248,12 +1256,13 @@ lmbd_status lmbd_compute_batch(lmbd_context* ctx, const lmbd_params* params, int
     ma.ca = forces ? as<double>(ctx->ca) : nullptr;
     ma.cf0 = forces ? as<double>(ctx->cf) : nullptr;
     HIP_TRY(mark(5, 0));
-    for (int gi = 0, first = 0; gi < 6; first += n_group[gi], ++gi) {   // the sparse forms pay once block
+    for (int gi = 0, first = 0; gi < 4; first += n_group[gi], ++gi) {   // the sparse form pays once block
         if (n_group[gi] == 0) continue;                                      // rows couple to a small part of K
         MbdArgs mf = ma;
         mf.n = n_group[gi];
         mf.order = ma.order + first;
-        HIP_TRY(launch_mbd(stream, mf, P.nkmax_lds, mixed, gi / 2, (gi & 1) != 0));
+        if (gi / 2 == kMbdDense) HIP_TRY(launch_mbd_dense(stream, mf, nk_group[gi], mixed, (gi & 1) != 0));
+        else HIP_TRY(launch_mbd_rows(stream, mf, nk_group[gi], mixed, (gi & 1) != 0));
     }
     HIP_TRY(mark(5, 1));
 

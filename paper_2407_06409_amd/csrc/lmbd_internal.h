@@ -288,7 +288,7 @@ hipError_t launch_gather_nu(hipStream_t st, int n, int nw, const Counts* counts,
 // blended polarisabilities at 0 and the nodes (nq + 1), their square roots at the nodes
 // (max(nq, 12): the force stage's pair sums take their place), SCS radii, f_SCS and its
 // derivative (3), polarisability adjoints (nq + 1), radius-adjoint parts (4), blend
-// gradients (3).  In LDS, or in the workspace for the sparse form with global site arrays.
+// gradients (3).  In LDS for the dense form, in the workspace for the sparse form.
 __host__ __device__ inline size_t mbd_site_doubles(size_t nk, int nq) {
     const size_t nw = (size_t)nq + 1;
     return 3 * nk + nk * nw + nk * (size_t)(nq > 12 ? nq : 12) + 3 * nk + nk * nw + 4 * nk + 3 * nk;
@@ -298,48 +298,72 @@ __host__ __device__ inline size_t mbd_small_doubles(int nq, int n_max, int lz_st
     return (size_t)(n_max + 1) * nq + (fit ? 2 * (size_t)(kMaxNmax + 1) * nq : 0) +
            (lz_steps > 0 ? (2 * (size_t)lz_steps + 3) * nq : 0);
 }
-// Capacity (entries) of the coupled-site lists of an atom with nK sites in the sparse form
-// with global site arrays: the central row couples to at most nK - 1 sites, every other row
+// Capacity (entries) reserved for the coupled-site lists of an atom with nK sites whose
+// neighbourhood only the sparse form takes: the central row couples to at most nK - 1 sites, every other row
 // to at most m2max - 1 sites within r_mbd2 plus the central atom (m2max: the structure's
 // largest count of sites within r_mbd2, itself included); two entries of slack per row.
 __host__ __device__ inline int64_t mbd_list_cap(int nK, int m2max) {
     return (int64_t)(nK - 1) * (m2max + 2) + nK;
 }
-// Per-atom workspace of that form, offsets in elements of the workspace type (size wsz),
-// each part on a 16-byte boundary: site arrays (double), the lists (cap entries of five
-// coefficients A, B, rhat of type W and one int32 site index; nK + 1 int32 row offsets),
-// the Krylov blocks, the two Lanczos/operand buffers and, with forces, P and Q.
-struct MbdGlobalLayout {
-    int64_t sites, lists, U, V, V2, P, Q, total;
-};
-__host__ __device__ inline MbdGlobalLayout mbd_global_layout(int nK, int nq, int n_max, int mmax, int64_t cap,
-                                                             int64_t wsz, bool forces) {
+// Elements (of size wsz) reserved per atom of that form: site arrays, lists of `cap`
+// entries (44 bytes at FP64), Krylov blocks, two operand buffers and, with forces, P and Q.
+// RowsLayout below needs less (about 38 of 67 MB per atom at 10 + 8 A); the reservation is
+// part of what lmbd_estimate_footprint promises and stays.
+__host__ __device__ inline int64_t mbd_global_elements(int nK, int nq, int n_max, int mmax, int64_t cap, int64_t wsz,
+                                                       bool forces) {
     const int64_t N3 = 3 * (int64_t)nK, N3p = (N3 + 3) / 4 * 4, ncol = 3 * (int64_t)nq;
     const int64_t KKp = ((int64_t)n_max * ncol + 3) / 4 * 4;
+    auto al16 = [](int64_t bytes) { return (bytes + 15) / 16 * 16; };
+    return (al16(8 * (int64_t)mbd_site_doubles((size_t)nK, nq)) + al16(cap * (5 * wsz + 4) + 4 * ((int64_t)nK + 1)) +
+            al16(wsz * mmax * N3 * ncol) + 2 * al16(wsz * ncol * N3p) + (forces ? 2 * al16(wsz * N3 * KKp) : 0)) /
+           wsz;
+}
+// Elements of the dense form's per-atom workspace: T_LR, the Krylov blocks, two operand
+// buffers and, with forces, P and Q.
+__host__ __device__ inline int64_t mbd_dense_elements(int nK, int nq, int n_max, int mmax, bool forces) {
+    const int64_t N3 = 3 * (int64_t)nK, N3p = (N3 + 3) / 4 * 4, ncol = 3 * (int64_t)nq;
+    auto al4 = [](int64_t x) { return (x + 3) / 4 * 4; };
+    return al4(N3 * N3p) + al4((int64_t)mmax * N3 * ncol) + 2 * al4(ncol * N3p) +
+           (forces ? 2 * N3 * al4((int64_t)n_max * ncol) : 0);
+}
+// The sparse form's workspace in the same space, offsets in elements of the workspace type
+// (size wsz), each part on a 16-byte boundary: site arrays (double); the lists, row i >= 1
+// with space for `stride` entries (every site within r_mbd2 of the structure's fullest atom,
+// the central atom, slack) and the central row for nK, as 4-vectors, int32 slots and row
+// lengths; the Krylov blocks P; V (Lanczos vectors, central terms of Tbar); with forces Q.
+__host__ __device__ inline int rows_stride(int nK, int m2max) { return nK < m2max + 2 ? nK : m2max + 2; }
+__host__ __device__ inline int64_t rows_cap(int nK, int m2max) {
+    return nK + (int64_t)(nK - 1) * rows_stride(nK, m2max);
+}
+struct RowsLayout {
+    int64_t sites, lists, P, V, Q, total;
+};
+__host__ __device__ inline RowsLayout rows_layout(int nK, int m2max, int nq, int n_max, int mmax, int64_t wsz,
+                                                  bool forces) {
+    const int64_t N3 = 3 * (int64_t)nK, N3p = (N3 + 3) / 4 * 4, ncol = 3 * (int64_t)nq;
+    const int64_t na = forces && n_max > 2 ? n_max - 2 : 0;
     int64_t o = 0;
-    MbdGlobalLayout g;
+    RowsLayout g;
     auto take = [&](int64_t bytes) {
         const int64_t at = o;
         o += (bytes + 15) / 16 * 16;
         return at / wsz;
     };
     g.sites = take(8 * (int64_t)mbd_site_doubles((size_t)nK, nq));
-    g.lists = take(cap * (5 * wsz + 4) + 4 * ((int64_t)nK + 1));
-    g.U = take(wsz * mmax * N3 * ncol);
+    g.lists = take(rows_cap(nK, m2max) * (4 * wsz + 4) + 4 * (int64_t)nK);
+    g.P = take(wsz * mmax * N3 * ncol);
     g.V = take(wsz * ncol * N3p);
-    g.V2 = take(wsz * ncol * N3p);
-    g.P = take(forces ? wsz * N3 * KKp : 0);
-    g.Q = take(forces ? wsz * N3 * KKp : 0);
+    g.Q = take(wsz * na * N3 * ncol);
     g.total = o / wsz;
     return g;
 }
-// MBD kernel forms: dense T_LR on the matrix cores; sparse products with the per-site
-// arrays in LDS; sparse products with them in the workspace (neighbourhoods too large for LDS)
-enum { kMbdDense = 0, kMbdSparse = 1, kMbdSparseGlobal = 2 };
+// MBD kernel forms: dense T_LR on the matrix cores (k_mbd.hip); lists of coupled sites (k_mbd_rows.hip)
+enum { kMbdDense = 0, kMbdRows = 1 };
 constexpr size_t kLdsBytes = 160 * 1024;   // LDS of a gfx950 workgroup
 size_t mbd_lds_bytes(int nkmax, int nq, int n_max, int lz_steps, bool fit);
 // two_body: every atom of the launch belongs to a structure with two-body radii of its own
-hipError_t launch_mbd(hipStream_t st, const MbdArgs& a, int nkmax, bool mixed, int form, bool two_body);
+hipError_t launch_mbd_dense(hipStream_t st, const MbdArgs& a, int nkmax, bool mixed, bool two_body);
+hipError_t launch_mbd_rows(hipStream_t st, const MbdArgs& a, int nkmax, bool mixed, bool two_body);
 hipError_t launch_gather_central(hipStream_t st, int n, int nw, const Counts* counts,
                                  const int64_t* site_off, const Site* sites, const int32_t* rev,
                                  const double* ca, double* abar_cen);
