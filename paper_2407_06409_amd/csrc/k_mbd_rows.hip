@@ -4,22 +4,25 @@
 // form (k_mbd.hip); here T_LR is kept as lists of coupled sites and one atom is spread
 // over many workgroups, one launch per step:
 //   k_rows_setup     site order, blend, SCS radii                     one workgroup per atom
-//   k_rows_lists     coupled-site lists, u_1                          a row per wavefront
-//   k_rows_product   u_{m+1} = D T D u_m                              block rows per lane group
+//   k_rows_lists     coupled-site lists, u_1                          three rows per wavefront
+//   k_rows_product   u_{m+1} = D T D u_m                              three rows per wavefront
 //   k_rows_energy    spectrum bounds, moments, energy                 one workgroup per atom
-//   k_rows_operands  polarisability adjoints, operands of Tbar        elementwise
-//   k_rows_pairs     Tbar and gradient of every coupled pair          a row per wavefront
+//   k_rows_operands  polarisability adjoints, operands of Tbar        a (site, node) per lane
+//   k_rows_pairs     Tbar and gradient of every coupled pair          three rows per wavefront
 //   k_rows_sums      pair terms summed per site                       a row per wavefront
 //   k_rows_final     blend adjoint, outputs                           one workgroup per atom
 // All of it is bound by gathers of the partners' rows.  What makes them cheap is where they
 // hit: the sites are ordered along a space-filling curve, so that the rows at work share
 // most of their partners, and the workgroups of one atom are dealt to one XCD one atom
 // after the other, so that this atom's Krylov block (2.1 MB of FP64 for 2,450 sites) and
-// not those of 32 atoms is what the XCD's L2 has to hold.
+// not those of 32 atoms is what the XCD's L2 has to hold.  What is left is then the rate
+// at which the L1 returns data, so rows go through the products and the pair sums three at
+// a time: neighbours on the curve share two thirds of their partners, and a partner's row
+// is loaded once for the three.
 //
-// Storage per atom (RowsLayout): the Krylov blocks scaled, P = [D u_1 .. D u_mmax] side by
-// side, which is the products' operand and Tbar's left operand at once; moments and
-// adjoints divide by alpha~ where they need u itself.
+// Storage per atom (RowsLayout): the Krylov blocks scaled, P_m = D u_m, which are the
+// products' operands and Tbar's left operand at once; moments and adjoints divide by
+// alpha~ where they need u itself.
 #include <algorithm>
 #include <type_traits>
 
@@ -31,13 +34,16 @@ constexpr int kRowsThreads = 256;    // row kernels: four wavefronts
 constexpr int kRowsWaves = kRowsThreads / 64;
 constexpr int kAtomThreads = 1024;   // one-workgroup-per-atom kernels
 constexpr int kBox = 16;             // slots per bounding box
-constexpr int kRowsPerWave = 3;      // rows of a wavefront in the list, pair and sum kernels
+constexpr int kTriple = 3;           // rows taken together: group 0 is the central row, group t >= 1
+                                     // rows 1 + 3 (t - 1) .. (nK + 1) / 3 groups in all
+constexpr int kSlotBits = 15;        // a union entry is slot | (bit per row of the group) << kSlotBits
+static_assert(kMaxSites <= (1 << kSlotBits), "slots fit their field");
 
 // What every kernel of this file derives from its atom.
 template <typename W>
 struct RowsAtom {
     typedef W W4 __attribute__((ext_vector_type(4)));
-    int k, nK, n1, nall, N3, N3p, nq, nwe, nw, ncol, ldp, na, ldq, stride, nbox;
+    int k, nK, n1, nall, N3, N3p, nq, nwe, nw, ncol, na, ldq, stride, nbox;
     const StructInfo* SI;
     const Site* S;
     MbdLds L;             // site arrays, in the workspace
@@ -46,8 +52,11 @@ struct RowsAtom {
     double* boxes;        // bounding boxes of kBox slots
     W4* rec;              // list entries: s = sqrt(A) rhat and B (T_LR = s s^T + B I; A >= 0)
     int32_t* pj;          // list entries: slot, ascending in each row
+    int32_t* uni;         // per group, from its first row's place: the union of its rows' entries, ascending
     int32_t* len;         // entries per row
-    W *P, *V, *Q;
+    int32_t* ulen;        // union entries per group
+    W *P, *V, *Q;         // P: block m - 1 holds D u_m
+    __device__ W* block(int m) const { return P + (size_t)(m - 1) * N3 * ncol; }
     __device__ size_t row0(int i) const { return i == 0 ? 0 : (size_t)nK + (size_t)(i - 1) * stride; }
 };
 
@@ -73,7 +82,6 @@ __device__ inline RowsAtom<W> rows_atom(const MbdArgs& a, int k, double* small) 
     R.nwe = a.nq + 1;
     R.nw = a.nw;
     R.ncol = a.ncol;
-    R.ldp = a.mmax * a.ncol;
     R.na = a.forces ? max(a.n_max - 2, 0) : 0;
     R.ldq = R.na * a.ncol;
     R.SI = &a.sinfo[a.atom_struct[k]];
@@ -90,7 +98,9 @@ __device__ inline RowsAtom<W> rows_atom(const MbdArgs& a, int k, double* small) 
     const int64_t cap = rows_cap(R.nK, R.SI->m2max);
     R.rec = reinterpret_cast<typename RowsAtom<W>::W4*>(w + G.lists);
     R.pj = reinterpret_cast<int32_t*>(R.rec + cap);
-    R.len = R.pj + cap;
+    R.uni = R.pj + cap;
+    R.len = R.uni + cap;
+    R.ulen = R.len + R.nK;
     R.P = w + G.P;
     R.V = w + G.V;
     R.Q = w + G.Q;
@@ -208,15 +218,15 @@ __global__ void __launch_bounds__(kAtomThreads) k_rows_setup(MbdArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Coupled sites of every block row and their coefficients, ascending in the slot, and the
-// row of D u_1 (u_1 = D T D e_k needs the central block column only).  A wavefront per
-// row, its lanes testing four boxes of 16 slots at a time: the first box (the central
-// atom) and those that reach within r_mbd2 (all of them for the central row).  Row i has
-// space for every site within r_mbd2 of the structure's fullest atom, so the rows need no
-// counting pass.
+// Coupled sites of every block row and their coefficients, ascending in the slot, the
+// union of the entries of three rows, and the rows of D u_1 (u_1 = D T D e_k needs the
+// central block column only).  A wavefront per group of rows, its lanes testing four boxes
+// of 16 slots at a time: the first box (the central atom) and those that reach within
+// r_mbd2 of a row (all of them for the central row).  Row i has space for every site
+// within r_mbd2 of the structure's fullest atom, so the rows need no counting pass.
 // ---------------------------------------------------------------------------
 template <typename W, bool TB>
-__global__ void __launch_bounds__(kRowsThreads) k_rows_lists(MbdArgs a, int parts) {
+__global__ void __launch_bounds__(kRowsThreads, 4) k_rows_lists(MbdArgs a, int parts) {
     int at, part;
     rows_place(blockIdx.x, parts, at, part);
     if (at >= a.n) return;
@@ -227,37 +237,51 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_lists(MbdArgs a, int part
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nK = R.nK, nq = a.nq, ncol = a.ncol;
     const double rcull = SI.r_mbd2 * SI.r_mbd2 * (1.0 + 1e-9);
-    const int i0 = (part * kRowsWaves + wave) * kRowsPerWave;
-    for (int i = i0; i < min(i0 + kRowsPerWave, nK); ++i) {
-        const size_t e0 = R.row0(i);
-        const int cap = i == 0 ? nK : R.stride;
-        int n = 0;
-        bool central = false;            // the row's first entry is the central atom
-        W4 r0 = {W(0), W(0), W(0), W(0)};
-        for (int b0 = 0; b0 < R.nbox; b0 += 64) {
-            const int b = b0 + lane;
-            bool near = b < R.nbox;
-            if (near && i != 0 && b != 0 && nK > 64) {
-                const double* bx = R.boxes + 6 * b;
+    const int grp = part * kRowsWaves + wave;
+    const int i0 = grp == 0 ? 0 : 1 + kTriple * (grp - 1);
+    if (i0 >= nK) return;
+    const int nr = grp == 0 ? 1 : min(kTriple, nK - i0);
+    const int cap = grp == 0 ? nK : R.stride;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int n[kTriple] = {0, 0, 0}, nu = 0;
+    bool central[kTriple] = {false, false, false};   // the row's first entry is the central atom, with r0
+    W4 r0[kTriple];
+#pragma unroll
+    for (int x = 0; x < kTriple; ++x) r0[x] = W4{W(0), W(0), W(0), W(0)};
+    for (int b0 = 0; b0 < R.nbox; b0 += 64) {
+        const int b = b0 + lane;
+        bool near = b < R.nbox;
+        if (near && grp != 0 && b != 0 && nK > 64) {
+            const double* bx = R.boxes + 6 * b;
+            near = false;
+            for (int x = 0; x < nr; ++x) {
+                const int i = i0 + x;
                 const double dx = fmax(0.0, fmax(bx[0] - L.px[i], L.px[i] - bx[3]));
                 const double dy = fmax(0.0, fmax(bx[1] - L.py[i], L.py[i] - bx[4]));
                 const double dz = fmax(0.0, fmax(bx[2] - L.pz[i], L.pz[i] - bx[5]));
-                near = dx * dx + dy * dy + dz * dz < rcull;
+                near = near || dx * dx + dy * dy + dz * dz < rcull;
             }
-            unsigned long long m = __ballot(near);
-            while (m) {
-                int box = 0;
-                bool have = false;
+        }
+        unsigned long long m = __ballot(near);
+        bool start = b0 == 0;   // lane 0 of the first step tests the central atom
+        while (m) {
+            int box = 0;
+            bool have = false;
 #pragma unroll
-                for (int u = 0; u < 64 / kBox; ++u) {   // the next four near boxes
-                    const int bit = m ? __ffsll((long long)m) - 1 : -1;
-                    m &= m - 1;
-                    if (lane / kBox == u) {
-                        have = bit >= 0;
-                        box = b0 + max(bit, 0);
-                    }
+            for (int u = 0; u < 64 / kBox; ++u) {   // the next four near boxes
+                const int bit = m ? __ffsll((long long)m) - 1 : -1;
+                m &= m - 1;
+                if (lane / kBox == u) {
+                    have = bit >= 0;
+                    box = b0 + max(bit, 0);
                 }
-                const int j = have ? kBox * box + lane % kBox : nK;
+            }
+            const int j = have ? kBox * box + lane % kBox : nK;
+            int bits = 0;
+#pragma unroll
+            for (int x = 0; x < kTriple; ++x) {
+                if (x >= nr) break;   // uniform
+                const int i = i0 + x;
                 double v[3], r;
                 W4 e = {W(0), W(0), W(0), W(0)};
                 const bool in = rows_coupled<W, TB>(R, i, j, v, r);
@@ -267,49 +291,71 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_lists(MbdArgs a, int part
                                                    W(a.r_buf));
                     const double sA = sqrt(fmax(double(t.A), 0.0)) / r;
                     e = W4{W(sA * v[0]), W(sA * v[1]), W(sA * v[2]), t.B};
+                    bits |= 1 << x;
                 }
                 const unsigned long long mask = __ballot(in);
-                const int at_e = n + __popcll(mask & ((1ull << lane) - 1ull));
+                const int at_e = n[x] + __popcll(mask & below);
                 if (in && at_e < cap) {
-                    R.pj[e0 + at_e] = j;
-                    R.rec[e0 + at_e] = e;
+                    R.pj[R.row0(i) + at_e] = j;
+                    R.rec[R.row0(i) + at_e] = e;
                 }
-                if (b0 == 0 && n == 0 && i != 0) {   // lane 0 of the first step tests the central atom
-                    const bool first = (mask & 1ull) != 0 && __shfl(j, 0) == 0;
-                    if (first) {
-                        central = true;
+                if (start && i != 0 && (mask & 1ull)) {
+                    central[x] = true;
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) r0[c] = __shfl(e[c], 0);
-                    }
+                    for (int c = 0; c < 4; ++c) r0[x][c] = __shfl(e[c], 0);
                 }
-                n += __popcll(mask);
+                n[x] += __popcll(mask);
             }
+            const unsigned long long any = __ballot(bits != 0);
+            const int at_u = nu + __popcll(any & below);
+            if (bits != 0 && at_u < nr * cap) R.uni[R.row0(i0) + at_u] = j | (bits << kSlotBits);
+            nu += __popcll(any);
+            start = false;
         }
-        if (n > cap && lane == 0) {   // the row outgrew its bound: refuse the call
+    }
+#pragma unroll
+    for (int x = 0; x < kTriple; ++x) {
+        if (x >= nr) break;
+        const int i = i0 + x;
+        if (n[x] > cap && lane == 0) {   // the row outgrew its bound: refuse the call
             atomicOr(a.err, 32);
             atomicMin(a.err_atom, R.k);
         }
-        if (lane == 0) R.len[i] = min(n, cap);
+        if (lane == 0) R.len[i] = min(n[x], cap);
         for (int col = lane; col < ncol; col += 64) {
             const int q = col / 3, c = col % 3;
             const double si = L.sqa[(size_t)i * nq + q];
-            const double s = central ? si * si * L.sqa[q] : 0.0;
-            for (int x = 0; x < 3; ++x)
-                R.P[(size_t)(3 * i + x) * R.ldp + col] =
-                    W(s * (double(r0[x]) * double(c == 0 ? r0[0] : c == 1 ? r0[1] : r0[2]) + (x == c ? double(r0[3]) : 0.0)));
+            const double s = central[x] ? si * si * L.sqa[q] : 0.0;
+            for (int y = 0; y < 3; ++y)
+                R.P[(size_t)(3 * i + y) * ncol + col] =
+                    W(s * (double(r0[x][y]) * double(c == 0 ? r0[x][0] : c == 1 ? r0[x][1] : r0[x][2]) +
+                           (y == c ? double(r0[x][3]) : 0.0)));
         }
     }
+    // (an entry beyond a row's capacity is in no list: the products would read past it)
+    if (lane == 0) R.ulen[grp] = (n[0] > cap || n[1] > cap || n[2] > cap) ? 0 : nu;
 }
 
 // ---------------------------------------------------------------------------
-// D u_{m+1} = D^2 T (D u_m).  A wavefront holds ng groups of nl lanes, a lane VW
-// consecutive columns (16-byte loads: 18 lanes and three groups for 36 FP64 columns, nine
-// and seven for FP32); each group walks a block row of its own, the rows side by side on
-// the curve.  The central row is longer than the others: its entries are dealt to the
-// groups of one wavefront and the parts summed in order.
+// D u_{m+1} = D^2 T (D u_m), three block rows per wavefront.  A wavefront holds ng groups
+// of nl lanes, a lane VW consecutive columns (16-byte loads: 18 lanes and three groups for
+// 36 FP64 columns, nine and seven for FP32).  The union of the rows' entries is taken 64
+// at a time: every lane brings one entry's coefficients for the three rows to LDS (zero for
+// a row that it is not in), then each group walks every ng-th entry, loading the partner's
+// rows once for its three accumulators.  The groups' parts are summed through LDS in order.
+// One row per group, with its entries read by every lane of it, was bound by the L1's
+// return rate (84 cycles for three entries, 32 of them for the coefficients): 512 C at
+// 10 + 8 A 15.6 -> 8.0 ms per product.
 // ---------------------------------------------------------------------------
+template <typename W>
+static size_t rows_product_lds(int ncol) {   // per wavefront: the window, or the groups' parts
+    const int vw = 16 / (int)sizeof(W), nlt = ncol / (ncol % vw ? 1 : vw), nl = std::min(nlt, 64), ng = 64 / nl;
+    return std::max<size_t>(64 * (kTriple * 4 * sizeof(W) + 4), (size_t)ng * 9 * nl * (ncol % vw ? 1 : vw) * sizeof(W));
+}
+
 template <typename W, int VW>
-__global__ void __launch_bounds__(kRowsThreads) k_rows_product(MbdArgs a, int parts, int m) {
+__global__ void __launch_bounds__(kRowsThreads) k_rows_product(MbdArgs a, int parts, int m, int lds_wave) {
+    extern __shared__ double lds[];
     int at, part;
     rows_place(blockIdx.x, parts, at, part);
     if (at >= a.n) return;
@@ -317,72 +363,81 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_product(MbdArgs a, int pa
     typedef W VV __attribute__((ext_vector_type(VW)));
     const RowsAtom<W> R = rows_atom<W>(a, a.order[at], nullptr);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nK = R.nK, nq = a.nq, ncol = a.ncol;
-    const size_t ldp = R.ldp;
+    const int nK = R.nK, ncol = a.ncol;
     const int nlt = ncol / VW;                           // lanes of all columns
     const int nl = min(nlt, 64), ng = 64 / nl;
-    const int g = lane / nl;
-    const int nrow = 1 + (nK - 1 + ng - 1) / ng;         // items per column chunk: the central row, then ng rows each
+    const int ngrp = (nK + 1) / kTriple + 1;             // the central row, then three rows each
     const int it = part * kRowsWaves + wave;
-    if (it >= nrow * ((nlt + 63) / 64)) return;
-    const int rit = it % nrow;
-    const int cl = (it / nrow) * 64 + lane - g * nl;
-    const bool okc = g < ng && cl < nlt;
-    const int col = okc ? VW * cl : 0;
-    const bool split = rit == 0;                         // uniform
-    const int i = split ? 0 : 1 + (rit - 1) * ng + g;
-    const bool okr = okc && i < nK;
-    const int n = okr ? R.len[i] : 0;
-    const size_t e0 = okr ? R.row0(i) : 0;
-    const int first = split ? g : 0, inc = split ? ng : 1;
-    VV acc0 = VV(W(0)), acc1 = VV(W(0)), acc2 = VV(W(0));
-    const W* const vc = R.P + (size_t)(m - 1) * ncol + col;
-    // two entries per step; an entry past the row's end reads its first entry with a zero
-    // factor, so that the loads of a step overlap
-    for (int s = first; s < n; s += 2 * inc) {
-        const size_t ea = e0 + s, eb = e0 + (s + inc < n ? s + inc : s);
-        const W4 ra = R.rec[ea];
-        W4 rb = R.rec[eb];
-        const int ja = R.pj[ea], jb = R.pj[eb];
-        const W* va = vc + (size_t)(3 * ja) * ldp;
-        const W* vb = vc + (size_t)(3 * jb) * ldp;
-        const VV a0 = *reinterpret_cast<const VV*>(va), a1 = *reinterpret_cast<const VV*>(va + ldp),
-                 a2 = *reinterpret_cast<const VV*>(va + 2 * ldp);
-        const VV b0 = *reinterpret_cast<const VV*>(vb), b1 = *reinterpret_cast<const VV*>(vb + ldp),
-                 b2 = *reinterpret_cast<const VV*>(vb + 2 * ldp);
-        if (s + inc >= n) rb = W4{W(0), W(0), W(0), W(0)};
-        const VV da = ra[0] * a0 + ra[1] * a1 + ra[2] * a2;
-        acc0 += ra[0] * da + ra[3] * a0;
-        acc1 += ra[1] * da + ra[3] * a1;
-        acc2 += ra[2] * da + ra[3] * a2;
-        const VV db = rb[0] * b0 + rb[1] * b1 + rb[2] * b2;
-        acc0 += rb[0] * db + rb[3] * b0;
-        acc1 += rb[1] * db + rb[3] * b1;
-        acc2 += rb[2] * db + rb[3] * b2;
-    }
-    if (split) {   // the groups' parts, in order
-        VV t0 = acc0, t1 = acc1, t2 = acc2;
-        for (int gg = 1; gg < ng; ++gg)
+    const int grp = it % ngrp, chunk = it / ngrp;
+    const int i0 = grp == 0 ? 0 : 1 + kTriple * (grp - 1);
+    if (chunk * 64 >= nlt || i0 >= nK) return;
+    const int nr = grp == 0 ? 1 : min(kTriple, nK - i0);
+    const int g = lane / nl;
+    const int cl = chunk * 64 + lane - g * nl;
+    const bool act = g < ng && cl < nlt;
+    const int col = act ? VW * cl : 0;
+    char* const mine = reinterpret_cast<char*>(lds) + (size_t)wave * lds_wave;
+    W4* const wrec = reinterpret_cast<W4*>(mine);                    // [64][kTriple]
+    int* const wj = reinterpret_cast<int*>(wrec + 64 * kTriple);     // [64]
+    const W* const vc = R.block(m) + col;
+    const int nu = R.ulen[grp];
+    size_t e0[kTriple];                                  // next entry of each row
 #pragma unroll
-            for (int v = 0; v < VW; ++v) {
-                const int from = (lane + gg * nl) & 63;
-                const W x0 = __shfl(acc0[v], from), x1 = __shfl(acc1[v], from), x2 = __shfl(acc2[v], from);
-                t0[v] += x0;
-                t1[v] += x1;
-                t2[v] += x2;
+    for (int x = 0; x < kTriple; ++x) e0[x] = R.row0(min(i0 + x, nK - 1));
+    const size_t u0 = R.row0(i0);
+    VV acc[kTriple][3];
+#pragma unroll
+    for (int x = 0; x < kTriple; ++x)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[x][c] = VV(W(0));
+    const unsigned long long below = (1ull << lane) - 1ull;
+    for (int t0 = 0; t0 < nu; t0 += 64) {
+        const int cnt = min(64, nu - t0);
+        const int ent = lane < cnt ? R.uni[u0 + t0 + lane] : 0;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // the last window has been read
+        wj[lane] = ent & ((1 << kSlotBits) - 1);
+#pragma unroll
+        for (int x = 0; x < kTriple; ++x) {
+            const bool in = (ent >> (kSlotBits + x)) & 1;
+            const unsigned long long mask = __ballot(in);
+            W4 r = {W(0), W(0), W(0), W(0)};
+            if (in) r = R.rec[e0[x] + __popcll(mask & below)];
+            wrec[lane * kTriple + x] = r;
+            e0[x] += __popcll(mask);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        for (int s = g; s < cnt; s += ng) {
+            const W* v = vc + (size_t)(3 * wj[s]) * ncol;
+            const VV x0 = *reinterpret_cast<const VV*>(v), x1 = *reinterpret_cast<const VV*>(v + ncol),
+                     x2 = *reinterpret_cast<const VV*>(v + 2 * ncol);
+#pragma unroll
+            for (int x = 0; x < kTriple; ++x) {
+                const W4 r = wrec[s * kTriple + x];
+                const VV d = r[0] * x0 + r[1] * x1 + r[2] * x2;
+                acc[x][0] += r[0] * d + r[3] * x0;
+                acc[x][1] += r[1] * d + r[3] * x1;
+                acc[x][2] += r[2] * d + r[3] * x2;
             }
-        acc0 = t0;
-        acc1 = t1;
-        acc2 = t2;
+        }
     }
-    if (okr && (!split || g == 0)) {
+    // the groups' parts, in order: part g, row x, component c at ((g * 9 + 3x + c) nl + lane) VV
+    VV* const red = reinterpret_cast<VV*>(mine);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    if (g < ng)
+#pragma unroll
+        for (int y = 0; y < 9; ++y) red[(g * 9 + y) * nl + lane - g * nl] = acc[y / 3][y % 3];
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    // lanes over (row, component, columns)
+    for (int e = lane; e < 3 * nr * nl; e += 64) {
+        const int y = e / nl, c = chunk * 64 + e % nl;
+        if (c >= nlt) continue;
+        VV t = red[e];
+        for (int gg = 1; gg < ng; ++gg) t += red[gg * 9 * nl + e];
+        const int i = i0 + y / 3;
         VV al;
 #pragma unroll
-        for (int v = 0; v < VW; ++v) al[v] = W(R.L.sa[(size_t)i * R.nwe + 1 + (col + v) / 3]);
-        W* const vo = R.P + (size_t)(3 * i) * ldp + (size_t)m * ncol + col;
-        *reinterpret_cast<VV*>(vo) = al * acc0;
-        *reinterpret_cast<VV*>(vo + ldp) = al * acc1;
-        *reinterpret_cast<VV*>(vo + 2 * ldp) = al * acc2;
+        for (int v = 0; v < VW; ++v) al[v] = W(R.L.sa[(size_t)i * R.nwe + 1 + (VW * c + v) / 3]);
+        *reinterpret_cast<VV*>(R.block(m + 1) + (size_t)(3 * i0 + y) * ncol + VW * c) = al * t;
     }
 }
 
@@ -405,11 +460,11 @@ __device__ inline bool rows_t2(const MbdArgs& a, const RowsAtom<W>& R, int i, in
 // <u_a, u_b> of site i at node q, times alpha~_i(q)
 template <typename W>
 __device__ inline double rows_dot(const RowsAtom<W>& R, int i, int q, int x, int y) {
-    const W* p = R.P + (size_t)(3 * i) * R.ldp + 3 * q;
-    const size_t ox = (size_t)(x - 1) * R.ncol, oy = (size_t)(y - 1) * R.ncol;
+    const size_t o = (size_t)(3 * i) * R.ncol + 3 * q;
+    const W *px = R.block(x) + o, *py = R.block(y) + o;
     double d = 0.0;
-    for (int r = 0; r < 3; ++r, p += R.ldp)
-        for (int c = 0; c < 3; ++c) d += double(p[ox + c]) * double(p[oy + c]);
+    for (int r = 0; r < 3; ++r)
+        for (int c = 0; c < 3; ++c) d += double(px[r * R.ncol + c]) * double(py[r * R.ncol + c]);
     return d;
 }
 
@@ -439,55 +494,88 @@ __device__ inline double rows_alpha_adjoint(const MbdArgs& a, const RowsAtom<W>&
 }
 
 // Adjoints of the polarisabilities (sites other than the central one), Q = W D Z and the
-// u_0 terms of Tbar's central block column (into V: nine values per site, see k_mbd.hip),
-// by threads t = first, first + step, ..
-template <typename W, bool TB, class CF>
-__device__ inline void rows_operands(const MbdArgs& a, const RowsAtom<W>& R, double wk, int first, int step, CF cfq) {
+// u_0 terms of Tbar's central block column (into V: nine values per site, see k_mbd.hip).
+// One (site, node) per lane, 64 / nq sites per wavefront (wavefronts first, first + step,
+// ..): its nine values of each Krylov block are read once for all three.  part: nine
+// doubles per lane of the wavefront's in LDS, for the sum of the central terms over the
+// nodes.  NM: body orders up to NM (register arrays).
+template <typename W, bool TB, int NM, class CF>
+__device__ inline void rows_operands(const MbdArgs& a, const RowsAtom<W>& R, double wk, int first, int step,
+                                        double* part, CF cfq) {
     const MbdLds& L = R.L;
-    const int nq = R.nq, ncol = R.ncol, n_max = a.n_max;
-    for (int t = first; t < R.nK * R.nwe; t += step) {
-        const int i = t / R.nwe, w = t % R.nwe;
-        if (i == 0 && w > 0) continue;   // with the moments, in k_rows_energy
-        L.ab[t] = w == 0 ? 0.0 : rows_alpha_adjoint<W, TB>(a, R, wk, i, w - 1, nullptr, cfq);
-    }
-    if (R.na > 0)
-        for (int t = first; t < R.N3 * ncol; t += step) {
-            const int r = t / ncol, col = t % ncol, q = col / 3;
-            const double scale = wk * a.wq[q];
-            const W* pr = R.P + (size_t)r * R.ldp + col;
-            W* qr = R.Q + (size_t)r * R.ldq + col;
-            double u[kMaxNmax - 1];
+    const int nq = R.nq, ncol = R.ncol, n_max = a.n_max, lane = threadIdx.x & 63;
+    const int spw = 64 / nq;                       // nq <= 32
+    const int s = lane / nq, q = lane - s * nq;
+    for (int i0 = spw * first; i0 < R.nK; i0 += spw * step) {
+        const int i = i0 + s;
+        if (s < spw && i < R.nK) {
+            const double al = L.sa[(size_t)i * R.nwe + 1 + q];
+            const double scale = wk * a.wq[q], sc = scale * L.sqa[q];
+            double pr[NM + 1];                     // <u_x, u_{n-x}>_i summed over x, times alpha~_i
 #pragma unroll
-            for (int b = 1; b < kMaxNmax - 1; ++b) u[b] = b <= R.na ? double(pr[(size_t)(b - 1) * ncol]) : 0.0;
+            for (int n = 2; n <= NM; ++n) pr[n] = 0.0;
 #pragma unroll
-            for (int x = 1; x < kMaxNmax - 1; ++x) {
-                if (x > R.na) break;
-                double z = 0.0;
+            for (int r = 0; r < 3; ++r) {
+                const size_t o = (size_t)(3 * i + r) * ncol + 3 * q;
+                double u[NM][3];
 #pragma unroll
-                for (int b = 1; b < kMaxNmax - 1; ++b)
-                    if (b <= n_max - 1 - x) z += cfq(min(x + b + 1, kMaxNmax), q) * u[b];
-                qr[(size_t)(x - 1) * ncol] = W(scale * z);
+                for (int b = 1; b < NM; ++b)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) u[b][c] = b < n_max ? double(R.block(b)[o + c]) : 0.0;
+#pragma unroll
+                for (int n = 2; n <= NM; ++n)
+#pragma unroll
+                    for (int x = 1; 2 * x <= n; ++x)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) pr[n] += (2 * x == n ? 1.0 : 2.0) * u[x][c] * u[n - x][c];
+                W* qr = R.Q + (size_t)(3 * i + r) * R.ldq + 3 * q;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    double z0 = 0.0;
+#pragma unroll
+                    for (int b = 1; b < NM; ++b)
+                        if (b < n_max) z0 += ((TB && b == 1) ? 0.0 : cfq(b + 1, q)) * u[b][c];
+                    part[9 * lane + 3 * r + c] = sc * z0;
+#pragma unroll
+                    for (int x = 1; x < NM - 1; ++x) {
+                        if (x > R.na) break;
+                        double z = 0.0;
+#pragma unroll
+                        for (int b = 1; x + b < NM; ++b)
+                            if (x + b < n_max) z += cfq(x + b + 1, q) * u[b][c];
+                        qr[(size_t)(x - 1) * ncol + c] = W(scale * z);
+                    }
+                }
             }
+            if (i > 0) {   // (the central site's with the moments, in k_rows_energy)
+                double t = 0.0;
+#pragma unroll
+                for (int n = 2; n <= NM; ++n) {
+                    if (n > n_max) break;
+                    if (TB && n == 2) t += cfq(2, q) * L.sa[1 + q] * al * L.fg[i];   // alpha~_k alpha~_i t2_i
+                    else t += cfq(n, q) * (pr[n] / al);
+                }
+                L.ab[(size_t)i * R.nwe + 1 + q] = scale * t / al;
+            }
+            if (q == 0) L.ab[(size_t)i * R.nwe] = 0.0;
         }
-    for (int t = 9 + first; t < 3 * R.N3; t += step) {
-        const W* p = R.P + (size_t)(t / 3) * R.ldp + t % 3;
-        double s = 0.0;
-        for (int q = 0; q < nq; ++q) {
-            double z = 0.0;
-            for (int b = 1; b <= n_max - 1; ++b)
-                z += ((TB && b == 1) ? 0.0 : cfq(b + 1, q)) * double(p[(size_t)(b - 1) * ncol + 3 * q]);
-            s += a.wq[q] * L.sqa[q] * z;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        for (int e = lane; e < 9 * spw; e += 64) {
+            const int se = e / 9;
+            if (i0 + se >= R.nK) continue;
+            double t = 0.0;
+            for (int y = 0; y < nq; ++y) t += part[9 * (se * nq + y) + e % 9];
+            R.V[(size_t)9 * (i0 + se) + e % 9] = W(t);
         }
-        R.V[t] = W(wk * s);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     }
 }
-
 // ---------------------------------------------------------------------------
 // Spectrum bounds and fitted coefficients, moments, energy, and the central site's
 // adjoints; with fitted coefficients or two-body radii (whose state stays in this
 // workgroup) also the operands.
 // ---------------------------------------------------------------------------
-template <typename W, bool TB>
+template <typename W, bool TB, int NM>
 __global__ void __launch_bounds__(kAtomThreads) k_rows_energy(MbdArgs a) {
     extern __shared__ double lds[];
     const int k = a.order[blockIdx.x], tid = threadIdx.x;
@@ -590,8 +678,9 @@ __global__ void __launch_bounds__(kAtomThreads) k_rows_energy(MbdArgs a) {
     if (!a.forces) return;
     if (tid < nq) L.ab[1 + tid] = rows_alpha_adjoint<W, TB>(a, R, wk, 0, tid, L.mu, cfq);
     if (!(fit || TB)) return;   // k_rows_operands follows
-    if (fit) rows_operands<W, TB>(a, R, wk, tid, blockDim.x, [&](int n, int q) { return L.cf[q * (kMaxNmax + 1) + n]; });
-    else rows_operands<W, TB>(a, R, wk, tid, blockDim.x, [&](int n, int) { return a.coef[n]; });
+    double* const op = parts + (size_t)rs * (n_max + 1) * nq + (size_t)wave * 64 * 9;
+    if (fit) rows_operands<W, TB, NM>(a, R, wk, wave, nwave, op, [&](int n, int q) { return L.cf[q * (kMaxNmax + 1) + n]; });
+    else rows_operands<W, TB, NM>(a, R, wk, wave, nwave, op, [&](int n, int) { return a.coef[n]; });
     if constexpr (TB) {
         // the two-body term's pair derivative C2 = kappa T2_kj, kappa = 2 w_k sum_q W_q c_2
         // alpha~_k alpha~_j, contracted with dT2/dp and, through S~, with dT2/dR~: the central
@@ -626,7 +715,7 @@ __global__ void __launch_bounds__(kAtomThreads) k_rows_energy(MbdArgs a) {
     }
 }
 
-template <typename W>
+template <typename W, int NM>
 __global__ void __launch_bounds__(kRowsThreads) k_rows_operands(MbdArgs a, int parts) {
     int at, part;
     rows_place(blockIdx.x, parts, at, part);
@@ -634,19 +723,24 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_operands(MbdArgs a, int p
     const int k = a.order[at];
     const RowsAtom<W> R = rows_atom<W>(a, k, nullptr);
     const double wk = a.e_weight ? a.e_weight[k] : 1.0;
-    rows_operands<W, false>(a, R, wk, part * kRowsThreads + threadIdx.x, parts * kRowsThreads,
+    __shared__ double terms[kRowsWaves * 64 * 9];
+    const int wave = threadIdx.x >> 6;
+    rows_operands<W, false, NM>(a, R, wk, part * kRowsWaves + wave, parts * kRowsWaves, terms + wave * 64 * 9,
                             [&](int n, int) { return a.coef[n]; });
 }
 
 // ---------------------------------------------------------------------------
-// Each unordered coupled pair once: from row i over its partners j < i (a prefix of the
-// row), Tbar_ij = P_i Q_j^T (and the u_0 terms for j = 0), C = Tbar_ij + Tbar_ij^T, and
-// the pair's terms (its gradient with respect to r_i and its R~ term) into the entry's
-// slot of a buffer, in the place of its T_LR coefficients (used for the last time by the
-// products).  A wavefront per row: eight pairs at a time, eight lanes per pair (16 bytes
-// of a row each, P_i from LDS); the pairs' C wait in LDS so that the evaluation of the
-// radial parts, far longer than a pair's sums, runs with a pair on every lane.
+// Each unordered coupled pair once: from row i over its partners j < i, Tbar_ij = P_i Q_j^T
+// (and the u_0 terms for j = 0), C = Tbar_ij + Tbar_ij^T, and the pair's terms (its
+// gradient with respect to r_i and its R~ term) into the entry's slot of a buffer, in the
+// place of its T_LR coefficients (used for the last time by the products).  Three rows per
+// wavefront, over the union of their entries: eight entries at a time, eight lanes per
+// entry (16 bytes of a row each), the partner's Q loaded once for the three rows' P in LDS;
+// the pairs' C wait in LDS so that the evaluation of the radial parts, longer than a
+// pair's sums, runs with a pair on every lane.
 // ---------------------------------------------------------------------------
+constexpr int kPairWindow = 64 / kTriple;   // union entries per window: a lane per pair
+
 template <typename W, int VW>
 __global__ void __launch_bounds__(kRowsThreads) k_rows_pairs(MbdArgs a, int parts) {
     extern __shared__ double lds[];
@@ -657,85 +751,108 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_pairs(MbdArgs a, int part
     const RowsAtom<W> R = rows_atom<W>(a, a.order[at], nullptr);
     const MbdLds& L = R.L;
     const StructInfo& SI = *R.SI;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nK = R.nK, KK = R.ldq;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
+    const int nK = R.nK, KK = R.ldq, ncol = a.ncol;
     double* const cb = lds + (size_t)wave * 64 * 7;      // six values of C per pair, padded to seven
-    W* const pi = reinterpret_cast<W*>(lds + kRowsWaves * 64 * 7) + (size_t)wave * ((3 * KK + 3) / 4 * 4);
+    W* const pi = reinterpret_cast<W*>(lds + nwave * 64 * 7) + (size_t)wave * ((9 * KK + 3) / 4 * 4);
     const int pu = lane >> 3, pt = lane & 7;
-    const int i0 = (part * kRowsWaves + wave) * kRowsPerWave;
-    for (int i = i0; i < min(i0 + kRowsPerWave, nK); ++i) {
-        const int n = R.len[i];
-        const size_t e0 = R.row0(i);
-        int nlo = 0;   // partners below i
-        for (int s0 = 0; s0 < n; s0 += 64) nlo += __popcll(__ballot(s0 + lane < n && R.pj[e0 + s0 + lane] < i));
-        if (nlo == 0) continue;   // uniform
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        for (int e = VW * lane; e < 3 * KK; e += VW * 64)
-            *reinterpret_cast<VV*>(pi + e) = *reinterpret_cast<const VV*>(R.P + (size_t)(3 * i + e / KK) * R.ldp + e % KK);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        for (int c0 = 0; c0 < nlo; c0 += 64) {
-            const int m = min(64, nlo - c0);
-            const int jl = R.pj[e0 + c0 + min(lane, m - 1)];   // the partner of this lane's pair
-            for (int s0 = 0; s0 < m; s0 += 8) {
-                const int j = __shfl(jl, min(s0 + pu, m - 1));
-                const W* qj = R.Q + (size_t)(3 * j) * R.ldq;
-                double sb[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-                for (int kk = VW * pt; kk < KK; kk += 8 * VW) {
-                    VV pv[3], qv[3];
+    const int grp = 1 + part * nwave + wave;             // (the central row has no partner below)
+    const int i0 = 1 + kTriple * (grp - 1);
+    if (i0 >= nK) return;
+    const int nr = min(kTriple, nK - i0);
+    const int nu = R.ulen[grp];
+    const size_t u0 = R.row0(i0);
+    size_t e0[kTriple];                                  // next entry of each row
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        pv[c] = *reinterpret_cast<const VV*>(pi + c * KK + kk);
-                        qv[c] = *reinterpret_cast<const VV*>(qj + (size_t)c * R.ldq + kk);
+    for (int x = 0; x < kTriple; ++x) e0[x] = R.row0(min(i0 + x, nK - 1));
+    for (int e = VW * lane; e < 3 * nr * KK; e += VW * 64) {   // P of the rows: [row][b ncol + col]
+        const int row = e / KK, kk = e - row * KK, b = kk / ncol;
+        *reinterpret_cast<VV*>(pi + e) =
+            *reinterpret_cast<const VV*>(R.block(b + 1) + (size_t)(3 * i0 + row) * ncol + (kk - b * ncol));
+    }
+    for (int e = 3 * nr * KK + lane; e < 9 * KK; e += 64) pi[e] = W(0);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    const unsigned long long below = (1ull << lane) - 1ull;
+    for (int t0 = 0; t0 < nu; t0 += kPairWindow) {
+        const int cnt = min(kPairWindow, nu - t0);
+        const int ent = lane < cnt ? R.uni[u0 + t0 + lane] : 0;
+        const int jw = ent & ((1 << kSlotBits) - 1);
+        if (__ballot(lane < cnt && jw < i0 + nr - 1) == 0) break;   // ascending: no partner below is left
+        // rank of this lane's entry in each row's list
+        int rank[kTriple];
+#pragma unroll
+        for (int x = 0; x < kTriple; ++x) rank[x] = __popcll(__ballot((ent >> (kSlotBits + x)) & 1) & below);
+        for (int s0 = 0; s0 < cnt; s0 += 8) {
+            const int j = __shfl(jw, min(s0 + pu, cnt - 1));
+            const W* qj = R.Q + (size_t)(3 * j) * R.ldq;
+            double sb[kTriple][9];
+#pragma unroll
+            for (int x = 0; x < kTriple; ++x)
+#pragma unroll
+                for (int y = 0; y < 9; ++y) sb[x][y] = 0.0;
+            for (int kk = VW * pt; kk < KK; kk += 8 * VW) {
+                VV qv[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) qv[c] = *reinterpret_cast<const VV*>(qj + (size_t)c * R.ldq + kk);
+#pragma unroll
+                for (int x = 0; x < kTriple; ++x)
+#pragma unroll
+                    for (int y = 0; y < 3; ++y) {
+                        const VV pv = *reinterpret_cast<const VV*>(pi + (3 * x + y) * KK + kk);
+#pragma unroll
+                        for (int c = 0; c < 3; ++c)
+#pragma unroll
+                            for (int v = 0; v < VW; ++v) sb[x][3 * y + c] += double(pv[v]) * double(qv[c][v]);
                     }
-#pragma unroll
-                    for (int x = 0; x < 3; ++x)
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-#pragma unroll
-                            for (int v = 0; v < VW; ++v) sb[3 * x + c] += double(pv[x][v]) * double(qv[c][v]);
-                        }
-                }
-#pragma unroll
-                for (int x = 0; x < 9; ++x) {
-                    sb[x] += __shfl_xor(sb[x], 1);
-                    sb[x] += __shfl_xor(sb[x], 2);
-                    sb[x] += __shfl_xor(sb[x], 4);
-                }
-                if (pt == 0 && s0 + pu < m) {
-                    if (j == 0) {   // the central column's u_0 terms
-#pragma unroll
-                        for (int x = 0; x < 9; ++x) sb[x] += double(R.V[(size_t)9 * i + x]);
-                    }
-                    double* c = cb + 7 * (s0 + pu);
-                    c[0] = 2.0 * sb[0];
-                    c[1] = sb[1] + sb[3];
-                    c[2] = sb[2] + sb[6];
-                    c[3] = 2.0 * sb[4];
-                    c[4] = sb[5] + sb[7];
-                    c[5] = 2.0 * sb[8];
-                }
             }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            if (lane < m) {
-                const double* c = cb + 7 * lane;
-                const double C[9] = {c[0], c[1], c[2], c[1], c[3], c[4], c[2], c[4], c[5]};
-                const int j = jl;
-                const double v[3] = {L.px[i] - L.px[j], L.py[i] - L.py[j], L.pz[i] - L.pz[j]};
-                const double r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-                const double rcut = (i == 0 || j == 0) ? SI.r_mbd1 : SI.r_mbd2;
-                const double rh[3] = {v[0] / r, v[1] / r, v[2] / r};
-                const LrPair<W> lp = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut), W(a.r_buf));
-                double gp[3];
-                radial_tensor_grad(rh, r, double(lp.A), double(lp.dA), double(lp.dB), C, gp);
-                double rCr = 0.0;
-                for (int x = 0; x < 3; ++x)
-                    for (int y = 0; y < 3; ++y) rCr += rh[x] * C[3 * x + y] * rh[y];
-                const double ct = (3.0 * rCr - (C[0] + C[4] + C[8])) / (r * r * r);
-                R.rec[e0 + c0 + lane] = typename RowsAtom<W>::W4{
-                    W(gp[0]), W(gp[1]), W(gp[2]), W(a.beta * double(lp.fLR) * double(lp.dfS) * ct)};
+#pragma unroll
+            for (int x = 0; x < kTriple; ++x) {
+                double c[6] = {2.0 * sb[x][0], sb[x][1] + sb[x][3], sb[x][2] + sb[x][6],
+                               2.0 * sb[x][4], sb[x][5] + sb[x][7], 2.0 * sb[x][8]};
+#pragma unroll
+                for (int y = 0; y < 6; ++y) {
+                    c[y] += __shfl_xor(c[y], 1);
+                    c[y] += __shfl_xor(c[y], 2);
+                    c[y] += __shfl_xor(c[y], 4);
+                }
+                if (pt == 0 && s0 + pu < cnt)
+#pragma unroll
+                    for (int y = 0; y < 6; ++y) cb[7 * (x * kPairWindow + s0 + pu) + y] = c[y];
             }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        // lane x kPairWindow + s: row x, entry s
+        const int x = lane / kPairWindow, s = lane - x * kPairWindow;
+        const int es = __shfl(ent, s), j = es & ((1 << kSlotBits) - 1);
+        const int k0 = __shfl(rank[0], s), k1 = __shfl(rank[1], s), k2 = __shfl(rank[2], s);
+        const int i = i0 + x;
+        if (x < nr && s < cnt && ((es >> (kSlotBits + x)) & 1) && j < i) {
+            const double* c = cb + 7 * lane;
+            double C[9] = {c[0], c[1], c[2], c[1], c[3], c[4], c[2], c[4], c[5]};
+            if (j == 0) {   // the central column's u_0 terms
+                const W* t = R.V + (size_t)9 * i;
+#pragma unroll
+                for (int y = 0; y < 3; ++y)
+#pragma unroll
+                    for (int z = 0; z < 3; ++z) C[3 * y + z] += double(t[3 * y + z]) + double(t[3 * z + y]);
+            }
+            const double v[3] = {L.px[i] - L.px[j], L.py[i] - L.py[j], L.pz[i] - L.pz[j]};
+            const double r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+            const double rcut = (i == 0 || j == 0) ? SI.r_mbd1 : SI.r_mbd2;
+            const double rh[3] = {v[0] / r, v[1] / r, v[2] / r};
+            const LrPair<W> lp = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut), W(a.r_buf));
+            double gp[3];
+            radial_tensor_grad(rh, r, double(lp.A), double(lp.dA), double(lp.dB), C, gp);
+            double rCr = 0.0;
+            for (int y = 0; y < 3; ++y)
+                for (int z = 0; z < 3; ++z) rCr += rh[y] * C[3 * y + z] * rh[z];
+            const double ct = (3.0 * rCr - (C[0] + C[4] + C[8])) / (r * r * r);
+            const size_t e = (x == 0 ? e0[0] + k0 : x == 1 ? e0[1] + k1 : e0[2] + k2);
+            R.rec[e] = typename RowsAtom<W>::W4{W(gp[0]), W(gp[1]), W(gp[2]), W(a.beta * double(lp.fLR) * double(lp.dfS) * ct)};
+        }
+#pragma unroll
+        for (int y = 0; y < kTriple; ++y) e0[y] += __popcll(__ballot((ent >> (kSlotBits + y)) & 1));
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     }
 }
 
@@ -752,8 +869,8 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_sums(MbdArgs a, int parts
     if (at >= a.n) return;
     const RowsAtom<W> R = rows_atom<W>(a, a.order[at], nullptr);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i0 = (part * kRowsWaves + wave) * kRowsPerWave;
-    for (int i = i0; i < min(i0 + kRowsPerWave, R.nK); ++i) {
+    const int i0 = (part * kRowsWaves + wave) * kTriple;
+    for (int i = i0; i < min(i0 + kTriple, R.nK); ++i) {
         double g[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         const int n = R.len[i];
         const size_t e0 = R.row0(i);
@@ -873,51 +990,65 @@ __global__ void __launch_bounds__(kAtomThreads) k_rows_final(MbdArgs a) {
     for (int e = tid; e < (nall - nK) * nw; e += blockDim.x) cap[(size_t)nK * nw + e] = 0.0;
 }
 
-// dynamic LDS of the two kernels that use any
-static size_t rows_energy_lds(const MbdArgs& a) {
+// dynamic LDS (operands: k_rows_energy forms them too)
+static size_t rows_energy_lds(const MbdArgs& a, bool operands) {
     const size_t sets = ((size_t)(a.n_max - 1) * a.nq + 7) / 8;
     const size_t rs = std::max<size_t>(1, kAtomThreads / 64 / sets);
-    return sizeof(double) * (mbd_small_doubles(a.nq, a.n_max, a.lz_steps, a.fit != 0) + rs * (a.n_max + 1) * a.nq);
+    return sizeof(double) * (mbd_small_doubles(a.nq, a.n_max, a.lz_steps, a.fit != 0) + rs * (a.n_max + 1) * a.nq +
+                             (operands ? (size_t)kAtomThreads * 9 : 0));
 }
-static size_t rows_pairs_lds(const MbdArgs& a, size_t wsz) {
+static size_t rows_pairs_lds(const MbdArgs& a, size_t wsz) {   // per wavefront
     const size_t KK = (size_t)std::max(a.n_max - 2, 0) * a.ncol;
-    return kRowsWaves * (sizeof(double) * 64 * 7 + wsz * ((3 * KK + 3) / 4 * 4));
+    return sizeof(double) * 64 * 7 + wsz * ((9 * KK + 3) / 4 * 4);
 }
 
-template <typename W, bool TB>
+template <typename W, bool TB, int NM>
 static hipError_t launch_rows_t(hipStream_t st, const MbdArgs& a, int nkmax) {
     constexpr int VW = 16 / sizeof(W);
     const bool vec = a.ncol % VW == 0;
     const unsigned atoms8 = 8u * (unsigned)((a.n + 7) / 8);
     const dim3 per_atom(a.n);
-    auto parts_of = [](int items) { return (items + kRowsWaves - 1) / kRowsWaves; };
-    const int rows = parts_of((nkmax + kRowsPerWave - 1) / kRowsPerWave);   // workgroups per atom, rows over wavefronts
-    const int nlt = a.ncol / (vec ? VW : 1), ng = 64 / std::min(nlt, 64);
-    const int prod = parts_of((1 + (nkmax - 1 + ng - 1) / ng) * ((nlt + 63) / 64));
+    auto parts_of = [](int items, int waves) { return (items + waves - 1) / waves; };
+    const int groups = (nkmax + 1) / kTriple + 1;                  // three rows per wavefront
+    const int rows = parts_of(groups, kRowsWaves);                 // workgroups per atom
+    const int nlt = a.ncol / (vec ? VW : 1);
+    const int prod = parts_of(groups * ((nlt + 63) / 64), kRowsWaves);
+    const int wl = (int)((rows_product_lds<W>(a.ncol) + 15) / 16 * 16);
     hipLaunchKernelGGL((k_rows_setup<W>), per_atom, dim3(kAtomThreads), 0, st, a);
     hipLaunchKernelGGL((k_rows_lists<W, TB>), dim3(atoms8 * rows), dim3(kRowsThreads), 0, st, a, rows);
     for (int m = 1; m < a.mmax; ++m) {
-        if (vec) hipLaunchKernelGGL((k_rows_product<W, VW>), dim3(atoms8 * prod), dim3(kRowsThreads), 0, st, a, prod, m);
-        else hipLaunchKernelGGL((k_rows_product<W, 1>), dim3(atoms8 * prod), dim3(kRowsThreads), 0, st, a, prod, m);
+        const dim3 grid(atoms8 * prod);
+        const size_t lds = (size_t)kRowsWaves * wl;
+        if (vec) hipLaunchKernelGGL((k_rows_product<W, VW>), grid, dim3(kRowsThreads), lds, st, a, prod, m, wl);
+        else hipLaunchKernelGGL((k_rows_product<W, 1>), grid, dim3(kRowsThreads), lds, st, a, prod, m, wl);
     }
-    hipLaunchKernelGGL((k_rows_energy<W, TB>), per_atom, dim3(kAtomThreads), rows_energy_lds(a), st, a);
+    const bool operands = a.forces && (a.fit || TB);   // in k_rows_energy
+    hipLaunchKernelGGL((k_rows_energy<W, TB, NM>), per_atom, dim3(kAtomThreads), rows_energy_lds(a, operands), st, a);
     if (a.forces) {
-        if (!(a.fit || TB)) {
-            const int ops = std::max(1, (nkmax + 63) / 64);
-            hipLaunchKernelGGL((k_rows_operands<W>), dim3(atoms8 * ops), dim3(kRowsThreads), 0, st, a, ops);
+        if (!operands) {
+            const int per = 2 * kRowsWaves * (64 / a.nq);   // sites of a workgroup: two rounds per wavefront
+            const int ops = parts_of(nkmax, per);
+            hipLaunchKernelGGL((k_rows_operands<W, NM>), dim3(atoms8 * ops), dim3(kRowsThreads), 0, st, a, ops);
         }
-        const size_t lds = rows_pairs_lds(a, sizeof(W));
-        if (vec) hipLaunchKernelGGL((k_rows_pairs<W, VW>), dim3(atoms8 * rows), dim3(kRowsThreads), lds, st, a, rows);
-        else hipLaunchKernelGGL((k_rows_pairs<W, 1>), dim3(atoms8 * rows), dim3(kRowsThreads), lds, st, a, rows);
+        // P of three rows in LDS per wavefront (10 KB at 12 nodes and n_max = 6): small workgroups
+        const size_t lw = rows_pairs_lds(a, sizeof(W));
+        const int pw = 2 * lw <= 64 * 1024 ? 2 : 1, pr = parts_of(groups, pw);
+        if (vec) hipLaunchKernelGGL((k_rows_pairs<W, VW>), dim3(atoms8 * pr), dim3(64 * pw), pw * lw, st, a, pr);
+        else hipLaunchKernelGGL((k_rows_pairs<W, 1>), dim3(atoms8 * pr), dim3(64 * pw), pw * lw, st, a, pr);
         hipLaunchKernelGGL((k_rows_sums<W>), dim3(atoms8 * rows), dim3(kRowsThreads), 0, st, a, rows);
         hipLaunchKernelGGL((k_rows_final<W, TB>), per_atom, dim3(kAtomThreads), 0, st, a);
     }
     return hipGetLastError();
 }
 
+template <typename W, bool TB>
+static hipError_t launch_rows_nm(hipStream_t st, const MbdArgs& a, int nkmax) {   // register arrays by the body order
+    return a.n_max <= 6 ? launch_rows_t<W, TB, 6>(st, a, nkmax) : launch_rows_t<W, TB, kMaxNmax>(st, a, nkmax);
+}
+
 hipError_t launch_mbd_rows(hipStream_t st, const MbdArgs& a, int nkmax, bool mixed, bool two_body) {
-    if (mixed) return two_body ? launch_rows_t<float, true>(st, a, nkmax) : launch_rows_t<float, false>(st, a, nkmax);
-    return two_body ? launch_rows_t<double, true>(st, a, nkmax) : launch_rows_t<double, false>(st, a, nkmax);
+    if (mixed) return two_body ? launch_rows_nm<float, true>(st, a, nkmax) : launch_rows_nm<float, false>(st, a, nkmax);
+    return two_body ? launch_rows_nm<double, true>(st, a, nkmax) : launch_rows_nm<double, false>(st, a, nkmax);
 }
 
 }  // namespace lmbd

@@ -329,8 +329,8 @@ __host__ __device__ inline int64_t mbd_dense_elements(int nK, int nq, int n_max,
 // The sparse form's workspace in the same space, offsets in elements of the workspace type
 // (size wsz), each part on a 16-byte boundary: site arrays (double); the lists, row i >= 1
 // with space for `stride` entries (every site within r_mbd2 of the structure's fullest atom,
-// the central atom, slack) and the central row for nK, as 4-vectors, int32 slots and row
-// lengths; the Krylov blocks P; V (Lanczos vectors, central terms of Tbar); with forces Q.
+// the central atom, slack) and the central row for nK, as 4-vectors, int32 slots, int32
+// unions over three rows, and lengths; the Krylov blocks P; V (Lanczos vectors, central terms of Tbar); with forces Q.
 __host__ __device__ inline int rows_stride(int nK, int m2max) { return nK < m2max + 2 ? nK : m2max + 2; }
 __host__ __device__ inline int64_t rows_cap(int nK, int m2max) {
     return nK + (int64_t)(nK - 1) * rows_stride(nK, m2max);
@@ -350,7 +350,7 @@ __host__ __device__ inline RowsLayout rows_layout(int nK, int m2max, int nq, int
         return at / wsz;
     };
     g.sites = take(8 * (int64_t)mbd_site_doubles((size_t)nK, nq));
-    g.lists = take(rows_cap(nK, m2max) * (4 * wsz + 4) + 4 * (int64_t)nK);
+    g.lists = take(rows_cap(nK, m2max) * (4 * wsz + 8) + 4 * (int64_t)nK + 4 * ((int64_t)(nK + 1) / 3 + 2));
     g.P = take(wsz * mmax * N3 * ncol);
     g.V = take(wsz * ncol * N3p);
     g.Q = take(wsz * na * N3 * ncol);
