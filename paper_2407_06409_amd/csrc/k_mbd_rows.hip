@@ -223,8 +223,12 @@ __global__ void __launch_bounds__(kAtomThreads) k_rows_setup(MbdArgs a) {
 // central block column only).  A wavefront per group of rows, its lanes testing four boxes
 // of 16 slots at a time: the first box (the central atom) and those that reach within
 // r_mbd2 of a row (all of them for the central row).  Row i has space for every site
-// within r_mbd2 of the structure's fullest atom, so the rows need no counting pass.
+// within r_mbd2 of the structure's fullest atom, so the rows need no counting pass.  The
+// coupled pairs wait in a ring in LDS until 64 are there, so that their coefficients are
+// evaluated with a pair on every lane (a tenth of the lanes where the pairs were found:
+// 988 -> 637 us for 1,728 C at 6 + 3 A, 7.9 -> 5.8 ms for 512 C at 10 + 8 A).
 // ---------------------------------------------------------------------------
+constexpr int kListRing = 256;   // at most 63 pairs wait when three rows add up to 64 each
 template <typename W, bool TB>
 __global__ void __launch_bounds__(kRowsThreads, 4) k_rows_lists(MbdArgs a, int parts) {
     int at, part;
@@ -243,11 +247,36 @@ __global__ void __launch_bounds__(kRowsThreads, 4) k_rows_lists(MbdArgs a, int p
     const int nr = grp == 0 ? 1 : min(kTriple, nK - i0);
     const int cap = grp == 0 ? nK : R.stride;
     const unsigned long long below = (1ull << lane) - 1ull;
-    int n[kTriple] = {0, 0, 0}, nu = 0;
-    bool central[kTriple] = {false, false, false};   // the row's first entry is the central atom, with r0
-    W4 r0[kTriple];
+    __shared__ int ring_all[kRowsWaves][2][kListRing];   // slot and row of the group; place in the lists
+    __shared__ double first_all[kRowsWaves][kTriple][4];
+    int(*const ring)[kListRing] = ring_all[wave];
+    double(*const first)[4] = first_all[wave];           // the entry of the central atom, per row
+    int n[kTriple] = {0, 0, 0}, nu = 0, head = 0, tail = 0;
+    for (int e = lane; e < 4 * kTriple; e += 64) first[e / 4][e % 4] = 0.0;
+    // the coefficients of up to 64 waiting pairs
+    auto evaluate = [&](int cnt) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        if (lane < cnt) {
+            const int p = (head + lane) % kListRing;
+            const int ent = ring[0][p], e = ring[1][p];
+            const int j = ent & ((1 << kSlotBits) - 1), x = ent >> kSlotBits, i = i0 + x;
+            double v[3], r;
+            (void)rows_coupled<W, TB>(R, i, j, v, r);
+            const double rcut = (i == 0 || j == 0) ? SI.r_mbd1 : SI.r_mbd2;
+            const LrPair<W> t = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut), W(a.r_buf));
+            const double sA = sqrt(fmax(double(t.A), 0.0)) / r;
+            const W4 rec = {W(sA * v[0]), W(sA * v[1]), W(sA * v[2]), t.B};
+            if (e >= 0) {
+                R.rec[R.row0(i) + e] = rec;
+                R.pj[R.row0(i) + e] = j;
+            }
+            if (j == 0)
 #pragma unroll
-    for (int x = 0; x < kTriple; ++x) r0[x] = W4{W(0), W(0), W(0), W(0)};
+                for (int c = 0; c < 4; ++c) first[x][c] = double(rec[c]);
+        }
+        head += cnt;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    };
     for (int b0 = 0; b0 < R.nbox; b0 += 64) {
         const int b = b0 + lane;
         bool near = b < R.nbox;
@@ -263,7 +292,6 @@ __global__ void __launch_bounds__(kRowsThreads, 4) k_rows_lists(MbdArgs a, int p
             }
         }
         unsigned long long m = __ballot(near);
-        bool start = b0 == 0;   // lane 0 of the first step tests the central atom
         while (m) {
             int box = 0;
             bool have = false;
@@ -280,56 +308,44 @@ __global__ void __launch_bounds__(kRowsThreads, 4) k_rows_lists(MbdArgs a, int p
             int bits = 0;
 #pragma unroll
             for (int x = 0; x < kTriple; ++x) {
-                if (x >= nr) break;   // uniform
-                const int i = i0 + x;
+                if (x >= nr) continue;   // uniform
                 double v[3], r;
-                W4 e = {W(0), W(0), W(0), W(0)};
-                const bool in = rows_coupled<W, TB>(R, i, j, v, r);
-                if (in) {
-                    const double rcut = (i == 0 || j == 0) ? SI.r_mbd1 : SI.r_mbd2;
-                    const LrPair<W> t = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut),
-                                                   W(a.r_buf));
-                    const double sA = sqrt(fmax(double(t.A), 0.0)) / r;
-                    e = W4{W(sA * v[0]), W(sA * v[1]), W(sA * v[2]), t.B};
-                    bits |= 1 << x;
-                }
+                const bool in = rows_coupled<W, TB>(R, i0 + x, j, v, r);
                 const unsigned long long mask = __ballot(in);
-                const int at_e = n[x] + __popcll(mask & below);
-                if (in && at_e < cap) {
-                    R.pj[R.row0(i) + at_e] = j;
-                    R.rec[R.row0(i) + at_e] = e;
-                }
-                if (start && i != 0 && (mask & 1ull)) {
-                    central[x] = true;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) r0[x][c] = __shfl(e[c], 0);
+                const int off = __popcll(mask & below);
+                if (in) {
+                    bits |= 1 << x;
+                    ring[0][(tail + off) % kListRing] = j | (x << kSlotBits);
+                    ring[1][(tail + off) % kListRing] = n[x] + off < cap ? n[x] + off : -1;
                 }
                 n[x] += __popcll(mask);
+                tail += __popcll(mask);
             }
             const unsigned long long any = __ballot(bits != 0);
             const int at_u = nu + __popcll(any & below);
             if (bits != 0 && at_u < nr * cap) R.uni[R.row0(i0) + at_u] = j | (bits << kSlotBits);
             nu += __popcll(any);
-            start = false;
+            while (tail - head >= 64) evaluate(64);
         }
     }
+    if (tail > head) evaluate(tail - head);
 #pragma unroll
     for (int x = 0; x < kTriple; ++x) {
-        if (x >= nr) break;
+        if (x >= nr) continue;
         const int i = i0 + x;
         if (n[x] > cap && lane == 0) {   // the row outgrew its bound: refuse the call
             atomicOr(a.err, 32);
             atomicMin(a.err_atom, R.k);
         }
         if (lane == 0) R.len[i] = min(n[x], cap);
+        const double r0 = first[x][0], r1 = first[x][1], r2 = first[x][2], r3 = first[x][3];   // zero if not coupled
         for (int col = lane; col < ncol; col += 64) {
             const int q = col / 3, c = col % 3;
             const double si = L.sqa[(size_t)i * nq + q];
-            const double s = central[x] ? si * si * L.sqa[q] : 0.0;
+            const double s = si * si * L.sqa[q], rc = c == 0 ? r0 : c == 1 ? r1 : r2;
             for (int y = 0; y < 3; ++y)
                 R.P[(size_t)(3 * i + y) * ncol + col] =
-                    W(s * (double(r0[x][y]) * double(c == 0 ? r0[x][0] : c == 1 ? r0[x][1] : r0[x][2]) +
-                           (y == c ? double(r0[x][3]) : 0.0)));
+                    W(s * ((y == 0 ? r0 : y == 1 ? r1 : r2) * rc + (y == c ? r3 : 0.0)));
         }
     }
     // (an entry beyond a row's capacity is in no list: the products would read past it)
@@ -538,12 +554,11 @@ __device__ inline void rows_operands(const MbdArgs& a, const RowsAtom<W>& R, dou
                     part[9 * lane + 3 * r + c] = sc * z0;
 #pragma unroll
                     for (int x = 1; x < NM - 1; ++x) {
-                        if (x > R.na) break;
                         double z = 0.0;
 #pragma unroll
                         for (int b = 1; x + b < NM; ++b)
                             if (x + b < n_max) z += cfq(x + b + 1, q) * u[b][c];
-                        qr[(size_t)(x - 1) * ncol + c] = W(scale * z);
+                        if (x <= R.na) qr[(size_t)(x - 1) * ncol + c] = W(scale * z);
                     }
                 }
             }
@@ -551,7 +566,7 @@ __device__ inline void rows_operands(const MbdArgs& a, const RowsAtom<W>& R, dou
                 double t = 0.0;
 #pragma unroll
                 for (int n = 2; n <= NM; ++n) {
-                    if (n > n_max) break;
+                    if (n > n_max) continue;
                     if (TB && n == 2) t += cfq(2, q) * L.sa[1 + q] * al * L.fg[i];   // alpha~_k alpha~_i t2_i
                     else t += cfq(n, q) * (pr[n] / al);
                 }
@@ -785,39 +800,54 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_pairs(MbdArgs a, int part
         for (int s0 = 0; s0 < cnt; s0 += 8) {
             const int j = __shfl(jw, min(s0 + pu, cnt - 1));
             const W* qj = R.Q + (size_t)(3 * j) * R.ldq;
-            double sb[kTriple][9];
+            double c[kTriple][6];   // C's 00, 01, 02, 11, 12, 22 (the diagonal halved)
 #pragma unroll
             for (int x = 0; x < kTriple; ++x)
 #pragma unroll
-                for (int y = 0; y < 9; ++y) sb[x][y] = 0.0;
+                for (int y = 0; y < 6; ++y) c[x][y] = 0.0;
+            // the next columns of Q are on their way while these are used
+            VV qn[3];
+            auto fetch = [&](int kk) {
+                const int ks = kk < KK ? kk : 0;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) qn[d] = *reinterpret_cast<const VV*>(qj + (size_t)d * R.ldq + ks);
+            };
+            if (KK > 0) fetch(VW * pt);
             for (int kk = VW * pt; kk < KK; kk += 8 * VW) {
-                VV qv[3];
+                const VV qv[3] = {qn[0], qn[1], qn[2]};
+                fetch(kk + 8 * VW);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) qv[c] = *reinterpret_cast<const VV*>(qj + (size_t)c * R.ldq + kk);
+                for (int x = 0; x < kTriple; ++x) {
+                    VV pv[3];
 #pragma unroll
-                for (int x = 0; x < kTriple; ++x)
+                    for (int y = 0; y < 3; ++y) pv[y] = *reinterpret_cast<const VV*>(pi + (3 * x + y) * KK + kk);
 #pragma unroll
-                    for (int y = 0; y < 3; ++y) {
-                        const VV pv = *reinterpret_cast<const VV*>(pi + (3 * x + y) * KK + kk);
-#pragma unroll
-                        for (int c = 0; c < 3; ++c)
-#pragma unroll
-                            for (int v = 0; v < VW; ++v) sb[x][3 * y + c] += double(pv[v]) * double(qv[c][v]);
+                    for (int v = 0; v < VW; ++v) {
+                        const double p0 = pv[0][v], p1 = pv[1][v], p2 = pv[2][v];
+                        const double q0 = qv[0][v], q1 = qv[1][v], q2 = qv[2][v];
+                        c[x][0] += p0 * q0;
+                        c[x][1] += p0 * q1;
+                        c[x][1] += p1 * q0;
+                        c[x][2] += p0 * q2;
+                        c[x][2] += p2 * q0;
+                        c[x][3] += p1 * q1;
+                        c[x][4] += p1 * q2;
+                        c[x][4] += p2 * q1;
+                        c[x][5] += p2 * q2;
                     }
+                }
             }
 #pragma unroll
             for (int x = 0; x < kTriple; ++x) {
-                double c[6] = {2.0 * sb[x][0], sb[x][1] + sb[x][3], sb[x][2] + sb[x][6],
-                               2.0 * sb[x][4], sb[x][5] + sb[x][7], 2.0 * sb[x][8]};
 #pragma unroll
                 for (int y = 0; y < 6; ++y) {
-                    c[y] += __shfl_xor(c[y], 1);
-                    c[y] += __shfl_xor(c[y], 2);
-                    c[y] += __shfl_xor(c[y], 4);
+                    c[x][y] += __shfl_xor(c[x][y], 1);
+                    c[x][y] += __shfl_xor(c[x][y], 2);
+                    c[x][y] += __shfl_xor(c[x][y], 4);
                 }
                 if (pt == 0 && s0 + pu < cnt)
 #pragma unroll
-                    for (int y = 0; y < 6; ++y) cb[7 * (x * kPairWindow + s0 + pu) + y] = c[y];
+                    for (int y = 0; y < 6; ++y) cb[7 * (x * kPairWindow + s0 + pu) + y] = c[x][y];
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -828,7 +858,7 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_pairs(MbdArgs a, int part
         const int i = i0 + x;
         if (x < nr && s < cnt && ((es >> (kSlotBits + x)) & 1) && j < i) {
             const double* c = cb + 7 * lane;
-            double C[9] = {c[0], c[1], c[2], c[1], c[3], c[4], c[2], c[4], c[5]};
+            double C[9] = {2.0 * c[0], c[1], c[2], c[1], 2.0 * c[3], c[4], c[2], c[4], 2.0 * c[5]};
             if (j == 0) {   // the central column's u_0 terms
                 const W* t = R.V + (size_t)9 * i;
 #pragma unroll
@@ -858,9 +888,10 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_pairs(MbdArgs a, int part
 
 // ---------------------------------------------------------------------------
 // Every row's pair terms summed over its partners: partner j < i from the row's own slots,
-// j > i from the slot in j's row (found by binary search in the sorted row) with the
-// gradient's sign turned: it is odd in rhat, the R~ term even.  Lane l takes the partners
-// l, l + 64, ..; the lanes are combined in a fixed order.
+// j > i from the slot in j's row with the gradient's sign turned: it is odd in rhat, the
+// R~ term even.  Three rows per wavefront over the union of their entries: lane l takes the
+// entries l, l + 64, ..; one binary search in j's sorted row finds the slots of all three
+// rows, which follow one another there.  The lanes are combined in a fixed order.
 // ---------------------------------------------------------------------------
 template <typename W>
 __global__ void __launch_bounds__(kRowsThreads) k_rows_sums(MbdArgs a, int parts) {
@@ -869,41 +900,75 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_sums(MbdArgs a, int parts
     if (at >= a.n) return;
     const RowsAtom<W> R = rows_atom<W>(a, a.order[at], nullptr);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i0 = (part * kRowsWaves + wave) * kTriple;
-    for (int i = i0; i < min(i0 + kTriple, R.nK); ++i) {
-        double g[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        const int n = R.len[i];
-        const size_t e0 = R.row0(i);
-        for (int s = lane; s < n; s += 64) {
-            const int j = R.pj[e0 + s];
-            size_t src = e0 + s;
-            double sg = 1.0;
-            if (j > i) {
-                const size_t b = R.row0(j);
-                const int end = R.len[j];
-                int lo = 0, hi = end;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (R.pj[b + mid] < i) lo = mid + 1;
-                    else hi = mid;
+    const int grp = part * kRowsWaves + wave;
+    const int i0 = grp == 0 ? 0 : 1 + kTriple * (grp - 1);
+    if (i0 >= R.nK) return;
+    const int nr = grp == 0 ? 1 : min(kTriple, R.nK - i0);
+    const int nu = R.ulen[grp];
+    const size_t u0 = R.row0(i0);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    size_t e0[kTriple];
+    double g[kTriple][9];
+#pragma unroll
+    for (int x = 0; x < kTriple; ++x) {
+        e0[x] = R.row0(min(i0 + x, R.nK - 1));
+#pragma unroll
+        for (int y = 0; y < 9; ++y) g[x][y] = 0.0;
+    }
+    for (int t0 = 0; t0 < nu; t0 += 64) {
+        const int ent = t0 + lane < nu ? R.uni[u0 + t0 + lane] : 0;
+        const int j = ent & ((1 << kSlotBits) - 1), bits = ent >> kSlotBits;
+        size_t up = 0;      // the slot of the first of the rows in j's row
+        int end = 0;
+        if (bits != 0 && j > i0) {
+            const size_t b = R.row0(j);
+            const int n = R.len[j];
+            int lo = 0, hi = n;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (R.pj[b + mid] < i0) lo = mid + 1;
+                else hi = mid;
+            }
+            up = b + lo;
+            end = n - lo;
+        }
+#pragma unroll
+        for (int x = 0; x < kTriple; ++x) {
+            const bool in = (bits >> x) & 1;
+            const unsigned long long mask = __ballot(in);
+            const int i = i0 + x;
+            if (in) {
+                size_t src = e0[x] + __popcll(mask & below);
+                double sg = 1.0;
+                bool ok = true;
+                if (j > i) {
+                    ok = end > 0 && R.pj[up] == i;
+                    src = up;
+                    sg = -1.0;
+                    ++up;
+                    --end;
                 }
-                if (!(lo < end && R.pj[b + lo] == i)) {   // the coupling relation is symmetric: never taken
+                if (ok) {
+                    const typename RowsAtom<W>::W4 t = R.rec[src];
+                    g[x][0] += sg * double(t[0]);
+                    g[x][1] += sg * double(t[1]);
+                    g[x][2] += sg * double(t[2]);
+                    g[x][3] += double(t[3]);
+                } else {   // the coupling relation is symmetric: never taken
                     atomicOr(a.err, 32);
                     atomicMin(a.err_atom, R.k);
-                    continue;
                 }
-                src = b + lo;
-                sg = -1.0;
             }
-            const typename RowsAtom<W>::W4 t = R.rec[src];
-            g[0] += sg * double(t[0]);
-            g[1] += sg * double(t[1]);
-            g[2] += sg * double(t[2]);
-            g[3] += double(t[3]);
+            e0[x] += __popcll(mask);
         }
+    }
+#pragma unroll
+    for (int x = 0; x < kTriple; ++x) {
+        if (x >= nr) continue;
         double tot[9];
-        wave_sum9(g, tot);
+        wave_sum9(g[x], tot);
         if (lane == 0) {
+            const int i = i0 + x;
             R.L.g[(size_t)i * 3 + 0] = tot[0];
             R.L.g[(size_t)i * 3 + 1] = tot[1];
             R.L.g[(size_t)i * 3 + 2] = tot[2];
