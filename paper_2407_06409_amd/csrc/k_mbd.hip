@@ -63,6 +63,11 @@
 namespace lmbd {
 
 
+// Doubles of the site arrays before the polarisability adjoints (see mbd_lds)
+__host__ __device__ inline size_t mbd_adjoint_offset(int nk, int nq) {
+    return (size_t)nk * (3 + (nq + 1) + (nq > 12 ? nq : 12) + 3);
+}
+
 size_t mbd_lds_bytes(int nkmax, int nq, int n_max, int lz_steps, bool fit) {
     return sizeof(double) * (mbd_site_doubles((size_t)nkmax, nq) + mbd_small_doubles(nq, n_max, lz_steps, fit));
 }
@@ -188,6 +193,129 @@ __device__ __forceinline__ void mfma_gemm_nt(int M, int N, int K, const W* __res
     __syncthreads();
 }
 
+// Products with T_LR.  T_LR is stored as one 4-vector per unordered pair of sites, s =
+// sqrt(A) rhat and B (block = s s^T + B I, A >= 0), and expanded on the way into the matrix
+// cores: a product reads T_LR once and nothing else of size, and with stored elements it
+// ran at the rate of those reads (600 KB per product at 91 sites: 112k cycles, 5 TB/s over
+// the chip in the Lanczos iteration).  The 4-vectors are 134 KB in FP64, about an XCD's L2
+// over its compute units.
+// out(m, n) = sum_k T[m][k] X[n][k] over k = (site j, component y): a k-step of the MFMA
+// takes one component of four sites (lane group lk: site j0 + lk), a chunk three steps.
+// X: operand rows by column, planes by component: X[n ldx + y ldp + j], in LDS where it
+// fits (planes padded with zeros to ldp, a multiple of four chunks), else in global memory
+// (planes of nK).  Items of one 16-row strip times NV column tiles; a wavefront takes its
+// strips in groups of kDeep chunks, the loads of the next group (clamped indices, no
+// conditions: a load in a conditional block is waited for at once) on their way during
+// the matrix work of this one.  Strips of 16 rows also spread evenly over the SIMDs (18
+// strips at 91 sites: 5, 5, 4, 4), where six 48-row items kept two of eight wavefronts
+// idle.  1,728 C at 6 A, per atom: four products 551k -> 396k cycles (FP32 325k -> 257k),
+// the Lanczos iteration's eleven 2,427k -> 1,596k.
+constexpr int kDeep = 4;
+__device__ inline int tri(int i, int j) {
+    const int hi = max(i, j), lo = min(i, j);
+    return ((hi * (hi + 1)) >> 1) + lo;
+}
+template <int NV, bool LDSX, typename W, typename ST>
+__device__ __forceinline__ void mfma_strips(int nK, int N, const W* __restrict__ rec, const W* X, int ldx, int ldp,
+                                            int tc0, ST st) {
+    typedef MfmaW<W> Mf;
+    typedef W V4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63, nwave = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    const int M = 3 * nK;
+    const int mt = (M + 15) / 16, ng = (nK + 4 * kDeep - 1) / (4 * kDeep);
+    const int total = (wave < mt ? (mt - wave + nwave - 1) / nwave : 0) * ng;   // groups of this wavefront
+    if (total == 0) return;
+    auto row_of = [&](int strip) { return min((16 * strip + li) / 3, nK - 1); };
+    int ls = wave, lg = 0;   // strip and group of the next loads
+    int row = row_of(ls);
+    auto fetch = [&](V4(&v)[kDeep]) {
+#pragma unroll
+        for (int j = 0; j < kDeep; ++j)
+            v[j] = *reinterpret_cast<const V4*>(rec + 4 * (unsigned)tri(row, min(4 * (kDeep * lg + j) + lk, nK - 1)));
+        lg = lg + 1 == ng ? 0 : lg + 1;
+        ls = lg == 0 ? ls + nwave : ls;
+        row = row_of(ls);
+    };
+    const W* px[NV];
+#pragma unroll
+    for (int c = 0; c < NV; ++c) px[c] = X + (size_t)min(16 * (tc0 + c) + li, N - 1) * ldx;
+    typename Mf::acc acc[NV];
+    W unit[3];               // the row's component as a unit vector
+    auto begin = [&](int strip) {
+        const int comp = (16 * strip + li) % 3;
+#pragma unroll
+        for (int y = 0; y < 3; ++y) unit[y] = comp == y ? W(1) : W(0);
+#pragma unroll
+        for (int c = 0; c < NV; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[c][q] = W(0);
+    };
+    int cs = wave, cg = 0;   // strip and group in work
+    begin(cs);
+    V4 cur[kDeep], nxt[kDeep];
+    fetch(cur);
+    for (int x = 0; x < total; ++x) {
+        fetch(nxt);
+#pragma unroll
+        for (int j = 0; j < kDeep; ++j) {
+            const int site = 4 * (kDeep * cg + j) + lk;
+            W b[3][NV];
+#pragma unroll
+            for (int y = 0; y < 3; ++y)
+#pragma unroll
+                for (int c = 0; c < NV; ++c) {
+                    if constexpr (LDSX) {
+                        b[y][c] = px[c][y * ldp + site];
+                    } else {
+                        const W v = px[c][y * ldp + min(site, nK - 1)];
+                        b[y][c] = site < nK ? v : W(0);
+                    }
+                }
+            const V4 r = cur[j];
+            const W sx = unit[0] * r[0] + unit[1] * r[1] + unit[2] * r[2];
+#pragma unroll
+            for (int y = 0; y < 3; ++y) {
+                const W t = sx * r[y] + unit[y] * r[3];
+#pragma unroll
+                for (int c = 0; c < NV; ++c) acc[c] = Mf::mma(t, b[y][c], acc[c]);
+            }
+        }
+        if (++cg == ng) {   // uniform
+#pragma unroll
+            for (int c = 0; c < NV; ++c) {
+                const int n = 16 * (tc0 + c) + li;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int m = 16 * cs + Mf::acc_row(lk, q);
+                    if (n < N && m < M) st(m, n, acc[c][q]);
+                }
+            }
+            cg = 0;
+            cs += nwave;
+            begin(cs);
+        }
+#pragma unroll
+        for (int j = 0; j < kDeep; ++j) cur[j] = nxt[j];
+    }
+}
+// all column tiles, three at a time; ends with a barrier
+template <bool LDSX, typename W, typename ST>
+__device__ __forceinline__ void product_tlr(int nK, int N, const W* rec, const W* X, int ldx, int ldp, ST st) {
+    const int nt = (N + 15) / 16;
+    for (int tc0 = 0; tc0 < nt; tc0 += 3) {
+        if (nt - tc0 >= 3) mfma_strips<3, LDSX, W>(nK, N, rec, X, ldx, ldp, tc0, st);
+        else if (nt - tc0 == 2) mfma_strips<2, LDSX, W>(nK, N, rec, X, ldx, ldp, tc0, st);
+        else mfma_strips<1, LDSX, W>(nK, N, rec, X, ldx, ldp, tc0, st);
+    }
+    __syncthreads();
+}
+// The operand in LDS: planes of whole groups of chunks, and an odd row stride, so that the
+// sixteen columns of a tile start on different banks
+__host__ __device__ inline int operand_plane(int nK) { return (nK + 4 * kDeep - 1) / (4 * kDeep) * (4 * kDeep); }
+__host__ __device__ inline int operand_ld(int nK) { return (3 * operand_plane(nK)) | 1; }
+
 // 512 threads: the eight wavefronts share the GEMM items of an atom (six
 // 48-row items per Krylov product, 21 lower-triangle items of Tbar), which
 // balances them better than four (measured 4.55 -> 4.42 ms FP64, 3.07 -> 2.62
@@ -199,7 +327,7 @@ constexpr int kMbdThreads = 512;
 // TB: the atoms' structures have two-body radii of their own (a separate instantiation,
 // so that the other kernel carries none of its registers)
 template <typename W, bool TB>
-__global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax) {
+__global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax, int vlds) {
     extern __shared__ double lds[];
     const int k = a.order[blockIdx.x];
     const int tid = threadIdx.x;
@@ -213,7 +341,11 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax) {
     const bool fit = a.fit != 0;
     constexpr bool has2b = TB;
     W* const wbase = static_cast<W*>(a.work) + a.work_off[k];
-    MbdLds L = mbd_lds(lds, nkmax, nq, lds + mbd_site_doubles((size_t)nkmax, nq), n_max, fit);
+    // vlds: doubles of LDS from the polarisability adjoints on (a multiple of two), which the
+    // products' operand takes until those are formed; 0: the operand stays in global memory
+    const size_t adj = mbd_adjoint_offset(nkmax, nq);
+    MbdLds L = mbd_lds(lds, nkmax, nq, lds + (vlds ? adj + vlds : mbd_site_doubles((size_t)nkmax, nq)), n_max, fit);
+    W* const Vl = reinterpret_cast<W*>(lds + ((adj + 1) & ~(size_t)1));
     // c_n at node q: fitted per atom and node, or the common series
     // (fitted: two copies in LDS, [kMaxNmax + 1][nq] here and [nq][kMaxNmax + 1] for the adjoint operands,
     // whose per-element loop keeps one node's coefficients at fixed offsets)
@@ -229,10 +361,10 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax) {
     const int na = a.paper ? 0 : max(n_max - 2, 0);
     const int KK = na * ncol, KKp = (KK + 3) / 4 * 4;
     const int N3p = (int)al4(N3);                            // row stride of T and of V^T (zero padded)
-    W* T = wbase;                                            // T_LR
+    W* T = wbase;                                            // T_LR's 4-vectors, then Tbar
     W* U = T + al4((size_t)N3 * N3p);                        // u_1 .. u_mmax
-    W* V = U + al4((size_t)a.mmax * N3 * ncol);              // (D u_m)^T, the next product's operand, ncol x N3p,
-    W* V2 = V + al4((size_t)ncol * N3p);                     //   in two buffers used in turn
+    W* V = U + al4((size_t)a.mmax * N3 * ncol);              // Lanczos vectors, central terms of Tbar
+    W* V2 = V + al4((size_t)ncol * N3p);                     // the products' operand where LDS has no room for it
     W* Pm = V2 + al4((size_t)ncol * N3p);                    // D u_a side by side, a = 1 .. na
     W* Qm = Pm + (size_t)N3 * KKp;                           // W D Z_a side by side
     auto Uat = [&](int m) { return U + (size_t)(m - 1) * N3 * ncol; };
@@ -280,71 +412,88 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax) {
     }
     __syncthreads();
 
-    // --- T_LR (row-major, symmetric, zero diagonal blocks).  One block (i, j)
-    // per thread, consecutive threads along a block row, so that the rows are
-    // written in contiguous runs (each unordered pair is evaluated from both
-    // ends: the block is the same for (i, j) and (j, i)).
-    for (int p = tid; p < nK * nK; p += blockDim.x) {
-        const int i = p / nK, j = p % nK;
-        double blk[9] = {};
+    // --- T_LR, one 4-vector per unordered pair (see the products), zero on the diagonal and
+    // for uncoupled pairs
+    typedef W W4 __attribute__((ext_vector_type(4)));
+    W4* const rec = reinterpret_cast<W4*>(T);
+    for (int p = tid; p < nK * (nK + 1) / 2; p += blockDim.x) {
+        int i = (int)((sqrtf(8.0f * (float)p + 1.0f) - 1.0f) * 0.5f);   // an estimate, corrected in integers
+        while ((i + 1) * (i + 2) / 2 <= p) ++i;
+        while (i * (i + 1) / 2 > p) --i;
+        const int j = p - i * (i + 1) / 2;
+        W4 e = {W(0), W(0), W(0), W(0)};
         if (i != j) {
             const double v[3] = {L.px[i] - L.px[j], L.py[i] - L.py[j], L.pz[i] - L.pz[j]};
             const double r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-            const double rcut = (i == 0 || j == 0) ? SI.r_mbd1 : SI.r_mbd2;
+            const double rcut = j == 0 ? SI.r_mbd1 : SI.r_mbd2;
             if (r < rcut) {
                 const LrPair<W> t = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut),
                                                W(a.r_buf));
-                const double rh[3] = {v[0] / r, v[1] / r, v[2] / r};
-                for (int q = 0; q < 3; ++q)
-                    for (int c = 0; c < 3; ++c)
-                        blk[3 * q + c] = double(t.A) * rh[q] * rh[c] + (q == c ? double(t.B) : 0.0);
+                const double sA = sqrt(fmax(double(t.A), 0.0)) / r;
+                e = W4{W(sA * v[0]), W(sA * v[1]), W(sA * v[2]), t.B};
             }
         }
-        for (int q = 0; q < 3; ++q)
-            for (int c = 0; c < 3; ++c) T[(size_t)(3 * i + q) * N3p + 3 * j + c] = W(blk[3 * q + c]);
-    }
-    for (int e = tid; e < N3 * (N3p - N3); e += blockDim.x) T[(size_t)(e / (N3p - N3)) * N3p + N3 + e % (N3p - N3)] = W(0);
-    for (int e = tid; e < ncol * (N3p - N3); e += blockDim.x) {
-        V[(size_t)(e / (N3p - N3)) * N3p + N3 + e % (N3p - N3)] = W(0);
-        V2[(size_t)(e / (N3p - N3)) * N3p + N3 + e % (N3p - N3)] = W(0);
+        rec[p] = e;
     }
     __syncthreads();
 
+    // the products' operand: column `col`, site and component of row r
+    W* const X = vlds ? Vl : V2;
+    const int ldx = vlds ? operand_ld(nK) : N3, ldp = vlds ? operand_plane(nK) : nK;
+    auto operand_at = [&](int r, int col) -> size_t { return (size_t)col * ldx + (r % 3) * ldp + r / 3; };
+    for (int e = tid; e < (vlds ? ncol * 3 * (ldp - nK) : 0); e += blockDim.x) {   // the planes' padding
+        const int row = e / (ldp - nK);
+        Vl[(size_t)(row / 3) * ldx + (row % 3) * ldp + nK + e % (ldp - nK)] = W(0);
+    }
     // --- u_1 = D T D e_k, V = D u_1
     W* U1 = Uat(1);
     for (int e = tid; e < N3 * ncol; e += blockDim.x) {
         const int row = e / ncol, col = e % ncol;
-        const int q = col / 3, c = col % 3;
+        const int q = col / 3, c = col % 3, x = row % 3;
         const double sq = L.sqa[(size_t)(row / 3) * nq + q];
-        const double u = sq * double(T[(size_t)row * N3p + c]) * L.sqa[q];
+        const W4 t = rec[tri(row / 3, 0)];
+        const double tx = x == 0 ? t[0] : x == 1 ? t[1] : t[2], tc = c == 0 ? t[0] : c == 1 ? t[1] : t[2];
+        const double u = sq * (tx * tc + (x == c ? double(t[3]) : 0.0)) * L.sqa[q];
         U1[e] = W(u);
-        V[(size_t)col * N3p + row] = W(sq * u);
+        X[operand_at(row, col)] = W(sq * u);
     }
     __syncthreads();
-    // --- u_{m+1} = D (T V), V' = D u_{m+1}  (T symmetric, so it is its own K-major
-    // operand); the product's stores write both, V' into the other buffer
+    // --- u_{m+1} = D (T X), then the next operand X = D u_{m+1}
     for (int m = 1; m < a.mmax; ++m) {
         W* Un = Uat(m + 1);
-        const W* Vin = (m & 1) ? V : V2;
-        W* Vout = (m & 1) ? V2 : V;
-        mfma_gemm_nt<3, 3, W>(N3, ncol, N3, T, N3p, Vin, N3p, false, [&](int r, int col, W v) {
-            const W sq = W(L.sqa[(size_t)(r / 3) * nq + col / 3]);
-            const W un = sq * v;
-            Un[(size_t)r * ncol + col] = un;
-            Vout[(size_t)col * N3p + r] = sq * un;
-        });   // ends with a barrier
+        auto st = [&](int r, int col, W v) {
+            Un[(size_t)r * ncol + col] = W(L.sqa[(size_t)(r / 3) * nq + col / 3]) * v;
+        };
+        // (two calls, so that the compiler knows which memory the operand is in)
+        if (vlds) product_tlr<true, W>(nK, ncol, T, Vl, ldx, ldp, st);
+        else product_tlr<false, W>(nK, ncol, T, V2, ldx, ldp, st);
+        if (m + 1 < a.mmax) {
+            for (int e = tid; e < nK * ncol; e += blockDim.x) {
+                const int i = e / ncol, col = e - i * ncol;
+                const W sq = W(L.sqa[(size_t)i * nq + col / 3]);
+                const W* u = Un + (size_t)(3 * i) * ncol + col;
+                W* x = X + (size_t)col * ldx + i;
+                const W u0 = u[0], u1 = u[ncol], u2 = u[2 * ncol];
+                x[0] = sq * u0;
+                x[ldp] = sq * u1;
+                x[2 * ldp] = sq * u2;
+            }
+            __syncthreads();
+        }
     }
 
     // --- spectrum bounds of G~ at every node (Lanczos) and, with a.fit, the fitted c_n: the
-    // vectors in the space of V, the products' operand D v (rows 0 .. nq-1, zero padded) in V2
+    // vectors in the space of V, the products' operand D v as above
     if (a.lz_steps > 0)
         lanczos_fit<W>(
             a, k, N3, N3p, L, V, [&](int r) { return lanczos_start(SI, k, S[r / 3], r); },
-            [&](int q, int r, W v) { V2[(size_t)q * N3p + r] = W(L.sqa[(size_t)(r / 3) * nq + q]) * v; },
+            [&](int q, int r, W v) { X[operand_at(r, q)] = W(L.sqa[(size_t)(r / 3) * nq + q]) * v; },
             [&](const W*, W* wv) {
-                mfma_gemm_nt<1, 2, W>(N3, nq, N3, T, N3p, V2, N3p, false, [&](int r, int q, W v) {
+                auto st = [&](int r, int q, W v) {
                     wv[(size_t)q * N3p + r] = W(L.sqa[(size_t)(r / 3) * nq + q]) * v;
-                });   // ends with a barrier
+                };
+                if (vlds) product_tlr<true, W>(nK, nq, T, Vl, ldx, ldp, st);   // ends with a barrier
+                else product_tlr<false, W>(nK, nq, T, V2, ldx, ldp, st);
             });
 
     // --- moments mu_n(q) = <u_a, u_b>, a + b = n: eight moments (consecutive in the
@@ -428,11 +577,11 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax) {
                         LrPair<double> t;
                         if (t2pair(i, j, r, rh, t)) nrm = (t.A + t.B) * (t.A + t.B) + 2.0 * t.B * t.B;
                     } else {
-                        for (int r = 0; r < 3; ++r)
-                            for (int c = 0; c < 3; ++c) {
-                                const double x = double(T[(size_t)(3 * i + r) * N3p + 3 * j + c]);
-                                nrm += x * x;
-                            }
+                        // |T_ij|^2 = (A + B)^2 + 2 B^2, A = |s|^2
+                        const W4 t = rec[tri(i, j)];
+                        const double A = double(t[0]) * double(t[0]) + double(t[1]) * double(t[1]) + double(t[2]) * double(t[2]);
+                        const double B = t[3];
+                        nrm = (A + B) * (A + B) + 2.0 * B * B;
                     }
 #pragma unroll
                     for (int x = 0; x < 4; ++x)
@@ -500,7 +649,7 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax) {
     // entry (row r >= 3, x): w_k sum_q W_q sqrt(alpha~_r alpha~_k) sum_{b>=1} c_{b+1}
     // u_b[r][3q + x] (the approximate forces: b >= 2 with c_{b+1} (b + 1); with two-body
     // radii the n = 2 term is apart), get their summand over q from the same values, into
-    // the space of V.  Leaving u_0 out of the product: Tbar 395k -> 265k cycles per atom
+    // the space of V.  Leaving u_0 out of the product: Tbar 395k -> 293k cycles per atom
     // of 1,728 C at 6 A.
     // (two instantiations: the common series coefficients are kernel arguments at
     // fixed offsets, the fitted ones LDS entries of the column's node)
@@ -548,18 +697,30 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax) {
     // Gbar are transposes of each other), so only blocks on or below the
     // diagonal are formed and read.
     if (a.paper) {   // 2 w_k sum_q c_2(q) W_q D_q^2 T D_q^2 (with two-body radii: apart), the central column below
+        // (evaluated again: Tbar takes the space of the 4-vectors)
         const double c2 = 2.0 * wk;
-        for (int e = tid; e < N3 * N3; e += blockDim.x) {
-            const int r = e / N3, s = e % N3;
-            if (s > r) continue;
-            const size_t at = (size_t)r * N3p + s;
-            const double t = has2b ? 0.0 : double(T[at]);
-            double f = 0.0;
-            if (t != 0.0)
-                for (int q = 0; q < nq; ++q)
-                    f += a.wq[q] * cfq(2, q) * L.sa[(size_t)(r / 3) * nwe + 1 + q] *
-                         L.sa[(size_t)(s / 3) * nwe + 1 + q];
-            T[at] = W(c2 * t * f);
+        for (int p = tid; p < nK * nK; p += blockDim.x) {
+            const int i = p / nK, j = p % nK;
+            if (j > i) continue;
+            double blk[9] = {};
+            if (j < i && !has2b) {
+                const double v[3] = {L.px[i] - L.px[j], L.py[i] - L.py[j], L.pz[i] - L.pz[j]};
+                const double r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+                const double rcut = j == 0 ? SI.r_mbd1 : SI.r_mbd2;
+                if (r < rcut) {
+                    const LrPair<W> t = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut),
+                                                   W(a.r_buf));
+                    double f = 0.0;
+                    for (int q = 0; q < nq; ++q)
+                        f += a.wq[q] * cfq(2, q) * L.sa[(size_t)i * nwe + 1 + q] * L.sa[(size_t)j * nwe + 1 + q];
+                    for (int x = 0; x < 3; ++x)
+                        for (int y = 0; y < 3; ++y)
+                            blk[3 * x + y] =
+                                c2 * f * (double(t.A) * (v[x] / r) * (v[y] / r) + (x == y ? double(t.B) : 0.0));
+                }
+            }
+            for (int x = 0; x < 3; ++x)
+                for (int y = 0; y < 3; ++y) T[(size_t)(3 * i + x) * N3p + 3 * j + y] = W(blk[3 * x + y]);
         }
         __syncthreads();
     } else {
@@ -735,14 +896,26 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax) {
 }
 
 hipError_t launch_mbd_dense(hipStream_t st, const MbdArgs& a, int nkmax, bool mixed, bool two_body) {
-    const size_t lds = mbd_lds_bytes(nkmax, a.nq, a.n_max, a.lz_steps, a.fit != 0);
+    size_t lds = mbd_lds_bytes(nkmax, a.nq, a.n_max, a.lz_steps, a.fit != 0);
     const dim3 grid(a.n), blk(kMbdThreads);
+    // the products' operand in LDS where it fits: in all of it (FP64, one workgroup per compute
+    // unit by its registers: up to 147 sites at 12 nodes) or in half (FP32, two workgroups: up
+    // to 118 sites; one workgroup with the operand in LDS ran slower than two without)
+    const size_t wsz = mixed ? sizeof(float) : sizeof(double);
+    const int ldv = operand_ld(nkmax);
+    const size_t adj = mbd_adjoint_offset(nkmax, a.nq);
+    const size_t own = mbd_site_doubles((size_t)nkmax, a.nq) - adj;                // adjoints, reduction parts, gradients
+    const size_t op = (wsz * (size_t)a.ncol * ldv + sizeof(double) - 1) / sizeof(double) + 1;   // (+ 1: 16-byte start)
+    int vlds = (int)((std::max(own, op) + 1) & ~(size_t)1);
+    const size_t with = sizeof(double) * (adj + vlds + mbd_small_doubles(a.nq, a.n_max, a.lz_steps, a.fit != 0));
+    if (with <= (mixed ? kLdsBytes / 2 : kLdsBytes)) lds = with;
+    else vlds = 0;
     if (mixed) {
-        if (two_body) hipLaunchKernelGGL((k_mbd<float, true>), grid, blk, lds, st, a, nkmax);
-        else hipLaunchKernelGGL((k_mbd<float, false>), grid, blk, lds, st, a, nkmax);
+        if (two_body) hipLaunchKernelGGL((k_mbd<float, true>), grid, blk, lds, st, a, nkmax, vlds);
+        else hipLaunchKernelGGL((k_mbd<float, false>), grid, blk, lds, st, a, nkmax, vlds);
     } else {
-        if (two_body) hipLaunchKernelGGL((k_mbd<double, true>), grid, blk, lds, st, a, nkmax);
-        else hipLaunchKernelGGL((k_mbd<double, false>), grid, blk, lds, st, a, nkmax);
+        if (two_body) hipLaunchKernelGGL((k_mbd<double, true>), grid, blk, lds, st, a, nkmax, vlds);
+        else hipLaunchKernelGGL((k_mbd<double, false>), grid, blk, lds, st, a, nkmax, vlds);
     }
     return hipGetLastError();
 }
