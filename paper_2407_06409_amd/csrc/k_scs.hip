@@ -88,12 +88,17 @@ __device__ inline void inner_buffer(double r, double rin, double& fin, double& d
 }
 
 // ---------------------------------------------------------------------------
-// Storage: the N x N matrix is row-major, lower triangle (A[row * ld + col],
-// col <= row), ld a multiple of 4 so that a 16-column row segment is four
-// aligned 4-vectors.  After the factorisation the strict upper part of each
-// 16x16 diagonal block holds the strict lower part of that block's inverse
-// Z = L_bb^{-1}, transposed (Z[r][q], r > q, at (q, r)); the diagonal of Z is
-// 1 / L[r][r].
+// Storage: 16 x 16 tiles (I, J) of the lower triangle and of the three rows of d^T below
+// it, row tile by row tile (FacTile).  Within a tile the order is that of the matrix
+// instructions' operands: 16-byte groups of kPack columns, the rows of a group side by
+// side, so that the 64 lanes of a load (lane = row + 16 x group) read one contiguous
+// kilobyte.  A row-major matrix spread each of these loads over 16 rows: 42 cache lines per
+// memory instruction, 2.8 times the line accesses of this order.  The last row tile holds only its own
+// rows and the last column tile only the columns below ld, so that a slot is never larger
+// than (N + 3) x ld.  The factorisation reads the strict lower tiles of L again and of the
+// diagonal tiles only the inverses Z = L_bb^{-1}: a diagonal tile is left holding Z^T (its
+// rows of d^T aside).  With the solves below, 1,728 C at 6 A: k_scs_factor 12.1 -> 10.7 ms
+// (FP32 11.0 -> 9.0), k_scs_solve 3.20 -> 2.14 ms (FP32 1.88 -> 1.09).
 //
 // Left-looking blocked Cholesky by one workgroup, 32-column panels P (two 16-column
 // tiles, h = 0, 1), in units of two 16-row tiles from the panel's diagonal down:
@@ -150,9 +155,57 @@ template <typename R> struct Vec4T;
 template <> struct Vec4T<double> { typedef d4_t type; };
 template <> struct Vec4T<float> { typedef f4_t type; };
 
+// Row tile I of a slot of Nr rows (N of B~, three of d^T)
+template <typename R> constexpr int kPack = 16 / (int)sizeof(R);   // columns of a 16-byte group
+template <typename R> struct PackT;
+template <> struct PackT<double> { typedef double type __attribute__((ext_vector_type(2))); };
+template <> struct PackT<float> { typedef f4_t type; };
+struct FacTile {
+    int base, h;   // first element; rows
+};
+__device__ __forceinline__ FacTile fac_tile(int Nr, int I) { return FacTile{128 * I * (I + 1), min(NB, Nr - NB * I)}; }
 template <typename R>
-__device__ inline typename Vec4T<R>::type load4(const R* p) {
-    return *reinterpret_cast<const typename Vec4T<R>::type*>(p);
+__device__ __forceinline__ int fac_in_tile(int h, int row, int col) {   // row, col < 16
+    constexpr int PW = kPack<R>;
+    return (col / PW) * (h * PW) + row * PW + col % PW;
+}
+template <typename R>
+__device__ __forceinline__ int fac_at(int Nr, int row, int col) {
+    const FacTile T = fac_tile(Nr, row / NB);
+    return T.base + (col / NB) * NB * T.h + fac_in_tile<R>(T.h, row % NB, col % NB);
+}
+// the four columns of lane (row, group) in tile operand order: groups g and, in FP64, g + 4.
+// base: uniform, of the tile; lane: the lane's byte offset in it (fac_lane)
+template <typename R>
+__device__ __forceinline__ unsigned fac_lane(int h, int li, int lk) {
+    return (unsigned)sizeof(R) * (unsigned)fac_in_tile<R>(h, min(li, h - 1), kPack<R> * lk);
+}
+template <typename P>
+__device__ __forceinline__ P load_at(const void* base, unsigned off) {
+    return *reinterpret_cast<const P*>(static_cast<const char*>(base) + off);
+}
+template <typename R>
+__device__ __forceinline__ typename Vec4T<R>::type fac_load4(const R* __restrict__ base, unsigned lane, int h) {
+    typedef typename PackT<R>::type PV;
+    typename Vec4T<R>::type v;
+    const PV a = load_at<PV>(base, lane);
+    if constexpr (sizeof(R) == 8) {
+        const PV b = load_at<PV>(base + 4 * kPack<R> * h, lane);
+        v[0] = a[0]; v[1] = a[1]; v[2] = b[0]; v[3] = b[1];
+    } else {
+        v = a;
+    }
+    return v;
+}
+// The compiler tracks loads in flight by register and, where paths meet, waits for the
+// latest of them: a loaded value that one path leaves unread then costs a full wait.  This
+// reads the value (waits for its load) on every path.
+template <typename V> __device__ __forceinline__ void arrive(V& v) { asm volatile("" : "+v"(v)); }
+// the column of a tile that element e of lane group lk of such a load holds
+template <typename R>
+__device__ __forceinline__ int fac_col(int lk, int e) {
+    constexpr int PW = kPack<R>;
+    return 4 * PW * (e / PW) + PW * lk + e % PW;
 }
 
 constexpr int kMaxParts = 3;          // stored k-split parts of a panel: at most wavefronts - 1
@@ -163,12 +216,11 @@ constexpr int kSpinMax = 1 << 22;     // polls of the diagonal flag before a wav
 // Z = L^{-1}.  Step c scales entry c of every lane by 1 / L_cc and reads L[s][c] (s > c)
 // from lane s; the same update x[s] -= L[s][c] x[c], one instruction for both halves,
 // is the right-looking update of the later rows of the tile and the forward
-// substitution of every column of Z in the order of c.  L goes to the matrix at
-// (c0, c0), Z to Zs (row-major) and its strict lower part, transposed, to the block's
-// strict upper part in the matrix.  Rows from jb on are those of the identity.  good
-// turns false on a pivot that is not positive.
+// substitution of every column of Z in the order of c.  Z goes to Zs (row-major) and
+// Z^T to the tile in the matrix (tile: its first element; h rows; w columns).  Rows from
+// jb on are those of the identity.  good turns false on a pivot that is not positive.
 template <typename R>
-__device__ __forceinline__ void diag_block(R* __restrict__ Lt, int jb, R* __restrict__ A, int ld, int c0,
+__device__ __forceinline__ void diag_block(R* __restrict__ Lt, int jb, R* __restrict__ tile, int h, int w,
                                            R* __restrict__ Zs, bool& good) {
     // (l is made opaque so that the per-lane constants are not hoisted out of the
     // panel loop, where they would only take registers)
@@ -193,18 +245,20 @@ __device__ __forceinline__ void diag_block(R* __restrict__ Lt, int jb, R* __rest
         for (int s = c + 1; s < NB; ++s) x[s] -= x[c] * bcast(x[c], s);   // L[s][c]
         __builtin_amdgcn_sched_barrier(0);
     }
-    if (lrow && r < jb) {
-#pragma unroll
-        for (int c = 0; c < NB; ++c)
-            if (c <= r) A[(size_t)(c0 + r) * ld + c0 + c] = x[c];
-    }
-    if (l >= NB && l < 2 * NB) {
+    if (l >= NB && l < 2 * NB) {   // lane 16 + r: column r of Z, zero above the diagonal
 #pragma unroll
         for (int q = 0; q < NB; ++q) Zs[q * kSlotLd + r] = x[q];
         if (r < jb) {
+            typedef typename PackT<R>::type PV;
+            constexpr int PW = kPack<R>;
 #pragma unroll
-            for (int q = 0; q < NB; ++q)
-                if (q > r && q < jb) A[(size_t)(c0 + r) * ld + c0 + q] = x[q];
+            for (int q = 0; q < NB; q += PW)
+                if (q < w) {   // uniform
+                    PV v;
+#pragma unroll
+                    for (int e = 0; e < PW; ++e) v[e] = x[q + e];
+                    *reinterpret_cast<PV*>(tile + fac_in_tile<R>(h, r, q)) = v;
+                }
         }
     }
 }
@@ -227,8 +281,9 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
     const int li = lane & 15, lk = lane >> 4;
     const int Nr = N + 3;                           // rows: B~, then d^T
     const int ntr = (Nr + NB - 1) / NB;             // row tiles
+    const int ntc = (N + NB - 1) / NB;              // column tiles
+    constexpr int PW = kPack<R>;
     const int npan = (N + 2 * NB - 1) / (2 * NB);   // 32-column panels
-    const V4 zero = {R(0), R(0), R(0), R(0)};
     Acc zacc;
 #pragma unroll
     for (int q = 0; q < 4; ++q) zacc[q] = R(0);
@@ -241,69 +296,92 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
         // them are formed per call rather than held, or spilled, over the panel loop)
         int lio = li, lko = lk;
         asm volatile("" : "+v"(lio), "+v"(lko));
+        // every load is unconditional, with indices clamped into the slot (a load in a
+        // conditional block is waited for at once): a row tile past the end repeats the last
+        // one, a row past a tile's end its last row; their values reach only entries that
+        // nothing reads
         bool v[2][2];
+        FacTile ti[2];
+        int row[2];
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+        for (int x = 0; x < 2; ++x) {
+            const int t = 2 * u + x;
+            ti[x] = fac_tile(Nr, min(c0p / NB + t, ntr - 1));
+            row[x] = min(lio, ti[x].h - 1);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const int t = 2 * u + x;
                 v[x][h] = t < mtp && (h == 0 || twop) && !(t == 0 && h == 1);
                 if (init != 2) {
+                    const int J = min(c0p / NB + h, min(c0p / NB + t, ntc - 1));   // (upper tile: not used)
+                    const R* T = A + ti[x].base + J * NB * ti[x].h;
+                    const int wid = min(NB, ld - NB * J);   // a multiple of 4; zero beyond
+                    if constexpr (sizeof(R) == 8) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int row = c0p + NB * t + lio, col = c0p + NB * h + M::acc_row(lko, q);
-                        m[x][h][q] = (init == 0 && v[x][h] && row < Nr && col < N && (t != h || row >= col))
-                                         ? A[(size_t)row * ld + col] : R(0);
+                        for (int q = 0; q < 4; ++q) {
+                            const R val = T[fac_in_tile<R>(ti[x].h, row[x], lko + min(4 * q, wid - 4))];
+                            m[x][h][q] = (init == 0 && v[x][h] && 4 * q < wid) ? val : R(0);
+                        }
+                    } else {
+                        const V4 val = *reinterpret_cast<const V4*>(T + fac_in_tile<R>(ti[x].h, row[x], min(4 * lko, wid - 4)));
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            m[x][h][q] = (init == 0 && v[x][h] && 4 * lko < wid) ? val[q] : R(0);
                     }
                 }
             }
+        }
         if (cb < ce) {   // uniform
-            const R* pt[2];
-            const R* ph[2];
-            bool okt[2], okh[2];
+            // sums of products minus the tiles, negated at the end
 #pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const int r = c0p + NB * (2 * u + x) + lio;
-                okt[x] = 2 * u + x < mtp && r < Nr;
-                pt[x] = A + (size_t)(okt[x] ? r : 0) * ld + 4 * lko;
-            }
+            for (int y = 0; y < 4; ++y)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) m[y >> 1][y & 1][q] = -m[y >> 1][y & 1][q];
+            unsigned at[2], ah[2];
+            FacTile th[2];
+#pragma unroll
+            for (int x = 0; x < 2; ++x) at[x] = fac_lane<R>(ti[x].h, lio, lko);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const int r = c0p + NB * h + lio;
-                okh[h] = (h == 0 || twop) && r < N;
-                ph[h] = A + (size_t)(okh[h] ? r : 0) * ld + 4 * lko;
+                th[h] = fac_tile(Nr, min(c0p / NB + h, ntr - 1));
+                ah[h] = fac_lane<R>(th[h].h, lio, lko);
             }
-            auto ld4 = [&](const R* base, bool okr, int c) { return (okr && c < ce) ? load4(base + NB * c) : zero; };
             // ring of kRing chunks: each chunk's registers are refilled with the chunk
-            // kRing ahead right after use
+            // kRing ahead right after use; all four tile products of a unit, also those
+            // that nothing reads (no branch between the loads)
             V4 rt[kRing][2], rh[kRing][2];
+            auto fetch = [&](int j, int c) {
+                c = min(c, ce - 1);
 #pragma unroll
-            for (int j = 0; j < kRing; ++j) {
+                for (int h = 0; h < 2; ++h) rh[j][h] = fac_load4<R>(A + (th[h].base + c * NB * th[h].h), ah[h], th[h].h);
 #pragma unroll
-                for (int x = 0; x < 2; ++x) rt[j][x] = ld4(pt[x], okt[x], cb + j * st);
+                for (int x = 0; x < 2; ++x) rt[j][x] = fac_load4<R>(A + (ti[x].base + c * NB * ti[x].h), at[x], ti[x].h);
+                __builtin_amdgcn_sched_barrier(0);
+            };
 #pragma unroll
-                for (int h = 0; h < 2; ++h) rh[j][h] = ld4(ph[h], okh[h], cb + j * st);
-            }
+            for (int j = 0; j < kRing; ++j) fetch(j, cb + j * st);
             for (int ch = cb; ch < ce; ch += kRing * st) {
 #pragma unroll
                 for (int j = 0; j < kRing; ++j) {
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) {
+                        arrive(rh[j][x]);
+                        arrive(rt[j][x]);
+                    }
                     if (ch + j * st < ce) {   // uniform
 #pragma unroll
-                        for (int x = 0; x < 2; ++x)
+                        for (int e = 0; e < 4; ++e)
 #pragma unroll
-                            for (int h = 0; h < 2; ++h)
-                                if (v[x][h]) {   // uniform
+                            for (int x = 0; x < 2; ++x)
 #pragma unroll
-                                    for (int e = 0; e < 4; ++e) m[x][h] = M::mma(-rh[j][h][e], rt[j][x][e], m[x][h]);
-                                }
+                                for (int h = 0; h < 2; ++h) m[x][h] = M::mma(rh[j][h][e], rt[j][x][e], m[x][h]);
                     }
-                    const int cn = ch + (j + kRing) * st;
-#pragma unroll
-                    for (int x = 0; x < 2; ++x) rt[j][x] = ld4(pt[x], okt[x], cn);
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) rh[j][h] = ld4(ph[h], okh[h], cn);
+                    fetch(j, ch + (j + kRing) * st);
                 }
             }
+#pragma unroll
+            for (int y = 0; y < 4; ++y)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) m[y >> 1][y & 1][q] = -m[y >> 1][y & 1][q];
         }
     };
     // k-split parts of panel Pq's units; and whether unit 0 of panel Pq is prepared
@@ -336,10 +414,16 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
         };
         // rows rmin.. of the result X (held transposed) of row tile t, column tile h
         auto store_x = [&](const Acc& xt, int t, int h, int rmin) {
+            const FacTile T = fac_tile(Nr, 2 * P + t);
+            const int J = 2 * P + h;
+            R* tile = A + T.base + J * NB * T.h;
+            if (li < rmin || li >= T.h) return;
+            if constexpr (sizeof(R) == 8) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = c0 + NB * t + li, col = c0 + NB * h + M::acc_row(lk, q);
-                if (li >= rmin && row < Nr && col < N) A[(size_t)row * ld + col] = xt[q];
+                for (int q = 0; q < 4; ++q)
+                    if (NB * J + 4 * q < ld) tile[fac_in_tile<R>(T.h, li, lk + 4 * q)] = xt[q];   // uniform
+            } else if (NB * J + 4 * lk < ld) {
+                *reinterpret_cast<Acc*>(tile + fac_in_tile<R>(T.h, li, 4 * lk)) = xt;
             }
         };
         // (2) unit 0, by one wavefront: the diagonal tiles and L21, published to the others
@@ -360,7 +444,8 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
             for (int b = 0; b < nblk; ++b) {
                 R* Zb = b == 0 ? Z1 : Z2;
                 const int jbb = b == 0 ? jb1 : jb2;
-                diag_block<R>(Lt, jbb, A, ld, c0 + NB * b, Zb, good);
+                const FacTile T = fac_tile(Nr, 2 * P + b);
+                diag_block<R>(Lt, jbb, A + T.base + (2 * P + b) * NB * T.h, T.h, min(NB, ld - NB * (2 * P + b)), Zb, good);
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 if (jbb < NB) {   // rows of d^T in the diagonal tile (still in Lt)
                     Acc mbb;
@@ -515,169 +600,239 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
     ok = good;
 }
 
-template <typename R>
-__device__ __forceinline__ void solve_row_update(const R* __restrict__ lrow, int c0, int jb, int i, R* Y) {
-    R s0 = 0, s1 = 0, s2 = 0;
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-        if (q < jb) {  // rows past N hold no solution values
-            s0 += lrow[q] * Y[(c0 + q) * 3 + 0];
-            s1 += lrow[q] * Y[(c0 + q) * 3 + 1];
-            s2 += lrow[q] * Y[(c0 + q) * 3 + 2];
-        }
-    }
-    Y[i * 3 + 0] -= s0;
-    Y[i * 3 + 1] -= s1;
-    Y[i * 3 + 2] -= s2;
+// Triangular solves with the stored factor: L L^T x = b (fwd) or L^T x = y, three
+// right-hand sides in Y (N x 3, padded with zero rows to whole tiles; LDS), four wavefronts.
+// Left-looking: block p of 16 rows is z = Z_p (b_p - sum_J L_pJ z_J), its sum formed tile by
+// tile with the loads of the factorisation's operands (coalesced, see the storage), each lane
+// holding one row and four columns of a tile.  In step p wavefront 0 adds the last tile, the
+// one that needs the block of step p - 1, and finishes block p, while wavefronts 1 .. 3 form
+// the sums of block p + 1 over all earlier blocks, tile s on wavefront 1 + s % 3: one barrier
+// per block, and only that chain between two barriers.  (Right-looking with a row per thread
+// it took two barriers per block and, on the packed tiles, loads of single columns.)  The
+// order of every sum depends on N alone.  part: 2 x 4 x 48 partial sums, sv: 48.
+constexpr int kSolveThreads = 256;
+constexpr int kSolvePart = 4 * 3 * NB;   // partial sums of a block: four wavefronts' 16 x 3
+__host__ __device__ inline int solve_rows(int N) { return (N + NB - 1) / NB * NB; }
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double src) {
+    const long long b = __double_as_longlong(src);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float src) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(src), CTRL, 0xF, 0xF, false));
 }
 
-// Triangular solves with the stored factor: L L^T x = b (fwd) or L^T x = y,
-// three right-hand sides in Y (N x 3, LDS), one row (forward) or column
-// (backward) per thread and slot: thread t takes t, t + blockDim, ..
-// (NS slots, NS * blockDim >= N).  The first NP slots load the next block's
-// segment a block ahead, the others load the segment they use at the start of
-// its step.  Each row's sums are formed in the same order whatever NS, NP and
-// blockDim are.
-template <typename R, int NS, int NP>
-__device__ __forceinline__ void chol_solve3(const R* __restrict__ A, int N, int ld, R* Y, R* zbuf, bool fwd) {
-    static_assert(NP >= 1 && NP <= NS, "slot 0 always loads ahead");
+template <typename R, bool FWD>
+__device__ __forceinline__ void tri_solve3(const R* __restrict__ A, int N, R* Y, R* part, R* sv) {
     typedef typename Vec4T<R>::type V4;
-    const int tid = threadIdx.x, nthr = blockDim.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int nt = (N + NB - 1) / NB;
-    const int r = tid & 15, c = tid >> 4;
-    const bool blk = tid < 48;   // threads of the block step (wavefront 0)
-    const V4 zero = {R(0), R(0), R(0), R(0)};
-    constexpr int kZ = NB * NB / 64;   // staged block entries per lane of wavefront 1
-    // block-step operators, staged by wavefront 1 into LDS one block ahead:
-    // forward Z[r][q] (q <= r), backward Z^T[r][q] = Z[q][r] (q >= r); Z[r][r] = 1 / L[r][r]
-    auto zload = [&](int p, bool fwd, R* zr) {
-        const int c0 = p * NB;
-        const int jb = (p >= 0 && p < nt) ? min(NB, N - c0) : 0;
+    typedef typename PackT<R>::type PV;
+    constexpr int PW = kPack<R>, kD = 3;   // tiles of a group (loads one group ahead)
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    const int Nr = N + 3, nt = (N + NB - 1) / NB;
+    // step p finishes block b(p); tile s of block b(p) couples it to block b(s), s < p
+    auto blk = [&](int p) { return FWD ? p : nt - 1 - p; };
+    const int hl = fac_tile(Nr, nt - 1).h;
+    const unsigned lane_full = fac_lane<R>(NB, li, lk), lane_last = fac_lane<R>(hl, li, lk);
+    auto tile = [&](int p, int s) {
+        const int I = FWD ? blk(p) : blk(s), J = FWD ? blk(s) : blk(p);
+        const FacTile T = fac_tile(Nr, I);
+        return fac_load4<R>(A + (T.base + J * NB * T.h), I == nt - 1 ? lane_last : lane_full, T.h);
+    };
+    // forward: one row, sums over the columns; backward: four columns, sums over the rows
+    // (rows past N: solution values of zero)
+    constexpr int NA = FWD ? 3 : 12;
+    auto add = [&](R(&acc)[NA], const V4 t, int s) {
+        if constexpr (FWD) {
 #pragma unroll
-        for (int t = 0; t < kZ; ++t) {
-            const int e = lane + 64 * t, rr = e / NB, q = e % NB;
-            R v = R(0);
-            if (wave == 1 && rr < jb && q < jb) {
-                if (q == rr) v = A[(size_t)(c0 + rr) * ld + c0 + rr];
-                else if (fwd && q < rr) v = A[(size_t)(c0 + q) * ld + c0 + rr];
-                else if (!fwd && q > rr) v = A[(size_t)(c0 + rr) * ld + c0 + q];
+            for (int g = 0; g < 4 / PW; ++g) {
+                R y[3 * PW];
+                const R* src = Y + 3 * (NB * blk(s) + 4 * PW * g + PW * lk);
+#pragma unroll
+                for (int v = 0; v < 3; ++v) {
+                    const PV yv = *reinterpret_cast<const PV*>(src + PW * v);
+#pragma unroll
+                    for (int e = 0; e < PW; ++e) y[PW * v + e] = yv[e];
+                }
+#pragma unroll
+                for (int e = 0; e < PW; ++e)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) acc[c] += t[PW * g + e] * y[3 * e + c];
             }
-            zr[t] = v;
+        } else {
+            const R* src = Y + 3 * (NB * blk(s) + li);
+            const R y[3] = {src[0], src[1], src[2]};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) acc[3 * e + c] += t[e] * y[c];
         }
     };
-    auto zstore = [&](R* zb, const R* zr) {
-        if (wave == 1) {
+    // (by value and opaque: a choice between array elements would go through memory)
+    auto pick = [](R v0, R v1, R v2, int c) {
+        asm volatile("" : "+v"(v0), "+v"(v1), "+v"(v2));
+        return c == 0 ? v0 : c == 1 ? v1 : v2;
+    };
+    // the wavefront's sums of a block to dst[row][rhs]
+    auto put = [&](R(&acc)[NA], R* dst) {
+        if constexpr (FWD) {
 #pragma unroll
-            for (int t = 0; t < kZ; ++t) {
-                const int e = lane + 64 * t, rr = e / NB, q = e % NB;
-                zb[rr * kSlotLd + q] = (q == rr && zr[t] != R(0)) ? R(1) / zr[t] : zr[t];
+            for (int c = 0; c < 3; ++c) {
+                acc[c] += __shfl_xor(acc[c], 16);
+                acc[c] += __shfl_xor(acc[c], 32);
+            }
+            if (lk < 3) dst[3 * li + lk] = pick(acc[0], acc[1], acc[2], lk);
+        } else {
+            // over the 16 rows: the lanes of a quad end with the three sums of column element
+            // li / 4 (exchanges with lane 15 - li, then 7 - li within halves, 3 - li and li ^ 1
+            // within quads)
+            R h6[6], h3[3];
+            const bool up8 = (li & 8) != 0, up4 = (li & 4) != 0;
+#pragma unroll
+            for (int x = 0; x < 6; ++x) h6[x] = (up8 ? acc[6 + x] : acc[x]) + dpp_move<0x140>(up8 ? acc[x] : acc[6 + x]);
+#pragma unroll
+            for (int x = 0; x < 3; ++x) h3[x] = (up4 ? h6[3 + x] : h6[x]) + dpp_move<0x141>(up4 ? h6[x] : h6[3 + x]);
+#pragma unroll
+            for (int x = 0; x < 3; ++x) h3[x] += dpp_move<0x1B>(h3[x]);
+#pragma unroll
+            for (int x = 0; x < 3; ++x) h3[x] += dpp_move<0xB1>(h3[x]);
+            const int c = li & 3;
+            if (c < 3) dst[3 * fac_col<R>(lk, li >> 2) + c] = pick(h3[0], h3[1], h3[2], c);
+        }
+    };
+    // lane li's row of the block operator of step p: Z (forward) or Z^T (backward) from the
+    // tile Z^T (entries past the system's rows repeat others; they meet zeros only)
+    auto zrow = [&](int p, R(&z)[NB]) {
+        const int B = blk(min(p, nt - 1)), jb = min(NB, N - NB * B), w = min(NB, (N + 3) / 4 * 4 - NB * B);
+        const FacTile T = fac_tile(Nr, B);
+        const R* src = A + (T.base + B * NB * T.h);
+        if constexpr (FWD) {
+            const unsigned col = (unsigned)sizeof(R) * (unsigned)fac_in_tile<R>(T.h, 0, min(li, jb - 1));
+#pragma unroll
+            for (int q = 0; q < NB; ++q) z[q] = load_at<R>(src + min(q, jb - 1) * PW, col);
+        } else {
+            const unsigned row = (unsigned)sizeof(R) * PW * (unsigned)min(li, jb - 1);
+#pragma unroll
+            for (int g = 0; g < NB / PW; ++g) {
+                const PV v = load_at<PV>(src + min(g, w / PW - 1) * T.h * PW, row);
+#pragma unroll
+                for (int e = 0; e < PW; ++e) z[PW * g + e] = v[e];
             }
         }
     };
-    // row `row`'s segment of block column p (forward)
-    auto rowseg = [&](R* dst, int row, int p, bool ok) {
+    // (registers of loads in flight alternate between two sets by code, not by copies: a copy
+    // waits for the load)
+    if (wave == 0) {
+        auto step = [&](int p, const V4 t, const R(&z)[NB]) {   // t: tile (p, p - 1)
+            const R* pp = part + (p & 1) * kSolvePart;
+            R* yb = Y + 3 * NB * blk(p);
+            const int rc = 3 * li + min(lk, 2);
+            const bool in = NB * blk(p) + li < N;
+            R s = yb[rc];
+            if (p > 1) s -= (pp[rc] + pp[48 + rc]) + pp[96 + rc];
+            if (p > 0) {
+                R acc[NA];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const V4 t4 = ok ? load4(A + (size_t)row * ld + p * NB + 4 * v) : zero;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) dst[4 * v + e] = t4[e];
-        }
-    };
-    // column `col`'s segment of block row p (backward; jb rows)
-    auto colseg = [&](R* dst, int col, int p, int jb, bool ok) {
-#pragma unroll
-        for (int q = 0; q < NB; ++q) dst[q] = (ok && q < jb) ? A[(size_t)(p * NB + q) * ld + col] : R(0);
-    };
-    R zr[kZ];
-    R cur[NS][NB], nxt[NP][NB];
-    if (fwd) {
-        // forward: L y = b
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int row = tid + s * nthr;
-            rowseg(cur[s], row, 0, row >= NB && row < N);
-        }
-        zload(0, true, zr);
-        zstore(zbuf, zr);
-        zload(1, true, zr);
-        __syncthreads();
-        for (int p = 0; p < nt; ++p) {
-            const int c0 = p * NB;
-            const int jb = min(NB, N - c0);
-            R* zb = zbuf + (p & 1) * NB * kSlotLd;
-            zstore(zbuf + ((p + 1) & 1) * NB * kSlotLd, zr);   // block p + 1 (loaded during block p - 1)
-            zload(p + 2, true, zr);
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int row = tid + s * nthr;
-                if (s < NP) rowseg(nxt[s < NP ? s : 0], row, p + 1, row >= c0 + 2 * NB && row < N);   // row follows block p + 1
-                else if (p > 0) rowseg(cur[s], row, p, row >= c0 + NB && row < N);
+                for (int x = 0; x < NA; ++x) acc[x] = R(0);
+                add(acc, t, p - 1);
+                R* own = part + (p & 1) * kSolvePart + 144;
+                put(acc, own);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                s -= own[rc];
             }
-            if (blk && r < jb) {
-                R v = 0;
+            if (lk < 3) sv[NB * lk + li] = in ? s : R(0);
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            const R* sc = sv + NB * min(lk, 2);
+            R v0 = R(0), v1 = R(0);
 #pragma unroll
-                for (int q = 0; q < NB; ++q)
-                    if (q < jb) v += zb[r * kSlotLd + q] * Y[(c0 + q) * 3 + c];  // rows past N hold no values
-                Y[(c0 + r) * 3 + c] = v;  // one wavefront: all reads of the block precede this write
+            for (int q = 0; q < NB; q += 2) {
+                v0 += z[q] * sc[q];
+                v1 += z[q + 1] * sc[q + 1];
             }
+            if (lk < 3) yb[rc] = in ? v0 + v1 : R(0);
             __syncthreads();
+        };
+        auto next = [&](int p) { return tile(min(p + 1, nt - 1), min(p, nt - 2)); };
+        V4 ta, tb;
+        R za[NB], zb[NB];
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int row = tid + s * nthr;
-                if (row >= c0 + NB && row < N) solve_row_update(cur[s], c0, NB, row, Y);  // jb = 16 when rows follow
+        for (int e = 0; e < 4; ++e) ta[e] = R(0);
+        zrow(0, za);
+        __syncthreads();
+        if (nt == 1) {
+            step(0, ta, za);
+        } else {
+            for (int p = 0; p < nt; p += 2) {
+                tb = next(p);
+                zrow(p + 1, zb);
+                step(p, ta, za);
+                if (p + 1 == nt) break;
+                ta = next(p + 1);
+                zrow(p + 2, za);
+                step(p + 1, tb, zb);
             }
-            __syncthreads();
-#pragma unroll
-            for (int s = 0; s < NP; ++s)
-#pragma unroll
-                for (int q = 0; q < NB; ++q) cur[s][q] = nxt[s][q];
         }
-    }
-    // backward: L^T x = y
-    {
-        const int c0 = (nt - 1) * NB, jb = N - c0;
+    } else {
+        // groups of kD tiles of the sums of block p + 1 over blocks 0 .. p - 1, tile s on
+        // wavefront 1 + s % 3; one group at least per block
+        auto groups = [&](int p) { const int m = (p - wave + 3) / 3; return max(1, (m + kD - 1) / kD); };
+        int fp = 1, fg = 0;   // step and group of the next loads
+        auto fetch = [&](V4(&v)[kD]) {
+            const int p = min(fp, nt - 2);   // block p + 1 exists
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int col = tid + s * nthr;
-            colseg(cur[s], col, nt - 1, jb, col < c0);
-        }
-    }
-    zload(nt - 1, false, zr);
-    zstore(zbuf + ((nt - 1) & 1) * NB * kSlotLd, zr);
-    zload(nt - 2, false, zr);
-    __syncthreads();
-    for (int p = nt - 1; p >= 0; --p) {
-        const int c0 = p * NB;
-        const int jb = min(NB, N - c0);
-        R* zb = zbuf + (p & 1) * NB * kSlotLd;
-        zstore(zbuf + ((p + 1) & 1) * NB * kSlotLd, zr);   // block p - 1
-        zload(p - 2, false, zr);
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int col = tid + s * nthr;
-            if (s < NP) colseg(nxt[s < NP ? s : 0], col, p - 1, NB, p > 0 && col < c0 - NB);
-            else if (p < nt - 1) colseg(cur[s], col, p, jb, col < c0);
-        }
-        if (blk && r < jb) {
-            R v = 0;
-#pragma unroll
-            for (int q = 0; q < NB; ++q)
-                if (q < jb) v += zb[r * kSlotLd + q] * Y[(c0 + q) * 3 + c];  // rows past N hold no values
-            Y[(c0 + r) * 3 + c] = v;
-        }
+            for (int j = 0; j < kD; ++j) v[j] = tile(p + 1, min(wave - 1 + 3 * (kD * fg + j), max(p - 1, 0)));
+            if (++fg == groups(fp)) {
+                fg = 0;
+                ++fp;
+            }
+        };
+        V4 va[kD], vb[kD];
+        if (nt > 2) fetch(va);
         __syncthreads();
+        __syncthreads();   // step 0
+        if (nt > 2) {   // steps 1 .. nt - 2
+            int p = 1, g = 0, ng = groups(1);
+            R acc[NA];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int col = tid + s * nthr;
-            if (col < c0) solve_row_update(cur[s], c0, jb, col, Y);
+            for (int x = 0; x < NA; ++x) acc[x] = R(0);
+            auto body = [&](V4(&v)[kD], V4(&ahead)[kD]) {   // true: that was the last one
+                fetch(ahead);
+#pragma unroll
+                for (int j = 0; j < kD; ++j) {
+                    const int sidx = wave - 1 + 3 * (kD * g + j);
+                    arrive(v[j]);
+                    if (sidx < p) add(acc, v[j], sidx);   // uniform
+                }
+                if (++g < ng) return false;
+                put(acc, part + ((p + 1) & 1) * kSolvePart + (wave - 1) * 48);
+                __syncthreads();
+                if (++p > nt - 2) return true;
+#pragma unroll
+                for (int x = 0; x < NA; ++x) acc[x] = R(0);
+                g = 0;
+                ng = groups(p);
+                return false;
+            };
+            for (;;) {
+                if (body(va, vb)) break;
+                if (body(vb, va)) break;
+            }
         }
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < NP; ++s)
-#pragma unroll
-            for (int q = 0; q < NB; ++q) cur[s][q] = nxt[s][q];
+        if (nt > 1) __syncthreads();   // step nt - 1
     }
+}
+
+template <typename R>
+__device__ __forceinline__ void chol_solve3(const R* __restrict__ A, int N, R* Y, R* extra, bool fwd) {
+    R* part = extra;
+    R* sv = part + 2 * kSolvePart;
+    if (fwd) tri_solve3<R, true>(A, N, Y, part, sv);   // ends with a barrier
+    tri_solve3<R, false>(A, N, Y, part, sv);
 }
 
 // ---------------------------------------------------------------------------
@@ -810,13 +965,10 @@ __device__ inline int32_t* pair_segs(const ScsArgs& a, int k) {
 }
 
 // sites only (assembly): K1 sites then shell sites
-// assembly of d: K1 sites and shell sites; assembly of B~: K1 sites, one
-// chunk of slots, word counts and a bit per K1 pair (coupled)
-__host__ __device__ inline int assemble_mask_words(int n1max) { return (n1max * (n1max + 1) / 2 + 31) / 32; }
-
+// assembly of d: K1 sites and shell sites; assembly of B~: K1 sites
 static size_t dvec_lds_bytes(int n1max, int n2max) { return sizeof(double) * 6 * ((size_t)n1max + n2max); }
 static size_t matrix_lds_bytes(int n1max) {
-    return sizeof(double) * 6 * (size_t)n1max + sizeof(int32_t) * (2 * kChunk + (size_t)assemble_mask_words(n1max));
+    return sizeof(double) * 6 * (size_t)n1max;
 }
 size_t scs_assemble_lds_bytes(int n1max, int n2max) {
     return std::max(dvec_lds_bytes(n1max, n2max), matrix_lds_bytes(n1max));
@@ -905,7 +1057,6 @@ __global__ void __launch_bounds__(kChunk) k_scs_dvec(ScsArgs a, int n1max, int n
     const Counts cnt = a.counts[k];
     const int n1 = cnt.n1, n12 = cnt.n12;
     const int N = 3 * n1;
-    const int ld = a.fac_ld[k];
     const double rc = a.sinfo[a.atom_struct[k]].r_scs;
     ScsLds L = scs_assemble_lds(lds, n1max, n2max, false);
     double* D = (mixed ? a.dvec : a.xsol) + a.x_off[k] + (size_t)w * N * 3;
@@ -914,9 +1065,6 @@ __global__ void __launch_bounds__(kChunk) k_scs_dvec(ScsArgs a, int n1max, int n
     const int32_t* lq = a.pl_q + a.pl_off[k];
     load_sites(a, k, w, n1, n12, L);
     __syncthreads();
-    // d (N x 3) to its slot, and d^T as the three rows appended to B~, so that the
-    // factorisation carries out the forward substitution
-    R* Dt = static_cast<R*>(a.fac) + a.fac_off[k] + (size_t)w * ld * (N + 3) + (size_t)N * ld;
     const int g = t / kSiteLanes, gl = t % kSiteLanes;
     for (int i = g; i < n1; i += kChunk / kSiteLanes) {
         double h[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -939,107 +1087,83 @@ __global__ void __launch_bounds__(kChunk) k_scs_dvec(ScsArgs a, int n1max, int n
         if (gl == 0) {
             const double d[9] = {1.0 - h[0], -h[1], -h[2], -h[1], 1.0 - h[3], -h[4], -h[2], -h[4], 1.0 - h[5]};
             for (int e = 0; e < 9; ++e) D[(3 * i + e / 3) * 3 + e % 3] = d[e];
-            for (int q = 0; q < 3; ++q)
-                for (int c = 0; c < 3; ++c) Dt[(size_t)c * ld + 3 * i + q] = R(d[3 * q + c]);
         }
     }
 }
 
-// Assembly of the lower triangle of B~ (into the factor slot) by the workgroup
-// of (atom, frequency) that then factorises it, pairs in triangle order in
-// chunks of kChunk: the
-// coupled pairs of a chunk (from the a-major list) are evaluated compactly,
-// one per thread, into LDS; then each pair of the chunk is written by its own
-// thread (rows of atom i in contiguous 3-element runs), zero blocks for
-// uncoupled pairs.  The mixed path also keeps the FP32 pair coefficients for
-// the refinement residual.
+// Assembly of the lower triangle of B~ and of the rows of d^T below it (into the factor
+// slot; with d^T there the factorisation carries out the forward substitution) by the
+// workgroup of (atom, frequency) that then factorises it: the slot is filled with zeros in
+// whole lines, then the coupled pairs, one per thread straight from the a-major list, write
+// their blocks.  (Going through all pairs in triangle order kept two of four wavefronts out
+// of the evaluation, as about half of the pairs of a sphere are coupled.)  The mixed path
+// also keeps the FP32 pair coefficients for the refinement residual.
 template <typename R>
 __device__ __forceinline__ void assemble_matrix(const ScsArgs& a, int k, int w, int n1max, double* lds) {
     constexpr bool mixed = sizeof(R) == 4;
+    typedef typename PackT<R>::type PV;
+    typedef R P2 __attribute__((ext_vector_type(2)));
     const int t = threadIdx.x;
     const Counts cnt = a.counts[k];
     const int n1 = cnt.n1, n12 = cnt.n12, n2 = n12 - n1;
-    const int N = 3 * n1;
+    const int N = 3 * n1, Nr = N + 3;
     const int ld = a.fac_ld[k];
     const double rc = a.sinfo[a.atom_struct[k]].r_scs;
     ScsLds L = scs_assemble_lds(lds, n1max, 0, true);
-    int32_t* slot = L.key;                                  // kChunk
-    int32_t* wcnt = L.key + kChunk;                         // kChunk / 32
-    uint32_t* mask = reinterpret_cast<uint32_t*>(L.key + 2 * kChunk);
-    R* A = static_cast<R*>(a.fac) + a.fac_off[k] + (size_t)w * ld * (N + 3);
+    R* A = static_cast<R*>(a.fac) + a.fac_off[k] + (size_t)w * ld * Nr;
     const int npairs = n1 * (n1 + 1) / 2;
     float* coef = mixed ? a.coef + a.coef_off[k] + (size_t)w * 2 * npairs : nullptr;
     const int32_t* seg_a = pair_segs(a, k) + (n12 + 2);
     const int32_t* la = a.pl_i + a.pl_off[k] + (int64_t)n1 * n2;
     load_sites(a, k, w, n1, n1, L);
-    for (int e = t; e < assemble_mask_words(n1); e += kChunk) mask[e] = 0u;
-    __syncthreads();
-    const int P11 = seg_a[n1];
-    for (int e = t; e < P11; e += kChunk) {   // coupled K1 pairs (a < b) -> bit of lower-triangle pair (b, a)
-        const int32_t ent = la[e];
-        const int i = ent & 0xFFFF, j = ent >> 16;
-        const int p = i * (i + 1) / 2 + j;
-        atomicOr(&mask[p >> 5], 1u << (p & 31));
+    {
+        const FacTile T = fac_tile(Nr, (Nr - 1) / NB);   // the last row tile, ld columns
+        PV zero;
+#pragma unroll
+        for (int e = 0; e < kPack<R>; ++e) zero[e] = R(0);
+        PV* slot = reinterpret_cast<PV*>(A);
+        for (int e = t; e < (T.base + T.h * ld) / kPack<R>; e += kChunk) slot[e] = zero;
+        if (mixed)
+            for (int e = t; e < 2 * npairs; e += kChunk) coef[e] = 0.f;
     }
     __syncthreads();
-    for (int p0 = 0; p0 < npairs; p0 += kChunk) {
-        const int w0 = p0 >> 5;
-        if (t < kChunk / 32) wcnt[t] = (p0 + 32 * t < npairs) ? __popc(mask[w0 + t]) : 0;
-        __syncthreads();
-        int total = 0;
-        for (int x = 0; x < kChunk / 32; ++x) total += wcnt[x];
-        const int p = p0 + t;
-        int rank = -1;
-        if (p < npairs) {
-            const int wd = p >> 5;
-            const uint32_t m = mask[wd];
-            if ((m >> (p & 31)) & 1u) {
-                int r = __popc(m & ((1u << (p & 31)) - 1u));
-                for (int x = w0; x < wd; ++x) r += wcnt[x - w0];
-                rank = r;
-                slot[r] = p;
-            }
+    // d^T, the diagonal blocks' diagonals, the coupled pairs' blocks
+    const double* D = (mixed ? a.dvec : a.xsol) + a.x_off[k] + (size_t)w * N * 3;
+    for (int e = t; e < 3 * N; e += kChunk) A[fac_at<R>(Nr, N + e % 3, e / 3)] = R(D[e]);
+    for (int r = t; r < N; r += kChunk) A[fac_at<R>(Nr, r, r)] = R(1.0 / L.ab[r / 3]);
+    const int P11 = seg_a[n1];
+    for (int e = t; e < P11; e += kChunk) {
+        const int32_t ent = la[e];
+        const int i = ent & 0xFFFF, j = ent >> 16;   // i > j
+        double rh[3], rr;
+        const SrPair<R> tp = k1_pair<R>(a, L, i, j, rc, rh, rr);
+        if (mixed) {
+            const int p = i * (i + 1) / 2 + j;
+            coef[2 * p] = (float)tp.A;
+            coef[2 * p + 1] = (float)tp.B;
         }
-        __syncthreads();
-        // coupled pairs, compacted: T_SR and its block of B~
-        if (t < total) {
-            const int pp = slot[t];
-            int i, j;
-            tri_decode(pp, i, j);
-            double rh[3], rr;
-            const SrPair<R> tp = k1_pair<R>(a, L, i, j, rc, rh, rr);
-            if (mixed) {
-                coef[2 * pp] = (float)tp.A;
-                coef[2 * pp + 1] = (float)tp.B;
-            }
-            const double Av = double(tp.A), Bv = double(tp.B);
-            R* blk = A + (size_t)(3 * i) * ld + 3 * j;
-            for (int q = 0; q < 3; ++q)
-                for (int c = 0; c < 3; ++c) blk[(size_t)q * ld + c] = R(Av * rh[q] * rh[c] + (q == c ? Bv : 0.0));
+        const double Av = double(tp.A), Bv = double(tp.B);
+        // columns 3j .. 3j + 2: an aligned pair and a single one (pairs never straddle tiles)
+        const bool odd = (j & 1) != 0;
+        const int c2 = 3 * j + (odd ? 1 : 0), c1 = 3 * j + (odd ? 0 : 2);
+        for (int q = 0; q < 3; ++q) {
+            R b[3];
+            for (int c = 0; c < 3; ++c) b[c] = R(Av * rh[q] * rh[c] + (q == c ? Bv : 0.0));
+            const int row = 3 * i + q;
+            const FacTile T = fac_tile(Nr, row / NB);
+            R* line = A + T.base + (row % NB) * kPack<R>;
+            auto at = [&](int col) {
+                return (col / NB) * NB * T.h + (col % NB) / kPack<R> * (T.h * kPack<R>) + col % kPack<R>;
+            };
+            *reinterpret_cast<P2*>(line + at(c2)) = odd ? P2{b[1], b[2]} : P2{b[0], b[1]};
+            line[at(c1)] = odd ? b[0] : b[2];
         }
-        // every other pair of the chunk: diagonal blocks and uncoupled zeros
-        if (p < npairs && rank < 0) {
-            int i, j;
-            tri_decode(p, i, j);
-            R* blk = A + (size_t)(3 * i) * ld + 3 * j;
-            if (i == j) {
-                const R inv = R(1.0 / L.ab[i]);
-                for (int q = 0; q < 3; ++q)
-                    for (int c = 0; c <= q; ++c) blk[(size_t)q * ld + c] = (q == c) ? inv : R(0);
-            } else {
-                for (int q = 0; q < 3; ++q)
-                    for (int c = 0; c < 3; ++c) blk[(size_t)q * ld + c] = R(0);
-            }
-            if (mixed) { coef[2 * p] = 0.f; coef[2 * p + 1] = 0.f; }
-        }
-        // (no barrier here: the next chunk's first barrier separates these reads of
-        // slot from its writes, and wcnt was last read before the barrier above)
     }
     __syncthreads();
 }
 
 // Triangular solves with the stored factor, one workgroup per (atom,
-// frequency), NS rows per thread.  Right-hand side and result by mode:
+// frequency).  Right-hand side and result by mode:
 //   kSolveD      : y = L^{-1} d (left by the factorisation) -> X (solution
 //                  slot) and Tr(X_i)/3                                       [FP64]
 //   kSolveFirst  : y = L^{-1} d -> X                                         [mixed]
@@ -1047,7 +1171,7 @@ __device__ __forceinline__ void assemble_matrix(const ScsArgs& a, int k, int w, 
 //   kSolveLambda : Xbar_i = xbar_i I / 3 from the polarisability adjoints -> lambda
 enum { kSolveD = 0, kSolveFirst = 1, kSolveCorr = 2, kSolveLambda = 3 };
 
-template <typename R, int NS, int NP>
+template <typename R>
 __device__ __forceinline__ void solve_slot(const ScsArgs& a, int k, int w, int n1max, int mode, double* lds) {
     const int n1 = a.counts[k].n1;
     const int N = 3 * n1;
@@ -1055,7 +1179,8 @@ __device__ __forceinline__ void solve_slot(const ScsArgs& a, int k, int w, int n
     const R* A = static_cast<const R*>(a.fac) + a.fac_off[k] + (size_t)w * ld * (N + 3);
     const size_t xo = a.x_off[k] + (size_t)w * N * 3;
     R* Y = reinterpret_cast<R*>(lds);
-    R* zbuf = Y + 9 * n1max;
+    R* extra = Y + 3 * solve_rows(3 * n1max);
+    for (int e = 3 * N + threadIdx.x; e < 3 * solve_rows(N); e += blockDim.x) Y[e] = R(0);
     if (mode == kSolveLambda) {
         const double* abl = a.abar_loc + a.aloc_off[k];
         for (int e = threadIdx.x; e < 3 * N; e += blockDim.x) {
@@ -1068,10 +1193,10 @@ __device__ __forceinline__ void solve_slot(const ScsArgs& a, int k, int w, int n
         for (int e = threadIdx.x; e < 3 * N; e += blockDim.x) Y[e] = R(a.resid[xo + e]);
     } else {
         // the factorisation left y = L^{-1} d in the rows appended to B~
-        for (int e = threadIdx.x; e < 3 * N; e += blockDim.x) Y[e] = A[(size_t)(N + e % 3) * ld + e / 3];
+        for (int e = threadIdx.x; e < 3 * N; e += blockDim.x) Y[e] = A[fac_at<R>(N + 3, N + e % 3, e / 3)];
     }
-    __syncthreads();
-    chol_solve3<R, NS, NP>(A, N, ld, Y, zbuf, mode == kSolveCorr || mode == kSolveLambda);
+    // (the solve's first barrier)
+    chol_solve3<R>(A, N, Y, extra, mode == kSolveCorr || mode == kSolveLambda);
     if (mode == kSolveLambda) {
         for (int e = threadIdx.x; e < 3 * N; e += blockDim.x) a.lam[xo + e] = double(Y[e]);
         return;
@@ -1085,25 +1210,16 @@ __device__ __forceinline__ void solve_slot(const ScsArgs& a, int k, int w, int n
         al[(size_t)s * a.nw + w] = (X[(3 * s) * 3 + 0] + X[(3 * s + 1) * 3 + 1] + X[(3 * s + 2) * 3 + 2]) / 3.0;
 }
 
-// The standalone solves (adjoint lambda; correction of the mixed path): two
-// rows per thread, 256 threads, the first slot loading a block ahead.  Against
-// one row per thread in 512-thread workgroups this keeps three workgroups on a
-// compute unit instead of two (more independent block chains, more loads in
-// flight): 3.45 -> 3.19 ms for the FP64 lambda solve of 1,728 C atoms.
-// Systems of more than 2 x 256 rows (K1 above 170 sites, e.g. r_SCS = 8 A at carbon
-// density) take three rows per thread; the rows' sums are the same either way.
-constexpr int kSolveThreads = 256;
-static_assert(3 * kSolveThreads >= 3 * kMaxN1, "three rows per thread cover the largest system");
-__host__ __device__ inline int solve_slots(int n1max) { return 3 * n1max <= 2 * kSolveThreads ? 2 : 3; }
-template <typename R, int NS>
-__global__ void __launch_bounds__(kSolveThreads, NS == 2 ? 3 : 2) k_scs_solve(ScsArgs a, int n1max, int mode) {
+// The standalone solve (adjoint lambda)
+template <typename R>
+__global__ void __launch_bounds__(kSolveThreads, 3) k_scs_solve(ScsArgs a, int n1max, int mode) {
     extern __shared__ double lds[];
-    solve_slot<R, NS, 1>(a, a.order[blockIdx.x], blockIdx.y, n1max, mode, lds);
+    solve_slot<R>(a, a.order[blockIdx.x], blockIdx.y, n1max, mode, lds);
 }
 
 size_t scs_solve_lds_bytes(int n1max, bool mixed) {
     const size_t r = mixed ? sizeof(float) : sizeof(double);
-    return r * (9 * (size_t)n1max + 2 * NB * kSlotLd);
+    return r * (3 * (size_t)solve_rows(3 * n1max) + 2 * kSolvePart + 3 * NB);
 }
 
 // Refinement residual of the mixed path: resid = d - B~ X in FP64, with B~
@@ -1174,10 +1290,10 @@ static size_t scs_residual_lds_bytes(int n1max) { return sizeof(double) * (9 * (
 // solves and the residual use the same space before and after); Z1, Z2 and L21 are a separate
 // static array so that the compiler sees they cannot alias it.
 static_assert(kChunk == 256, "the 256 threads of the factorisation kernel run the assembly's chunks");
-static_assert(3 * 256 >= 3 * kMaxN1, "three rows per thread of the factorisation kernel cover its first solve");
+static_assert(kSolveThreads == 256, "and its solves");
 static_assert(256 / 64 - 1 <= kMaxParts, "k-split parts of four wavefronts");
-template <typename R, int NS>
-__global__ void __launch_bounds__(256, NS == 2 ? 3 : 2) k_scs_factor(ScsArgs a, int n1max) {
+template <typename R>
+__global__ void __launch_bounds__(256, 3) k_scs_factor(ScsArgs a, int n1max) {
     extern __shared__ double lds[];
     __shared__ R Zsh[3 * NB * kSlotLd];
     __shared__ int ctl[4];
@@ -1204,7 +1320,7 @@ __global__ void __launch_bounds__(256, NS == 2 ? 3 : 2) k_scs_factor(ScsArgs a, 
     }
     // the first solve (backward: the forward substitution was carried by the
     // factorisation) while the factor is still in the caches
-    solve_slot<R, NS, 1>(a, k, w, n1max, sizeof(R) == 4 ? kSolveFirst : kSolveD, lds);
+    solve_slot<R>(a, k, w, n1max, sizeof(R) == 4 ? kSolveFirst : kSolveD, lds);
     if constexpr (sizeof(R) == 4) {
         // the mixed path's refinement in the same launch, the FP32 factor still in
         // the caches for the correction solve
@@ -1212,7 +1328,7 @@ __global__ void __launch_bounds__(256, NS == 2 ? 3 : 2) k_scs_factor(ScsArgs a, 
             __syncthreads();   // X written; the LDS of the solve free
             residual_slot(a, k, w, n1max, lds);
             __syncthreads();   // the residual written
-            solve_slot<R, NS, 1>(a, k, w, n1max, kSolveCorr, lds);
+            solve_slot<R>(a, k, w, n1max, kSolveCorr, lds);
         }
     }
 }
@@ -1840,28 +1956,16 @@ hipError_t launch_scs_rhs(hipStream_t st, const ScsArgs& a, int n1max, int n2max
 hipError_t launch_scs_factor(hipStream_t st, const ScsArgs& a, int n1max, bool mixed) {
     const dim3 grid(a.n, a.nw);
     const size_t lf = factor_dynamic_bytes(n1max, mixed);
-    const bool three = solve_slots(n1max) == 3;
-    if (mixed) {
-        if (three) hipLaunchKernelGGL((k_scs_factor<float, 3>), grid, dim3(256), lf, st, a, n1max);
-        else hipLaunchKernelGGL((k_scs_factor<float, 2>), grid, dim3(256), lf, st, a, n1max);
-    } else {
-        if (three) hipLaunchKernelGGL((k_scs_factor<double, 3>), grid, dim3(256), lf, st, a, n1max);
-        else hipLaunchKernelGGL((k_scs_factor<double, 2>), grid, dim3(256), lf, st, a, n1max);
-    }
+    if (mixed) hipLaunchKernelGGL(k_scs_factor<float>, grid, dim3(256), lf, st, a, n1max);
+    else hipLaunchKernelGGL(k_scs_factor<double>, grid, dim3(256), lf, st, a, n1max);
     return hipGetLastError();
 }
 
 hipError_t launch_scs_lambda(hipStream_t st, const ScsArgs& a, int n1max, bool mixed) {
     const dim3 grid(a.n, a.nw);
     const size_t ls = scs_solve_lds_bytes(n1max, mixed);
-    const bool three = solve_slots(n1max) == 3;
-    if (mixed) {
-        if (three) hipLaunchKernelGGL((k_scs_solve<float, 3>), grid, dim3(kSolveThreads), ls, st, a, n1max, (int)kSolveLambda);
-        else hipLaunchKernelGGL((k_scs_solve<float, 2>), grid, dim3(kSolveThreads), ls, st, a, n1max, (int)kSolveLambda);
-    } else {
-        if (three) hipLaunchKernelGGL((k_scs_solve<double, 3>), grid, dim3(kSolveThreads), ls, st, a, n1max, (int)kSolveLambda);
-        else hipLaunchKernelGGL((k_scs_solve<double, 2>), grid, dim3(kSolveThreads), ls, st, a, n1max, (int)kSolveLambda);
-    }
+    if (mixed) hipLaunchKernelGGL(k_scs_solve<float>, grid, dim3(kSolveThreads), ls, st, a, n1max, (int)kSolveLambda);
+    else hipLaunchKernelGGL(k_scs_solve<double>, grid, dim3(kSolveThreads), ls, st, a, n1max, (int)kSolveLambda);
     return hipGetLastError();
 }
 
