@@ -10,7 +10,7 @@
 // is factorised by a left-looking blocked Cholesky in its own slot of device
 // memory; the factor is kept for the adjoint solve.  A non-positive pivot is a
 // breakdown reported to the host.  Kernels: k_pairlist (pair lists of an atom),
-// k_scs_dvec (d and the rows of d^T), k_scs_factor (assembly of B~,
+// k_scs_dvec (d), k_scs_factor (assembly of B~,
 // factorisation, first solve and the mixed path's refinement), k_scs_solve (the
 // adjoint solve), k_scs_adjoint (pair gradients).
 //
@@ -97,20 +97,20 @@ __device__ inline void inner_buffer(double r, double rin, double& fin, double& d
 // rows and the last column tile only the columns below ld, so that a slot is never larger
 // than (N + 3) x ld.  The factorisation reads the strict lower tiles of L again and of the
 // diagonal tiles only the inverses Z = L_bb^{-1}: a diagonal tile is left holding Z^T (its
-// rows of d^T aside).  With the solves below, 1,728 C at 6 A: k_scs_factor 12.1 -> 10.7 ms
-// (FP32 11.0 -> 9.0), k_scs_solve 3.20 -> 2.14 ms (FP32 1.88 -> 1.09).
+// rows of d^T aside).  With the solves and the pair coefficients below, 1,728 C at 6 A:
+// k_scs_factor 12.1 -> 8.8 ms (FP32 11.0 -> 8.0), k_scs_solve 3.20 -> 2.14 ms (FP32 1.88 ->
+// 1.09).
 //
 // Left-looking blocked Cholesky by one workgroup, 32-column panels P (two 16-column
 // tiles, h = 0, 1), in units of two 16-row tiles from the panel's diagonal down:
 //  (1) update  A[c0:N+3, c0:c0+32] -= L[c0:N+3, 0:c0] L[c0:c0+32, 0:c0]^T  on MFMA
-//      16x16x4, 16 k at a time from aligned 4-vector loads, a ring of chunks in
-//      flight per wavefront.  The tiles of a unit stay in registers, held
+//      16x16x4, 16 k at a time, a ring of chunks in flight per wavefront; the elements of
+//      B~ are formed from its pairs' coefficients (SysSrc) when the sums are done.  The tiles of a unit stay in registers, held
 //      transposed (M = A^T: the accumulator layout in which a tile's four
 //      registers are directly the right-hand operands of the four k-steps of
 //      the next 16 x 16 x 16 product).  Units are handed out from a counter in
 //      LDS; with fewer units than wavefronts their k range is split and the
-//      parts meet in LDS; in long panels the k range of unit 0 is split over
-//      all wavefronts first;
+//      parts meet in LDS;
 //  (2) unit 0 (the diagonal tiles), by one wavefront at raised priority:
 //      factorise the first diagonal tile and invert it (Z1 = L11^{-1}), L21 =
 //      A21 Z1^T, A22 -= L21 L21^T, factorise and invert the second (Z2), all
@@ -263,13 +263,28 @@ __device__ __forceinline__ void diag_block(R* __restrict__ Lt, int jb, R* __rest
     }
 }
 
+// B~ and d^T for the factorisation, which forms their elements where it first needs them:
+// pair (i, j) is cf[i (i + 1) / 2 + j] (i >= j) with block cf.x v v^T + cf.y I, v = r_i - r_j,
+// the diagonal pairs hold (0, 1 / abar_i), and a pair of zeros follows the last.  16 bytes
+// per pair instead of nine elements written (zeros for uncoupled pairs first) and read back:
+// 870 -> 490 KB written per system of 273 rows, k_scs_factor 10.7 -> 8.8 ms (FP32 9.0 -> 8.0).
+typedef double PairCoef __attribute__((ext_vector_type(2)));
+constexpr int kSmallPairs = 37;   // up to 8 sites: kept in LDS (the slot has no room for them)
+struct SysSrc {
+    const PairCoef* cf;    // in the slot's memory behind the tiles
+    const PairCoef* cfs;   // in LDS
+    const double* pos;     // LDS: x, y, z of the K1 sites, stride n1max
+    const double* D;       // d, N x 3
+    int n1, n1max;
+};
+
 // The factorisation (see the storage and algorithm notes above).  Lt: one tile and
-// its padding column; part: kMaxParts x 4 tiles of k-split partial sums; pre: 2 x 4
-// tiles (the prepared unit 0, double-buffered over panels); Z1, Z2, L21: one tile
+// its padding column; part: kMaxParts x 4 tiles of k-split partial sums or the prepared
+// unit 0, double-buffered over panels; Z1, Z2, L21: one tile
 // each; ctl: two unit counters, the diagonal flag and the give-up flag.
 template <typename R>
-__device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R* __restrict__ Lt,
-                                            R* __restrict__ part, R* __restrict__ pre, R* __restrict__ Z1,
+__device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, const SysSrc& B, R* __restrict__ Lt,
+                                            R* __restrict__ part, R* __restrict__ Z1,
                                             R* __restrict__ Z2, R* __restrict__ L21, int* ctl, int dw, bool& ok,
                                             bool& stalled) {
     typedef Mfma<R> M;
@@ -287,6 +302,51 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
     Acc zacc;
 #pragma unroll
     for (int q = 0; q < 4; ++q) zacc[q] = R(0);
+    // Column c of the system as (site, component) and its place among the positions
+    auto site_of = [&](int c, int& comp) {
+        const int j = (int)(__umul24((unsigned)c, 43691u) >> 17);   // c / 3 (exact below 98,304)
+        comp = c - 3 * j;
+        return j;
+    };
+    // m = tiles of B~ - m.  Rows of d^T take the zero pair behind the others (their part of m
+    // holds -d from the start); indices past the system repeat its last row or column, and
+    // above the diagonal the diagonal pair stands in: entries that nothing reads.
+    auto from_system = [&](int c0p, int u, const PairCoef* __restrict__ cf, Acc(&m)[2][2]) {
+        int lio = li, lko = lk;   // (opaque: see the update)
+        asm volatile("" : "+v"(lio), "+v"(lko));
+        int i[2], ip[2], im[2], qi[2];
+        double pi[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const int r = c0p + NB * (2 * u + x) + lio;
+            i[x] = site_of(min(r, N - 1), qi[x]);
+            pi[x] = B.pos[qi[x] * B.n1max + i[x]];
+            ip[x] = r < N ? (i[x] * (i[x] + 1)) >> 1 : B.n1 * (B.n1 + 1) >> 1;
+            im[x] = r < N ? i[x] : 0;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            PairCoef c[2][4];
+            int j[4], qj[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                j[q] = site_of(min(c0p + NB * h + M::acc_row(lko, q), N - 1), qj[q]);
+#pragma unroll
+                for (int x = 0; x < 2; ++x) c[x][q] = cf[(unsigned)(ip[x] + min(j[q], im[x]))];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double* pq = B.pos + qj[q] * B.n1max;
+                const double pj = pq[j[q]];
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    const double vi = pi[x] - B.pos[qi[x] * B.n1max + j[q]];
+                    const double vj = pq[i[x]] - pj;
+                    m[x][h][q] = R(c[x][q][0] * vi * vj + (qi[x] == qj[q] ? c[x][q][1] : 0.0)) - m[x][h][q];
+                }
+            }
+        }
+    };
     // (1) the update of unit u (row tiles 2u, 2u + 1; both column tiles) of the panel
     // at column c0p (mtp row tiles from its diagonal down, a second column tile if twop)
     // with the chunks cb, cb + st, .. below ce: m[x][h] = A(2u + x, h)^T - (L_h L_t^T)^T,
@@ -302,40 +362,33 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
         // nothing reads
         bool v[2][2];
         FacTile ti[2];
-        int row[2];
 #pragma unroll
         for (int x = 0; x < 2; ++x) {
             const int t = 2 * u + x;
             ti[x] = fac_tile(Nr, min(c0p / NB + t, ntr - 1));
-            row[x] = min(lio, ti[x].h - 1);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                v[x][h] = t < mtp && (h == 0 || twop) && !(t == 0 && h == 1);
-                if (init != 2) {
-                    const int J = min(c0p / NB + h, min(c0p / NB + t, ntc - 1));   // (upper tile: not used)
-                    const R* T = A + ti[x].base + J * NB * ti[x].h;
-                    const int wid = min(NB, ld - NB * J);   // a multiple of 4; zero beyond
-                    if constexpr (sizeof(R) == 8) {
+            for (int h = 0; h < 2; ++h) v[x][h] = t < mtp && (h == 0 || twop) && !(t == 0 && h == 1);
+        }
+        // sums of products (less m as given for init 2, less d in its rows for init 0); the
+        // matrix minus them at the end
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const R val = T[fac_in_tile<R>(ti[x].h, row[x], lko + min(4 * q, wid - 4))];
-                            m[x][h][q] = (init == 0 && v[x][h] && 4 * q < wid) ? val : R(0);
-                        }
-                    } else {
-                        const V4 val = *reinterpret_cast<const V4*>(T + fac_in_tile<R>(ti[x].h, row[x], min(4 * lko, wid - 4)));
+        for (int y = 0; y < 4; ++y)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            m[x][h][q] = (init == 0 && v[x][h] && 4 * lko < wid) ? val[q] : R(0);
+            for (int q = 0; q < 4; ++q) m[y >> 1][y & 1][q] = init == 2 ? -m[y >> 1][y & 1][q] : R(0);
+        if (init == 0 && c0p + NB * (2 * u + 2) > N) {   // uniform: the last units hold rows of d^T
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const int r = c0p + NB * (2 * u + x) + lio, rd = min(max(r - N, 0), 2);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const R d = R(B.D[3 * min(c0p + NB * h + M::acc_row(lko, q), N - 1) + rd]);
+                        m[x][h][q] = r >= N ? -d : R(0);
                     }
-                }
             }
         }
         if (cb < ce) {   // uniform
-            // sums of products minus the tiles, negated at the end
-#pragma unroll
-            for (int y = 0; y < 4; ++y)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) m[y >> 1][y & 1][q] = -m[y >> 1][y & 1][q];
             unsigned at[2], ah[2];
             FacTile th[2];
 #pragma unroll
@@ -378,6 +431,11 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
                     fetch(j, ch + (j + kRing) * st);
                 }
             }
+        }
+        if (init == 0) {
+            if (B.n1 * (B.n1 + 1) / 2 < kSmallPairs) from_system(c0p, u, B.cfs, m);   // uniform
+            else from_system(c0p, u, B.cf, m);
+        } else {
 #pragma unroll
             for (int y = 0; y < 4; ++y)
 #pragma unroll
@@ -393,6 +451,10 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
     };
     auto has_pre = [&](int Pq) { return Pq >= 2 && Pq < npan && kparts(Pq) == 1; };
     const int pw = (dw + 1) % nwave;
+    // the two buffers of the prepared unit 0, in the space of the parts behind the two tiles
+    // of the diagonal unit: a panel has either (S > 1 from some panel on, S = 1 before)
+    static_assert(kMaxParts * 4 >= 10, "room for both buffers");
+    R* pre = part + 2 * 4 * 64;
     bool good = true;
     if (tid < 4) ctl[tid] = 0;
     __syncthreads();
@@ -419,9 +481,11 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
             R* tile = A + T.base + J * NB * T.h;
             if (li < rmin || li >= T.h) return;
             if constexpr (sizeof(R) == 8) {
+                const unsigned lane8 = 8u * (unsigned)fac_in_tile<R>(T.h, li, lk);   // column lk + 4q: 4 h q elements on
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    if (NB * J + 4 * q < ld) tile[fac_in_tile<R>(T.h, li, lk + 4 * q)] = xt[q];   // uniform
+                    if (NB * J + 4 * q < ld)   // uniform
+                        *reinterpret_cast<R*>(reinterpret_cast<char*>(tile + 4 * T.h * q) + lane8) = xt[q];
             } else if (NB * J + 4 * lk < ld) {
                 *reinterpret_cast<Acc*>(tile + fac_in_tile<R>(T.h, li, 4 * lk)) = xt;
             }
@@ -519,66 +583,61 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
                 }
             }
         };
-        if (S == 1) {
-            // the diagonal wavefront takes unit 0 and starts its chain at once; units 1..
-            // go to whichever wavefront asks next
-            // the chain of the diagonal tiles is the panel's critical path: its
-            // wavefront issues ahead of the other workgroups' updates on its SIMD and
-            // finds unit 0 prepared but for the last two chunks
-            if (wave == dw) {
+        // The items of a wavefront, through one copy of the code each of the update, the
+        // diagonal and the units below (all of it has to fit the instruction cache).
+        // S = 1: the diagonal wavefront takes unit 0 and starts its chain at once (the
+        // panel's critical path: it issues ahead of the other workgroups' updates on its
+        // SIMD and finds unit 0 prepared but for the last two chunks); the next wavefront
+        // prepares unit 0 of the next panel with this panel's chunks; units 1 .. go to
+        // whichever wavefront asks next.
+        // S > 1, few units: item g = (unit g % nu, part g / nu) on wavefront dw + g; the parts
+        // s > 0 go through LDS to the wavefront of part 0, which adds them in order.
+        const bool split = S > 1;
+        const int gs = (wave - dw + nwave) % nwave;
+        enum { kDiag, kPrepare, kBelow };
+        int kind = split ? (gs % nu == 0 ? kDiag : kBelow)
+                         : wave == dw ? kDiag : (wave == pw && has_pre(P + 1)) ? kPrepare : kBelow;
+        if (tid == 0) ctl[(P + 1) & 1] = 0;   // the next panel's counter (last used before the previous barrier)
+        int* ctr = ctl + (P & 1);
+        for (;;) {
+            int u = 0, cb = 0, st = 1, init = 0;
+            bool have = true;
+            if (split) {
+                have = gs < nu * S;
+                u = gs % nu;
+                cb = gs / nu;
+                st = S;
+                init = cb == 0 ? 0 : 1;
+            } else if (kind == kBelow) {
+                int g = 0;
+                if (lane == 0) g = atomicAdd(ctr, 1);
+                u = 1 + __builtin_amdgcn_readfirstlane(g);
+                if (u >= nu) break;
+            }
+            Acc m[2][2] = {{zacc, zacc}, {zacc, zacc}};   // defined on every path: nothing carried between items
+            if (kind == kDiag) {
                 __builtin_amdgcn_s_setprio(2);
-                Acc m[2][2];
                 if (has_pre(P)) {
                     const R* pr = pre + (P & 1) * 16 * 64;
 #pragma unroll
                     for (int y = 0; y < 4; ++y)
 #pragma unroll
                         for (int q = 0; q < 4; ++q) m[y >> 1][y & 1][q] = pr[(y * 4 + q) * 64 + lane];
-                    update(c0, mt, two, 0, nch - 2, 1, nch, 2, m);
-                } else {
-                    update(c0, mt, two, 0, 0, 1, nch, 0, m);
+                    cb = nch - 2;
+                    init = 2;
                 }
-                diag_unit(m);
-                __builtin_amdgcn_s_setprio(0);
             }
-            if (wave == pw && has_pre(P + 1)) {   // unit 0 of the next panel with this panel's chunks
-                const int c0n = c0 + 2 * NB;
-                Acc m[2][2];
-                update(c0n, mt - 2, N - c0n > NB, 0, 0, 1, nch, 0, m);
-                R* pr = pre + ((P + 1) & 1) * 16 * 64;
+            const int ahead = kind == kPrepare ? 1 : 0;   // (its chunks: this panel's)
+            if (have) update(c0 + 2 * NB * ahead, mt - 2 * ahead, ahead ? N - c0 - 2 * NB > NB : two, u, cb, st, nch, init, m);
+            if (split) {
+                if (have && cb > 0) {
 #pragma unroll
-                for (int y = 0; y < 4; ++y)
+                    for (int y = 0; y < 4; ++y)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) pr[(y * 4 + q) * 64 + lane] = m[y >> 1][y & 1][q];
-            }
-            if (tid == 0) ctl[(P + 1) & 1] = 0;   // the next panel's counter (last used before the previous barrier)
-            int* ctr = ctl + (P & 1);
-            for (;;) {
-                int g = 0;
-                if (lane == 0) g = atomicAdd(ctr, 1);
-                g = __builtin_amdgcn_readfirstlane(g);
-                if (1 + g >= nu) break;
-                Acc m[2][2];
-                update(c0, mt, two, 1 + g, 0, 1, nch, 0, m);
-                below_unit(1 + g, m);
-            }
-        } else {
-            // few units: item g = (unit g % nu, part g / nu) on wavefront dw + g; the parts
-            // s > 0 go through LDS to the wavefront of part 0, which adds them in order
-            const int g = (wave - dw + nwave) % nwave;
-            const bool have = g < nu * S;
-            const int u = g % nu, s = g / nu;
-            Acc m[2][2] = {{zacc, zacc}, {zacc, zacc}};   // defined on every path: nothing carried between panels
-            if (have) update(c0, mt, two, u, s, S, nch, s == 0 ? 0 : 1, m);
-            if (have && s > 0) {
-#pragma unroll
-                for (int y = 0; y < 4; ++y)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) part[(((g - nu) * 4 + y) * 4 + q) * 64 + lane] = m[y >> 1][y & 1][q];
-            }
-            if (tid == 0) ctl[(P + 1) & 1] = 0;
-            __syncthreads();
-            if (have && s == 0) {
+                        for (int q = 0; q < 4; ++q) part[(((gs - nu) * 4 + y) * 4 + q) * 64 + lane] = m[y >> 1][y & 1][q];
+                }
+                __syncthreads();
+                if (!have || cb > 0) break;
                 for (int s2 = 1; s2 < S; ++s2) {
                     const int g2 = u + s2 * nu;
 #pragma unroll
@@ -586,15 +645,23 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, R*
 #pragma unroll
                         for (int q = 0; q < 4; ++q) m[y >> 1][y & 1][q] += part[(((g2 - nu) * 4 + y) * 4 + q) * 64 + lane];
                 }
-                if (u == 0) {
-                    __builtin_amdgcn_s_setprio(2);
-                    diag_unit(m);
-                    __builtin_amdgcn_s_setprio(0);
-                } else {
-                    below_unit(u, m);
-                }
             }
+            if (kind == kDiag) {
+                diag_unit(m);
+                __builtin_amdgcn_s_setprio(0);
+            } else if (kind == kPrepare) {
+                R* pr = pre + ((P + 1) & 1) * 16 * 64;
+#pragma unroll
+                for (int y = 0; y < 4; ++y)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) pr[(y * 4 + q) * 64 + lane] = m[y >> 1][y & 1][q];
+            } else {
+                below_unit(u, m);
+            }
+            if (split) break;
+            kind = kBelow;
         }
+        __builtin_amdgcn_s_setprio(0);
         __syncthreads();   // the panel's columns are in the matrix before the next panel reads them
     }
     ok = good;
@@ -965,10 +1032,10 @@ __device__ inline int32_t* pair_segs(const ScsArgs& a, int k) {
 }
 
 // sites only (assembly): K1 sites then shell sites
-// assembly of d: K1 sites and shell sites; assembly of B~: K1 sites
+// assembly of d: K1 sites and shell sites; of B~: three arrays of K1 sites (the positions apart)
 static size_t dvec_lds_bytes(int n1max, int n2max) { return sizeof(double) * 6 * ((size_t)n1max + n2max); }
 static size_t matrix_lds_bytes(int n1max) {
-    return sizeof(double) * 6 * (size_t)n1max;
+    return sizeof(double) * 3 * (size_t)n1max;
 }
 size_t scs_assemble_lds_bytes(int n1max, int n2max) {
     return std::max(dvec_lds_bytes(n1max, n2max), matrix_lds_bytes(n1max));
@@ -1012,13 +1079,13 @@ __device__ inline void load_sites(const ScsArgs& a, int k, int w, int n1, int n1
     }
 }
 
-// T_SR of K1 pair (i, j) as (A, B) in the arithmetic type P, with rhat in double
+// T_SR of K1 pair (i, j) as (A, B) in the arithmetic type P, with rhat, r and 1/r in double
 template <typename P>
 __device__ inline SrPair<P> k1_pair(const ScsArgs& a, const ScsLds& L, int i, int j, double rc, double rh[3],
-                                    double& r) {
+                                    double& r, double& ir) {
     const double v[3] = {L.px[i] - L.px[j], L.py[i] - L.py[j], L.pz[i] - L.pz[j]};
     r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-    const double ir = 1.0 / r;
+    ir = 1.0 / r;
     rh[0] = v[0] * ir; rh[1] = v[1] * ir; rh[2] = v[2] * ir;
     const double s_ij = sqrt(L.sg[i] * L.sg[i] + L.sg[j] * L.sg[j]);
     return sr_pair<P>(P(r), P(ir), P(s_ij), P(a.beta * (L.R[i] + L.R[j])), P(a.damp_d), P(rc), P(a.r_buf),
@@ -1091,75 +1158,62 @@ __global__ void __launch_bounds__(kChunk) k_scs_dvec(ScsArgs a, int n1max, int n
     }
 }
 
-// Assembly of the lower triangle of B~ and of the rows of d^T below it (into the factor
-// slot; with d^T there the factorisation carries out the forward substitution) by the
-// workgroup of (atom, frequency) that then factorises it: the slot is filled with zeros in
-// whole lines, then the coupled pairs, one per thread straight from the a-major list, write
-// their blocks.  (Going through all pairs in triangle order kept two of four wavefronts out
-// of the evaluation, as about half of the pairs of a sphere are coupled.)  The mixed path
-// also keeps the FP32 pair coefficients for the refinement residual.
+// Assembly of B~ as its pairs' coefficients (see SysSrc), by the workgroup of (atom,
+// frequency) that then factorises it: all pairs are set to zero in whole lines, then the
+// coupled pairs are evaluated, one per thread straight from the a-major list.  (Going
+// through all pairs in triangle order kept two of four wavefronts out of the evaluation, as
+// about half of the pairs of a sphere are coupled.)  The mixed path also keeps the FP32 pair
+// coefficients for the refinement residual.
+// pos: 3 n1max doubles that outlast the factorisation; lds: scratch; small: kSmallPairs pairs
 template <typename R>
-__device__ __forceinline__ void assemble_matrix(const ScsArgs& a, int k, int w, int n1max, double* lds) {
+__device__ __forceinline__ SysSrc assemble_matrix(const ScsArgs& a, int k, int w, int n1max, double* pos, double* lds,
+                                                  PairCoef* small) {
     constexpr bool mixed = sizeof(R) == 4;
-    typedef typename PackT<R>::type PV;
-    typedef R P2 __attribute__((ext_vector_type(2)));
     const int t = threadIdx.x;
     const Counts cnt = a.counts[k];
     const int n1 = cnt.n1, n12 = cnt.n12, n2 = n12 - n1;
     const int N = 3 * n1, Nr = N + 3;
     const int ld = a.fac_ld[k];
     const double rc = a.sinfo[a.atom_struct[k]].r_scs;
-    ScsLds L = scs_assemble_lds(lds, n1max, 0, true);
+    ScsLds L = {};
+    L.px = pos;
+    L.py = L.px + n1max;
+    L.pz = L.py + n1max;
+    L.ab = lds;
+    L.sg = L.ab + n1max;
+    L.R = L.sg + n1max;
     R* A = static_cast<R*>(a.fac) + a.fac_off[k] + (size_t)w * ld * Nr;
     const int npairs = n1 * (n1 + 1) / 2;
+    const FacTile T = fac_tile(Nr, (Nr - 1) / NB);   // the last row tile, ld columns
+    PairCoef* cf = npairs < kSmallPairs ? small : reinterpret_cast<PairCoef*>(A + (T.base + T.h * ld));
     float* coef = mixed ? a.coef + a.coef_off[k] + (size_t)w * 2 * npairs : nullptr;
     const int32_t* seg_a = pair_segs(a, k) + (n12 + 2);
     const int32_t* la = a.pl_i + a.pl_off[k] + (int64_t)n1 * n2;
     load_sites(a, k, w, n1, n1, L);
-    {
-        const FacTile T = fac_tile(Nr, (Nr - 1) / NB);   // the last row tile, ld columns
-        PV zero;
-#pragma unroll
-        for (int e = 0; e < kPack<R>; ++e) zero[e] = R(0);
-        PV* slot = reinterpret_cast<PV*>(A);
-        for (int e = t; e < (T.base + T.h * ld) / kPack<R>; e += kChunk) slot[e] = zero;
-        if (mixed)
-            for (int e = t; e < 2 * npairs; e += kChunk) coef[e] = 0.f;
+    for (int e = t; e <= npairs; e += kChunk) {
+        cf[e] = PairCoef{0.0, 0.0};
+        if (mixed && e < npairs) {
+            coef[2 * e] = 0.f;
+            coef[2 * e + 1] = 0.f;
+        }
     }
     __syncthreads();
-    // d^T, the diagonal blocks' diagonals, the coupled pairs' blocks
-    const double* D = (mixed ? a.dvec : a.xsol) + a.x_off[k] + (size_t)w * N * 3;
-    for (int e = t; e < 3 * N; e += kChunk) A[fac_at<R>(Nr, N + e % 3, e / 3)] = R(D[e]);
-    for (int r = t; r < N; r += kChunk) A[fac_at<R>(Nr, r, r)] = R(1.0 / L.ab[r / 3]);
+    for (int i = t; i < n1; i += kChunk) cf[i * (i + 1) / 2 + i] = PairCoef{0.0, 1.0 / L.ab[i]};
     const int P11 = seg_a[n1];
     for (int e = t; e < P11; e += kChunk) {
         const int32_t ent = la[e];
         const int i = ent & 0xFFFF, j = ent >> 16;   // i > j
-        double rh[3], rr;
-        const SrPair<R> tp = k1_pair<R>(a, L, i, j, rc, rh, rr);
+        const int p = i * (i + 1) / 2 + j;
+        double rh[3], r, ir;
+        const SrPair<R> tp = k1_pair<R>(a, L, i, j, rc, rh, r, ir);
         if (mixed) {
-            const int p = i * (i + 1) / 2 + j;
             coef[2 * p] = (float)tp.A;
             coef[2 * p + 1] = (float)tp.B;
         }
-        const double Av = double(tp.A), Bv = double(tp.B);
-        // columns 3j .. 3j + 2: an aligned pair and a single one (pairs never straddle tiles)
-        const bool odd = (j & 1) != 0;
-        const int c2 = 3 * j + (odd ? 1 : 0), c1 = 3 * j + (odd ? 0 : 2);
-        for (int q = 0; q < 3; ++q) {
-            R b[3];
-            for (int c = 0; c < 3; ++c) b[c] = R(Av * rh[q] * rh[c] + (q == c ? Bv : 0.0));
-            const int row = 3 * i + q;
-            const FacTile T = fac_tile(Nr, row / NB);
-            R* line = A + T.base + (row % NB) * kPack<R>;
-            auto at = [&](int col) {
-                return (col / NB) * NB * T.h + (col % NB) / kPack<R> * (T.h * kPack<R>) + col % kPack<R>;
-            };
-            *reinterpret_cast<P2*>(line + at(c2)) = odd ? P2{b[1], b[2]} : P2{b[0], b[1]};
-            line[at(c1)] = odd ? b[0] : b[2];
-        }
+        cf[p] = PairCoef{double(tp.A) * ir * ir, double(tp.B)};
     }
     __syncthreads();
+    return SysSrc{cf, small, pos, (mixed ? a.dvec : a.xsol) + a.x_off[k] + (size_t)w * N * 3, n1, n1max};
 }
 
 // Triangular solves with the stored factor, one workgroup per (atom,
@@ -1297,10 +1351,13 @@ __global__ void __launch_bounds__(256, 3) k_scs_factor(ScsArgs a, int n1max) {
     extern __shared__ double lds[];
     __shared__ R Zsh[3 * NB * kSlotLd];
     __shared__ int ctl[4];
-    R* Lt = reinterpret_cast<R*>(lds);
+    __shared__ PairCoef small[kSmallPairs];
     const int k = a.order[blockIdx.x];
     const int w = blockIdx.y;
-    assemble_matrix<R>(a, k, w, n1max, lds);   // ends with a barrier
+    double* pos = lds;   // 3 n1max, an even number
+    double* rest = lds + 3 * n1max + (n1max & 1);
+    R* Lt = reinterpret_cast<R*>(rest);
+    const SysSrc B = assemble_matrix<R>(a, k, w, n1max, pos, rest, small);   // ends with a barrier
     const int N = 3 * a.counts[k].n1;
     const int ld = a.fac_ld[k];
     R* A = static_cast<R*>(a.fac) + a.fac_off[k] + (size_t)w * ld * (N + 3);
@@ -1308,7 +1365,7 @@ __global__ void __launch_bounds__(256, 3) k_scs_factor(ScsArgs a, int n1max) {
     const int dw = (k + w) % (blockDim.x >> 6);
     bool ok = true, stalled = false;
     R* part = Lt + NB * kSlotLd;
-    chol_factor<R>(A, N, ld, Lt, part, part + kMaxParts * 16 * 64, Zsh, Zsh + NB * kSlotLd, Zsh + 2 * NB * kSlotLd,
+    chol_factor<R>(A, N, ld, B, Lt, part, Zsh, Zsh + NB * kSlotLd, Zsh + 2 * NB * kSlotLd,
                    ctl, dw, ok, stalled);   // ends with a barrier
     if (!ok && (threadIdx.x & 63) == 0) {   // only lanes of the diagonal wave can fail
         atomicOr(a.err, 4);
@@ -1320,37 +1377,38 @@ __global__ void __launch_bounds__(256, 3) k_scs_factor(ScsArgs a, int n1max) {
     }
     // the first solve (backward: the forward substitution was carried by the
     // factorisation) while the factor is still in the caches
-    solve_slot<R>(a, k, w, n1max, sizeof(R) == 4 ? kSolveFirst : kSolveD, lds);
+    solve_slot<R>(a, k, w, n1max, sizeof(R) == 4 ? kSolveFirst : kSolveD, rest);
     if constexpr (sizeof(R) == 4) {
         // the mixed path's refinement in the same launch, the FP32 factor still in
         // the caches for the correction solve
         for (int it = 0; it < a.n_refine; ++it) {
             __syncthreads();   // X written; the LDS of the solve free
-            residual_slot(a, k, w, n1max, lds);
+            residual_slot(a, k, w, n1max, rest);
             __syncthreads();   // the residual written
-            solve_slot<R>(a, k, w, n1max, kSolveCorr, lds);
+            solve_slot<R>(a, k, w, n1max, kSolveCorr, rest);
         }
     }
 }
 
-// dynamic LDS of the factorisation: the diagonal tile, the k-split parts and the two
-// buffers of the prepared unit 0
+// dynamic LDS of the factorisation: the diagonal tile and the k-split parts (the two
+// buffers of the prepared unit 0 share their space)
 static size_t factor_panel_bytes(bool mixed) {
     const size_t r = mixed ? sizeof(float) : sizeof(double);
-    return r * ((size_t)NB * kSlotLd + (size_t)(kMaxParts + 2) * 16 * 64);
+    return r * ((size_t)NB * kSlotLd + (size_t)kMaxParts * 16 * 64);
 }
 
 // dynamic LDS of the assembly and factorisation kernel
 static size_t factor_dynamic_bytes(int n1max, bool mixed) {
     const size_t solve = scs_solve_lds_bytes(n1max, mixed);
-    return std::max(std::max(factor_panel_bytes(mixed), matrix_lds_bytes(n1max)),
+    return sizeof(double) * (3 * (size_t)n1max + n1max % 2) +
+           std::max(std::max(factor_panel_bytes(mixed), matrix_lds_bytes(n1max)),
                     mixed ? std::max(solve, scs_residual_lds_bytes(n1max)) : solve);
 }
 
 // all LDS of the assembly and factorisation: the dynamic part and Z1, Z2, L21
 size_t scs_factor_lds_bytes(int n1max, bool mixed) {
     const size_t r = mixed ? sizeof(float) : sizeof(double);
-    return factor_dynamic_bytes(n1max, mixed) + r * 3 * NB * kSlotLd;
+    return factor_dynamic_bytes(n1max, mixed) + r * 3 * NB * kSlotLd + sizeof(PairCoef) * kSmallPairs;
 }
 
 
@@ -1459,8 +1517,8 @@ __global__ void __launch_bounds__(kChunk, 3) k_scs_adjoint(ScsArgs a, int n1max,
             if (e < P) {
                 const int i = ent >> 16, j = ent & 0xFFFF;
                 key = i;
-                double rh[3], r;
-                const SrPair<R> tp = k1_pair<R>(a, L, i, j, rc, rh, r);
+                double rh[3], r, ir;
+                const SrPair<R> tp = k1_pair<R>(a, L, i, j, rc, rh, r, ir);
                 const double* Xi = L.X + 9 * i;
                 const double* Yi = L.Y + 9 * i;
                 const double* Xj = L.X + 9 * j;

@@ -179,7 +179,7 @@ struct ScsArgs {
     const StructInfo* sinfo;
     double beta, damp_d, r_buf, r_inner;   // bohr
     void* fac;               // factor slots (double or float): per (atom, frequency) (N + 3) * ld, used by the
-                             // 16x16 tiles of B~'s lower triangle and of the rows of d^T
+                             // 16x16 tiles of the factor and of y^T = (L^{-1} d)^T below it, then B~'s pair coefficients
     const int64_t* fac_off;
     const int32_t* fac_ld;   // ld >= N, a multiple of 4
     float* coef;             // mixed path: FP32 pair coefficients (A, B) of B~, per atom nw * n1 (n1 + 1) / 2 pairs
