@@ -94,28 +94,28 @@ template <> struct MfmaW<float> {
     static __device__ inline int acc_row(int g, int q) { return 4 * g + q; }
 };
 
-// Workgroup GEMM on the matrix cores: out(m, n) = sum_k A[m][k] B[n][k] with both operands k-contiguous
-// (row-major, lda/ldb multiples of 4, K a multiple of 4).  Lane (i, g) of an MFMA
-// operand reads the 4-vector k = 16 c + 4 g .. + 3 and feeds element e to k-step e,
-// the same permutation of k for both operands; 16 k per chunk, the next chunk in
-// flight.  Each wavefront takes MR 16-row strips times up to NVMAX 16-column tiles.
-// With `lower` set, only items holding entries on or below the diagonal are
-// computed (for a product known to be symmetric; the rest of the output is left
-// as it was).
-template <int MR, int NVMAX, typename W, typename ST>
-__device__ __forceinline__ void mfma_gemm_nt(int M, int N, int K, const W* __restrict__ A, int lda,
-                                             const W* __restrict__ B, int ldb, bool lower, ST st) {
+// Symmetric workgroup product on the matrix cores: out(m, n) = sum_k A[m][k] B[n][k] for the
+// items holding entries on or below the diagonal of the M x M result (the rest of the output
+// is left as it was), both operands k-contiguous (row-major, ld a multiple of 4, K a multiple
+// of 4).  Lane (i, g) of an MFMA operand reads the 4-vector k = 16 c + 4 g .. + 3 and feeds
+// element e to k-step e, the same permutation of k for both operands.  Items of MR 16-row
+// strips times up to MR 16-column tiles; the next chunk of 16 k is in flight in a second set
+// of registers, every load with clamped indices and no condition (rows past M repeat the last
+// one, nothing stores them; k past K is zeroed in A).  Tbar per atom of 64 C open: 39.7k ->
+// 29.9k cycles against conditional loads, which were waited for at once (1,728 C at 6 A,
+// where more wavefronts hide them: 293k -> 289k).
+template <int MR, typename W, typename ST>
+__device__ __forceinline__ void mfma_syrk_nt(int M, int K, const W* __restrict__ A, const W* __restrict__ B, int ld,
+                                             ST st) {
     typedef MfmaW<W> Mf;
     typedef W V4 __attribute__((ext_vector_type(4)));
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, nwave = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = lane & 15, lk = lane >> 4;
     const int mt = (M + 16 * MR - 1) / (16 * MR);   // items of MR 16-row strips
-    const int nt = (N + 15) / 16;
-    const int ng = (nt + NVMAX - 1) / NVMAX;
+    const int nt = (M + 15) / 16;
     const int nch = (K + 15) / 16;
-    const V4 zero = {W(0), W(0), W(0), W(0)};
-    auto kin = [&](int ch) { return ch < nch && 16 * ch + 4 * lk < K; };
-    // MR 16-row strips times NV column tiles (NV = the tiles of the group inside N)
+    // MR 16-row strips times NV column tiles (NV = the tiles of the group inside M)
     auto item = [&](int m0, int tc0, auto nvc) {
         constexpr int NV = decltype(nvc)::value;
         typename Mf::acc acc[MR][NV];
@@ -125,69 +125,70 @@ __device__ __forceinline__ void mfma_gemm_nt(int M, int N, int K, const W* __res
             for (int c = 0; c < NV; ++c)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) acc[x][c][q] = W(0);
-        const W* pa[MR];
-        bool aok[MR];
+        unsigned oa[MR], ob[NV];
 #pragma unroll
-        for (int x = 0; x < MR; ++x) {
-            const int am = m0 + 16 * x + li;
-            aok[x] = am < M;
-            pa[x] = A + (size_t)(aok[x] ? am : 0) * lda + 4 * lk;
-        }
-        const W* pb[NV];
-        bool bok[NV];
-        int bn[NV];
+        for (int x = 0; x < MR; ++x) oa[x] = (unsigned)min(m0 + 16 * x + li, M - 1) * (unsigned)ld;
 #pragma unroll
-        for (int c = 0; c < NV; ++c) {
-            bn[c] = (tc0 + c) * 16 + li;
-            bok[c] = bn[c] < N;
-            pb[c] = B + (size_t)(bok[c] ? bn[c] : 0) * ldb + 4 * lk;
-        }
-        V4 a[MR], b[NV];
+        for (int c = 0; c < NV; ++c) ob[c] = (unsigned)min((tc0 + c) * 16 + li, M - 1) * (unsigned)ld;
+        struct Set {
+            V4 a[MR], b[NV];
+        };
+        auto fetch = [&](Set& s, int ch) {
+            const unsigned k0 = (unsigned)min(16 * min(ch, nch - 1) + 4 * lk, K - 4);
 #pragma unroll
-        for (int x = 0; x < MR; ++x) a[x] = (aok[x] && kin(0)) ? *reinterpret_cast<const V4*>(pa[x]) : zero;
+            for (int x = 0; x < MR; ++x) s.a[x] = *reinterpret_cast<const V4*>(A + (oa[x] + k0));
 #pragma unroll
-        for (int c = 0; c < NV; ++c) b[c] = (bok[c] && kin(0)) ? *reinterpret_cast<const V4*>(pb[c]) : zero;
-        for (int ch = 0; ch < nch; ++ch) {
-            const bool kn = kin(ch + 1);
-            V4 na[MR], nb[NV];
+            for (int c = 0; c < NV; ++c) s.b[c] = *reinterpret_cast<const V4*>(B + (ob[c] + k0));
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto mma = [&](Set& s, int ch) {
 #pragma unroll
-            for (int x = 0; x < MR; ++x)
-                na[x] = (aok[x] && kn) ? *reinterpret_cast<const V4*>(pa[x] + 16 * (ch + 1)) : zero;
+            for (int x = 0; x < MR; ++x) arrive(s.a[x]);
 #pragma unroll
-            for (int c = 0; c < NV; ++c)
-                nb[c] = (bok[c] && kn) ? *reinterpret_cast<const V4*>(pb[c] + 16 * (ch + 1)) : zero;
+            for (int c = 0; c < NV; ++c) arrive(s.b[c]);
+            if (16 * ch + 16 > K) {   // uniform: the last chunk of a K that is no multiple of 16
+                const bool in = 16 * ch + 4 * lk < K;
+#pragma unroll
+                for (int x = 0; x < MR; ++x)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s.a[x][e] = in ? s.a[x][e] : W(0);
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
                 for (int x = 0; x < MR; ++x)
 #pragma unroll
-                    for (int c = 0; c < NV; ++c) acc[x][c] = Mf::mma(a[x][e], b[c][e], acc[x][c]);
-#pragma unroll
-            for (int x = 0; x < MR; ++x) a[x] = na[x];
-#pragma unroll
-            for (int c = 0; c < NV; ++c) b[c] = nb[c];
+                    for (int c = 0; c < NV; ++c) acc[x][c] = Mf::mma(s.a[x][e], s.b[c][e], acc[x][c]);
+        };
+        Set s0, s1;
+        fetch(s0, 0);
+        for (int ch = 0; ch < nch; ch += 2) {
+            fetch(s1, ch + 1);
+            mma(s0, ch);
+            fetch(s0, ch + 2);
+            if (ch + 1 < nch) mma(s1, ch + 1);   // uniform
         }
 #pragma unroll
         for (int x = 0; x < MR; ++x)
 #pragma unroll
             for (int c = 0; c < NV; ++c) {
-                if (bok[c]) {
+                const int n = (tc0 + c) * 16 + li;
+                if (n < M) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int m = m0 + 16 * x + Mf::acc_row(lk, q);
-                        if (m < M) st(m, bn[c], acc[x][c][q]);
+                        if (m < M) st(m, n, acc[x][c][q]);
                     }
                 }
             }
     };
-    for (int t = wave; t < mt * ng; t += nwave) {
-        const int m0 = (t / ng) * 16 * MR;
-        const int tc0 = (t % ng) * NVMAX;
-        if (lower && 16 * tc0 > m0 + 16 * MR - 1) continue;   // wholly above the diagonal
-        const int nv = min(NVMAX, nt - tc0);   // uniform over the wavefront
-        if (nv >= 4) item(m0, tc0, std::integral_constant<int, NVMAX >= 4 ? 4 : 1>());
-        else if (nv == 3) item(m0, tc0, std::integral_constant<int, NVMAX >= 3 ? 3 : 1>());
-        else if (nv == 2) item(m0, tc0, std::integral_constant<int, NVMAX >= 2 ? 2 : 1>());
+    for (int t = wave; t < mt * mt; t += nwave) {
+        const int m0 = (t / mt) * 16 * MR;
+        const int tc0 = (t % mt) * MR;
+        if (16 * tc0 > m0 + 16 * MR - 1) continue;   // wholly above the diagonal
+        const int nv = min(MR, nt - tc0);   // uniform over the wavefront
+        if (nv >= 3) item(m0, tc0, std::integral_constant<int, MR >= 3 ? 3 : 1>());
+        else if (nv == 2) item(m0, tc0, std::integral_constant<int, MR >= 2 ? 2 : 1>());
         else item(m0, tc0, std::integral_constant<int, 1>());
     }
     __syncthreads();
@@ -724,7 +725,7 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax, in
         }
         __syncthreads();
     } else {
-        mfma_gemm_nt<3, 3, W>(N3, N3, KKp, Pm, KKp, Qm, KKp, true, [&](int r, int s, W v) { T[(size_t)r * N3p + s] = v; });
+        mfma_syrk_nt<3, W>(N3, KKp, Pm, Qm, KKp, [&](int r, int s, W v) { T[(size_t)r * N3p + s] = v; });
     }
     for (int e = 9 + tid; e < 3 * N3; e += blockDim.x) {
         W* const t = T + (size_t)(e / 3) * N3p + e % 3;

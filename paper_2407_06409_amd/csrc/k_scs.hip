@@ -197,10 +197,6 @@ __device__ __forceinline__ typename Vec4T<R>::type fac_load4(const R* __restrict
     }
     return v;
 }
-// The compiler tracks loads in flight by register and, where paths meet, waits for the
-// latest of them: a loaded value that one path leaves unread then costs a full wait.  This
-// reads the value (waits for its load) on every path.
-template <typename V> __device__ __forceinline__ void arrive(V& v) { asm volatile("" : "+v"(v)); }
 // the column of a tile that element e of lane group lk of such a load holds
 template <typename R>
 __device__ __forceinline__ int fac_col(int lk, int e) {

@@ -84,6 +84,11 @@ __device__ inline float m_erf(float x) { return erff(x); }
 __device__ inline double m_sqrt(double x) { return sqrt(x); }
 __device__ inline float m_sqrt(float x) { return sqrtf(x); }
 
+// The compiler tracks loads in flight by register and, where paths meet, waits for the
+// latest of them: a loaded value that one path leaves unread then costs a full wait.  This
+// reads the value (waits for its load) on every path.
+template <typename V> __device__ __forceinline__ void arrive(V& v) { asm volatile("" : "+v"(v)); }
+
 // Fermi damping f(r, S) = 1 / (1 + exp(-d (r / S - 1))) and its partial
 // derivatives: df/dr = d f (1 - f) / S, df/dS = -d r f (1 - f) / S^2.
 template <typename P>
