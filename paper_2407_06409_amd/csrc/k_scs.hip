@@ -50,6 +50,50 @@ template <> struct Mfma<float> {
     static __device__ inline int acc_row(int g, int q) { return 4 * g + q; }
 };
 
+// erf(u) from e = exp(-u^2) and iu = 1 / u.  FP64, u >= 1: 1 - (e / u) P(1 / u) with P a
+// polynomial for u exp(u^2) erfc(u) on 1 <= u <= 6.7, a least-squares fit in Chebyshev
+// polynomials, reweighted towards the smallest largest error of e P / u, to values of the
+// function's continued fraction; error of erf below 1e-16.  (Beyond 6.7 the term is below
+// 1e-20.)
+// (in constant memory and visible outside, so read into scalar registers; folded into the
+// code they took 36 vector registers)
+__constant__ double kErfPoly[18] = {
+    0.4981550751511198, -0.07268131761945643, -0.0024323845503493296, 0.0068581806637320036,
+    -0.0029722579490559903, 0.0007100401101900358, 1.3489176394792296e-05, -0.00011946555314113735,
+    7.565445053605531e-05, -3.0213069356892446e-05, 7.145527159318135e-06, 7.237890761575772e-07,
+    -2.0064520352091425e-06, 1.3792883268755802e-06, -6.309455041351348e-07, 1.998532338991096e-07,
+    -3.92151962955357e-08, 3.5001334795832343e-09};
+__device__ inline double m_erf_e(double u, double e, double iu) {
+    if (u < 1.0) return erf(u);
+    const double t = fma(fmax(iu, 1.0 / 6.7), 2.3508771929824563, -1.3508771929824561);
+    double p = kErfPoly[17];
+#pragma unroll
+    for (int k = 16; k >= 0; --k) p = fma(p, t, kErfPoly[k]);
+    return fma(-e * iu, p, 1.0);
+}
+__device__ inline float m_erf_e(float u, float, float) { return erff(u); }
+
+// Coefficients of the short-range core H = -T g + h = -(Hessian of erf(r/s)/r)
+// written as A rhat rhat^T + B I:
+//   A = -(3 g - 2 c u^3 e) / r^3,  B = g / r^3,  c = 2/sqrt(pi), u = r/s, e = exp(-u^2)
+// with g = erf(u) - c u e (Sec. II.B, T_SR with the g and h functions).
+template <typename P>
+__device__ inline void sr_core(P ir, P u, P iu, P& A, P& B, P& dA, P& dB) {
+    const P c = P(kTwoOverSqrtPi);
+    const P e = m_exp(-u * u);
+    const P g = m_erf_e(u, e, iu) - c * u * e;
+    const P u3e = u * u * u * e;
+    const P ir3 = ir * ir * ir;
+    const P ir4 = ir3 * ir;
+    const P Pc = P(3) * g - P(2) * c * u3e;       // A = -Pc / r^3
+    // dPc/dr = 4 c u^5 e / r  (from g' = 2 c u^3 e / r and (u^3 e)' = (3 - 2u^2) u^3 e / r)
+    const P dP = P(4) * c * u3e * u * u * ir;
+    A = -Pc * ir3;
+    dA = -dP * ir3 + P(3) * Pc * ir4;
+    B = g * ir3;
+    dB = P(2) * c * u3e * ir4 - P(3) * g * ir4;
+}
+
 // T_SR,K for one pair as A rhat rhat^T + B I, with radial derivatives.
 template <typename P>
 struct SrPair {
@@ -57,9 +101,9 @@ struct SrPair {
 };
 
 template <typename P>
-__device__ inline SrPair<P> sr_pair(P r, P ir, P s_ij, P S, P damp_d, P rc, P rb, P wmul, P dwmul) {
+__device__ inline SrPair<P> sr_pair(P r, P ir, P u, P iu, P S, P damp_d, P rc, P rb, P wmul, P dwmul) {
     P A, B, dA, dB;
-    sr_core<P>(r, ir, s_ij, A, B, dA, dB);
+    sr_core<P>(ir, u, iu, A, B, dA, dB);
     P dfdr, dfdS, dcut;
     const P f = fermi<P>(r, S, damp_d, dfdr, dfdS);
     const P fc = cutoff_poly<P>(r, rc, rb, dcut);
@@ -81,9 +125,9 @@ __device__ inline void inner_buffer(double r, double rin, double& fin, double& d
     fin = 1.0;
     dfin = 0.0;
     if (r < rin) {
-        const double x = r / rin;
+        const double irin = m_rcp(rin), x = r * irin;
         fin = 3.0 * x * x - 2.0 * x * x * x;
-        dfin = (6.0 * x - 6.0 * x * x) / rin;
+        dfin = (6.0 * x - 6.0 * x * x) * irin;
     }
 }
 
@@ -1080,11 +1124,12 @@ template <typename P>
 __device__ inline SrPair<P> k1_pair(const ScsArgs& a, const ScsLds& L, int i, int j, double rc, double rh[3],
                                     double& r, double& ir) {
     const double v[3] = {L.px[i] - L.px[j], L.py[i] - L.py[j], L.pz[i] - L.pz[j]};
-    r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-    ir = 1.0 / r;
+    const double r2 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
+    ir = m_rsqrt(r2);
+    r = m_sqrt_of(r2, ir);
     rh[0] = v[0] * ir; rh[1] = v[1] * ir; rh[2] = v[2] * ir;
-    const double s_ij = sqrt(L.sg[i] * L.sg[i] + L.sg[j] * L.sg[j]);
-    return sr_pair<P>(P(r), P(ir), P(s_ij), P(a.beta * (L.R[i] + L.R[j])), P(a.damp_d), P(rc), P(a.r_buf),
+    const double s2 = L.sg[i] * L.sg[i] + L.sg[j] * L.sg[j], is = m_rsqrt(s2);
+    return sr_pair<P>(P(r), P(ir), P(r * is), P(s2 * is * ir), P(a.beta * (L.R[i] + L.R[j])), P(a.damp_d), P(rc), P(a.r_buf),
                       P(1), P(0));
 }
 
@@ -1093,13 +1138,13 @@ template <typename P>
 __device__ inline SrPair<P> k2_pair(const ScsArgs& a, const ScsLds& L, int i, int q, double rc, double rh[3],
                                     double& r) {
     const double v[3] = {L.px[i] - L.qx[q], L.py[i] - L.qy[q], L.pz[i] - L.qz[q]};
-    r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-    const double ir = 1.0 / r;
+    const double r2 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2], ir = m_rsqrt(r2);
+    r = m_sqrt_of(r2, ir);
     rh[0] = v[0] * ir; rh[1] = v[1] * ir; rh[2] = v[2] * ir;
-    const double s_ij = sqrt(L.sg[i] * L.sg[i] + L.qsg[q] * L.qsg[q]);
+    const double s2 = L.sg[i] * L.sg[i] + L.qsg[q] * L.qsg[q], is = m_rsqrt(s2);
     double fin, dfin;
     inner_buffer(r, a.r_inner, fin, dfin);
-    return sr_pair<P>(P(r), P(ir), P(s_ij), P(a.beta * (L.R[i] + L.qR[q])), P(a.damp_d), P(rc), P(a.r_buf),
+    return sr_pair<P>(P(r), P(ir), P(r * is), P(s2 * is * ir), P(a.beta * (L.R[i] + L.qR[q])), P(a.damp_d), P(rc), P(a.r_buf),
                       P(fin), P(dfin));
 }
 

@@ -79,10 +79,27 @@ struct Counts {
 // ---------------------------------------------------------------------------
 __device__ inline double m_exp(double x) { return exp(x); }
 __device__ inline float m_exp(float x) { return expf(x); }
-__device__ inline double m_erf(double x) { return erf(x); }
-__device__ inline float m_erf(float x) { return erff(x); }
-__device__ inline double m_sqrt(double x) { return sqrt(x); }
-__device__ inline float m_sqrt(float x) { return sqrtf(x); }
+// 1 / x: in FP64 the hardware estimate and two Newton steps (below 1 ulp, half the
+// instructions of a division; x normal, not infinite).  The pair kernels are bound by the
+// number of FP64 instructions (the vector units are busy 85 % of k_scs_dvec's time): with
+// these forms of the divisions and square roots and the erf of k_scs.hip, 1,728 C at 6 A took
+// k_scs_dvec 1.36 -> 1.10 ms, k_scs_adjoint 3.80 -> 3.32 ms (mixed 1.07 -> 0.95, 3.02 -> 2.96).
+__device__ inline double m_rcp(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ inline float m_rcp(float x) { return 1.0f / x; }
+// 1 / sqrt(x) likewise, and sqrt(x) = x / sqrt(x) with a correction
+__device__ inline double m_rsqrt(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * fma(-x * y, y, 1.0), y, y);
+    return fma(0.5 * fma(-x * y, y, 1.0), y, y);
+}
+__device__ inline double m_sqrt_of(double x, double rsqrt_x) {
+    const double r = x * rsqrt_x;
+    return fma(fma(-r, r, x), 0.5 * rsqrt_x, r);
+}
 
 // The compiler tracks loads in flight by register and, where paths meet, waits for the
 // latest of them: a loaded value that one path leaves unread then costs a full wait.  This
@@ -93,8 +110,10 @@ template <typename V> __device__ __forceinline__ void arrive(V& v) { asm volatil
 // derivatives: df/dr = d f (1 - f) / S, df/dS = -d r f (1 - f) / S^2.
 template <typename P>
 __device__ inline P fermi(P r, P S, P d, P& dfdr, P& dfdS) {
-    const P iS = P(1) / S;
-    const P f = P(1) / (P(1) + m_exp(-d * (r * iS - P(1))));
+    const P iS = m_rcp(S);
+    P x = -d * (r * iS - P(1));
+    if constexpr (sizeof(P) == 8) x = fmin(x, 700.0);   // (the reciprocal of an infinity is not formed)
+    const P f = m_rcp(P(1) + m_exp(x));
     const P g = d * f * (P(1) - f) * iS;
     dfdr = g;
     dfdS = -g * r * iS;
@@ -107,7 +126,7 @@ template <typename P>
 __device__ inline P cutoff_poly(P r, P rc, P rb, P& dcdr) {
     if (r < rc - rb) { dcdr = P(0); return P(1); }
     if (r >= rc) { dcdr = P(0); return P(0); }
-    const P irb = P(1) / rb;
+    const P irb = m_rcp(rb);
     const P x = (r - rc + rb) * irb;
     dcdr = (P(-6) * x + P(6) * x * x) * irb;
     return P(1) - P(3) * x * x + P(2) * x * x * x;
@@ -124,33 +143,10 @@ __device__ inline void radial_tensor_grad(const double rh[3], double r, double A
     const double Cr2 = C[6] * rh[0] + C[7] * rh[1] + C[8] * rh[2];
     const double rCr = rh[0] * Cr0 + rh[1] * Cr1 + rh[2] * Cr2;
     const double tr = C[0] + C[4] + C[8];
-    const double a = (dA - 2.0 * A / r) * rCr + dB * tr;
-    const double b = 2.0 * A / r;
+    const double b = 2.0 * A * m_rcp(r), a = (dA - b) * rCr + dB * tr;
     g[0] = a * rh[0] + b * Cr0;
     g[1] = a * rh[1] + b * Cr1;
     g[2] = a * rh[2] + b * Cr2;
-}
-
-// Coefficients of the short-range core H = -T g + h = -(Hessian of erf(r/s)/r)
-// written as A rhat rhat^T + B I:
-//   A = -(3 g - 2 c u^3 e) / r^3,  B = g / r^3,  c = 2/sqrt(pi), u = r/s, e = exp(-u^2)
-// with g = erf(u) - c u e (Sec. II.B, T_SR with the g and h functions).
-template <typename P>
-__device__ inline void sr_core(P r, P ir, P s, P& A, P& B, P& dA, P& dB) {
-    const P c = P(kTwoOverSqrtPi);
-    const P u = r / s;
-    const P e = m_exp(-u * u);
-    const P g = m_erf(u) - c * u * e;
-    const P u3e = u * u * u * e;
-    const P ir3 = ir * ir * ir;
-    const P ir4 = ir3 * ir;
-    const P Pc = P(3) * g - P(2) * c * u3e;       // A = -Pc / r^3
-    // dPc/dr = 4 c u^5 e / r  (from g' = 2 c u^3 e / r and (u^3 e)' = (3 - 2u^2) u^3 e / r)
-    const P dP = P(4) * c * u3e * u * u * ir;
-    A = -Pc * ir3;
-    dA = -dP * ir3 + P(3) * Pc * ir4;
-    B = g * ir3;
-    dB = P(2) * c * u3e * ir4 - P(3) * g * ir4;
 }
 
 // ---------------------------------------------------------------------------
