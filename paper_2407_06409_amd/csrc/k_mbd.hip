@@ -202,9 +202,10 @@ __device__ __forceinline__ void mfma_syrk_nt(int M, int K, const W* __restrict__
 // over its compute units.
 // out(m, n) = sum_k T[m][k] X[n][k] over k = (site j, component y): a k-step of the MFMA
 // takes one component of four sites (lane group lk: site j0 + lk), a chunk three steps.
-// X: operand rows by column, planes by component: X[n ldx + y ldp + j], in LDS where it
-// fits (planes padded with zeros to ldp, a multiple of four chunks), else in global memory
-// (planes of nK).  Items of one 16-row strip times NV column tiles; a wavefront takes its
+// X: in LDS where it fits, rows by column and planes by component, X[n ldx + y ldp + j]
+// (planes padded with zeros to ldp, a multiple of four chunks); else in global memory by row
+// of the block, X[(3 j + y) ldp + n], so that sixteen lanes read one line (by column, 306
+// sites per neighbourhood took 41.0 ms for the stage, by row 29.8).  Items of one 16-row strip times NV column tiles; a wavefront takes its
 // strips in groups of kDeep chunks, the loads of the next group (clamped indices, no
 // conditions: a load in a conditional block is waited for at once) on their way during
 // the matrix work of this one.  Strips of 16 rows also spread evenly over the SIMDs (18
@@ -270,7 +271,7 @@ __device__ __forceinline__ void mfma_strips(int nK, int N, const W* __restrict__
                     if constexpr (LDSX) {
                         b[y][c] = px[c][y * ldp + site];
                     } else {
-                        const W v = px[c][y * ldp + min(site, nK - 1)];
+                        const W v = px[c][(3 * min(site, nK - 1) + y) * ldp];
                         b[y][c] = site < nK ? v : W(0);
                     }
                 }
@@ -440,8 +441,8 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax, in
 
     // the products' operand: column `col`, site and component of row r
     W* const X = vlds ? Vl : V2;
-    const int ldx = vlds ? operand_ld(nK) : N3, ldp = vlds ? operand_plane(nK) : nK;
-    auto operand_at = [&](int r, int col) -> size_t { return (size_t)col * ldx + (r % 3) * ldp + r / 3; };
+    const int ldx = vlds ? operand_ld(nK) : 1, ldp = vlds ? operand_plane(nK) : ncol, ldj = vlds ? 1 : 3 * ncol;
+    auto operand_at = [&](int r, int col) -> size_t { return (size_t)col * ldx + (r % 3) * ldp + (size_t)(r / 3) * ldj; };
     for (int e = tid; e < (vlds ? ncol * 3 * (ldp - nK) : 0); e += blockDim.x) {   // the planes' padding
         const int row = e / (ldp - nK);
         Vl[(size_t)(row / 3) * ldx + (row % 3) * ldp + nK + e % (ldp - nK)] = W(0);
@@ -473,7 +474,7 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax, in
                 const int i = e / ncol, col = e - i * ncol;
                 const W sq = W(L.sqa[(size_t)i * nq + col / 3]);
                 const W* u = Un + (size_t)(3 * i) * ncol + col;
-                W* x = X + (size_t)col * ldx + i;
+                W* x = X + (size_t)col * ldx + (size_t)i * ldj;
                 const W u0 = u[0], u1 = u[ncol], u2 = u[2 * ncol];
                 x[0] = sq * u0;
                 x[ldp] = sq * u1;
