@@ -318,10 +318,9 @@ __device__ __forceinline__ void product_tlr(int nK, int N, const W* rec, const W
 __host__ __device__ inline int operand_plane(int nK) { return (nK + 4 * kDeep - 1) / (4 * kDeep) * (4 * kDeep); }
 __host__ __device__ inline int operand_ld(int nK) { return (3 * operand_plane(nK)) | 1; }
 
-// 512 threads: the eight wavefronts share the GEMM items of an atom (six
-// 48-row items per Krylov product, 21 lower-triangle items of Tbar), which
-// balances them better than four (measured 4.55 -> 4.42 ms FP64, 3.07 -> 2.62
-// ms FP32 on 1,728 C atoms; 384, 768 and 1,024 threads were slower)
+// 512 threads: the eight wavefronts share the strips of a product (18 at 91 sites) and the 21
+// lower-triangle items of Tbar; four, six, twelve and sixteen wavefronts were slower with
+// 48-row items in both places (4.42 ms FP64 and 2.62 ms FP32 with eight on 1,728 C atoms).
 constexpr int kMbdThreads = 512;
 
 // The dense form: T_LR is stored and every product runs on the matrix cores (the sparse

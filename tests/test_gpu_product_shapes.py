@@ -52,3 +52,27 @@ def test_product_shapes_against_oracle(form, n, n_freq, n_max, precision, forces
         df = np.abs(g["forces"] - f).max()
         print(f"  max |dF| {df:.3e} eV/A", flush=True)
         assert df < f_tol
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_operand_placement_does_not_change_results(precision):
+    """A 33-atom cluster alone (the products' operand in LDS) and in one batch with a cluster of
+    150 sites (operand of the whole launch in global memory): bitwise the same."""
+    import torch
+    from paper_2407_06409_amd import Context, compute_batch
+    from tests.gpu_common import method_params
+    dev = torch.device("cuda:0")
+
+    def desc(n):
+        st = C.hcno_cluster(n, 900 + n)
+        return dict(pos=torch.as_tensor(st.pos, device=dev), species=torch.as_tensor(st.species, device=dev),
+                    v_ratio=torch.as_tensor(st.nu, device=dev), cell=None, pbc=(0, 0, 0), cutoffs=CUT)
+
+    print(f"33 sites alone and with 150, {precision}", flush=True)
+    ctx = Context(0)
+    ctx.set_mbd_product("dense")
+    params = method_params(precision=precision)
+    alone = compute_batch([desc(33)], params, SPECIES_TABLE, ctx=ctx)[0]
+    batch = compute_batch([desc(33), desc(150)], params, SPECIES_TABLE, ctx=ctx)[0]
+    for key in ("energies", "forces"):
+        assert torch.equal(alone[key], batch[key]), key
