@@ -112,7 +112,7 @@ template <typename P>
 __device__ inline P fermi(P r, P S, P d, P& dfdr, P& dfdS) {
     const P iS = m_rcp(S);
     P x = -d * (r * iS - P(1));
-    if constexpr (sizeof(P) == 8) x = fmin(x, 700.0);   // (the reciprocal of an infinity is not formed)
+    if (sizeof(P) == 8 && x > P(700)) x = P(700);   // (the reciprocal of an infinity is not formed; a NaN stays one)
     const P f = m_rcp(P(1) + m_exp(x));
     const P g = d * f * (P(1) - f) * iS;
     dfdr = g;
