@@ -97,8 +97,8 @@ template <> struct MfmaW<float> {
 // Symmetric workgroup product on the matrix cores: out(m, n) = sum_k A[m][k] B[n][k] for the
 // items holding entries on or below the diagonal of the M x M result (the rest of the output
 // is left as it was), both operands k-contiguous (row-major, ld a multiple of 4, K a multiple
-// of 4).  Lane (i, g) of an MFMA operand reads the 4-vector k = 16 c + 4 g .. + 3 and feeds
-// element e to k-step e, the same permutation of k for both operands.  Items of MR 16-row
+// of 4; K = 0: zeros, and nothing is read).  Lane (i, g) of an MFMA operand reads the 4-vector
+// k = 16 c + 4 g .. + 3 and feeds element e to k-step e, the same permutation of k for both operands.  Items of MR 16-row
 // strips times up to MR 16-column tiles; the next chunk of 16 k is in flight in a second set
 // of registers, every load with clamped indices and no condition (rows past M repeat the last
 // one, nothing stores them; k past K is zeroed in A).  Tbar per atom of 64 C open: 39.7k ->
@@ -160,13 +160,15 @@ __device__ __forceinline__ void mfma_syrk_nt(int M, int K, const W* __restrict__
 #pragma unroll
                     for (int c = 0; c < NV; ++c) acc[x][c] = Mf::mma(s.a[x][e], s.b[c][e], acc[x][c]);
         };
-        Set s0, s1;
-        fetch(s0, 0);
-        for (int ch = 0; ch < nch; ch += 2) {
-            fetch(s1, ch + 1);
-            mma(s0, ch);
-            fetch(s0, ch + 2);
-            if (ch + 1 < nch) mma(s1, ch + 1);   // uniform
+        if (nch > 0) {   // uniform: with no column there is nothing to clamp the loads to
+            Set s0, s1;
+            fetch(s0, 0);
+            for (int ch = 0; ch < nch; ch += 2) {
+                fetch(s1, ch + 1);
+                mma(s0, ch);
+                fetch(s0, ch + 2);
+                if (ch + 1 < nch) mma(s1, ch + 1);   // uniform
+            }
         }
 #pragma unroll
         for (int x = 0; x < MR; ++x)
