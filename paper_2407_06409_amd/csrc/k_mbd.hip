@@ -200,8 +200,11 @@ __device__ __forceinline__ void mfma_syrk_nt(int M, int K, const W* __restrict__
 // sqrt(A) rhat and B (block = s s^T + B I, A >= 0), and expanded on the way into the matrix
 // cores: a product reads T_LR once and nothing else of size, and with stored elements it
 // ran at the rate of those reads (600 KB per product at 91 sites: 112k cycles, 5 TB/s over
-// the chip in the Lanczos iteration).  The 4-vectors are 134 KB in FP64, about an XCD's L2
-// over its compute units.
+// the chip in the Lanczos iteration).  The 4-vectors are 134 KB, about an XCD's L2 over its
+// compute units.  They are FP64 on the mixed path too, whose elements are thus formed in FP64
+// and rounded once: from FP32 4-vectors the energies of frames with one atom per local SCS
+// were 5 % further from FP64 (rms; a dimer's block over its directions 8.9e-8 against 3.2e-8
+// with rounded elements and 1.2e-8 now), for 15.71 instead of 15.83 ms on 1,728 C at 6 A.
 // out(m, n) = sum_k T[m][k] X[n][k] over k = (site j, component y): a k-step of the MFMA
 // takes one component of four sites (lane group lk: site j0 + lk), a chunk three steps.
 // X: in LDS where it fits, rows by column and planes by component, X[n ldx + y ldp + j]
@@ -215,15 +218,15 @@ __device__ __forceinline__ void mfma_syrk_nt(int M, int K, const W* __restrict__
 // idle.  1,728 C at 6 A, per atom: four products 551k -> 396k cycles (FP32 325k -> 257k),
 // the Lanczos iteration's eleven 2,427k -> 1,596k.
 constexpr int kDeep = 4;
+typedef double LrRec __attribute__((ext_vector_type(4)));
 __device__ inline int tri(int i, int j) {
     const int hi = max(i, j), lo = min(i, j);
     return ((hi * (hi + 1)) >> 1) + lo;
 }
 template <int NV, bool LDSX, typename W, typename ST>
-__device__ __forceinline__ void mfma_strips(int nK, int N, const W* __restrict__ rec, const W* X, int ldx, int ldp,
+__device__ __forceinline__ void mfma_strips(int nK, int N, const LrRec* __restrict__ rec, const W* X, int ldx, int ldp,
                                             int tc0, ST st) {
     typedef MfmaW<W> Mf;
-    typedef W V4 __attribute__((ext_vector_type(4)));
     const int lane = threadIdx.x & 63, nwave = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = lane & 15, lk = lane >> 4;
@@ -234,10 +237,9 @@ __device__ __forceinline__ void mfma_strips(int nK, int N, const W* __restrict__
     auto row_of = [&](int strip) { return min((16 * strip + li) / 3, nK - 1); };
     int ls = wave, lg = 0;   // strip and group of the next loads
     int row = row_of(ls);
-    auto fetch = [&](V4(&v)[kDeep]) {
+    auto fetch = [&](LrRec(&v)[kDeep]) {
 #pragma unroll
-        for (int j = 0; j < kDeep; ++j)
-            v[j] = *reinterpret_cast<const V4*>(rec + 4 * (unsigned)tri(row, min(4 * (kDeep * lg + j) + lk, nK - 1)));
+        for (int j = 0; j < kDeep; ++j) v[j] = rec[(unsigned)tri(row, min(4 * (kDeep * lg + j) + lk, nK - 1))];
         lg = lg + 1 == ng ? 0 : lg + 1;
         ls = lg == 0 ? ls + nwave : ls;
         row = row_of(ls);
@@ -246,11 +248,11 @@ __device__ __forceinline__ void mfma_strips(int nK, int N, const W* __restrict__
 #pragma unroll
     for (int c = 0; c < NV; ++c) px[c] = X + (size_t)min(16 * (tc0 + c) + li, N - 1) * ldx;
     typename Mf::acc acc[NV];
-    W unit[3];               // the row's component as a unit vector
+    double unit[3];          // the row's component as a unit vector
     auto begin = [&](int strip) {
         const int comp = (16 * strip + li) % 3;
 #pragma unroll
-        for (int y = 0; y < 3; ++y) unit[y] = comp == y ? W(1) : W(0);
+        for (int y = 0; y < 3; ++y) unit[y] = comp == y ? 1.0 : 0.0;
 #pragma unroll
         for (int c = 0; c < NV; ++c)
 #pragma unroll
@@ -258,7 +260,7 @@ __device__ __forceinline__ void mfma_strips(int nK, int N, const W* __restrict__
     };
     int cs = wave, cg = 0;   // strip and group in work
     begin(cs);
-    V4 cur[kDeep], nxt[kDeep];
+    LrRec cur[kDeep], nxt[kDeep];
     fetch(cur);
     for (int x = 0; x < total; ++x) {
         fetch(nxt);
@@ -277,11 +279,11 @@ __device__ __forceinline__ void mfma_strips(int nK, int N, const W* __restrict__
                         b[y][c] = site < nK ? v : W(0);
                     }
                 }
-            const V4 r = cur[j];
-            const W sx = unit[0] * r[0] + unit[1] * r[1] + unit[2] * r[2];
+            const LrRec r = cur[j];
+            const double sx = unit[0] * r[0] + unit[1] * r[1] + unit[2] * r[2];
 #pragma unroll
             for (int y = 0; y < 3; ++y) {
-                const W t = sx * r[y] + unit[y] * r[3];
+                const W t = W(sx * r[y] + unit[y] * r[3]);
 #pragma unroll
                 for (int c = 0; c < NV; ++c) acc[c] = Mf::mma(t, b[y][c], acc[c]);
             }
@@ -306,7 +308,7 @@ __device__ __forceinline__ void mfma_strips(int nK, int N, const W* __restrict__
 }
 // all column tiles, three at a time; ends with a barrier
 template <bool LDSX, typename W, typename ST>
-__device__ __forceinline__ void product_tlr(int nK, int N, const W* rec, const W* X, int ldx, int ldp, ST st) {
+__device__ __forceinline__ void product_tlr(int nK, int N, const LrRec* rec, const W* X, int ldx, int ldp, ST st) {
     const int nt = (N + 15) / 16;
     for (int tc0 = 0; tc0 < nt; tc0 += 3) {
         if (nt - tc0 >= 3) mfma_strips<3, LDSX, W>(nK, N, rec, X, ldx, ldp, tc0, st);
@@ -417,14 +419,13 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax, in
 
     // --- T_LR, one 4-vector per unordered pair (see the products), zero on the diagonal and
     // for uncoupled pairs
-    typedef W W4 __attribute__((ext_vector_type(4)));
-    W4* const rec = reinterpret_cast<W4*>(T);
+    LrRec* const rec = reinterpret_cast<LrRec*>(T);
     for (int p = tid; p < nK * (nK + 1) / 2; p += blockDim.x) {
         int i = (int)((sqrtf(8.0f * (float)p + 1.0f) - 1.0f) * 0.5f);   // an estimate, corrected in integers
         while ((i + 1) * (i + 2) / 2 <= p) ++i;
         while (i * (i + 1) / 2 > p) --i;
         const int j = p - i * (i + 1) / 2;
-        W4 e = {W(0), W(0), W(0), W(0)};
+        LrRec e = {0.0, 0.0, 0.0, 0.0};
         if (i != j) {
             const double v[3] = {L.px[i] - L.px[j], L.py[i] - L.py[j], L.pz[i] - L.pz[j]};
             const double r = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
@@ -433,7 +434,7 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax, in
                 const LrPair<W> t = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut),
                                                W(a.r_buf));
                 const double sA = sqrt(fmax(double(t.A), 0.0)) / r;
-                e = W4{W(sA * v[0]), W(sA * v[1]), W(sA * v[2]), t.B};
+                e = LrRec{sA * v[0], sA * v[1], sA * v[2], double(t.B)};
             }
         }
         rec[p] = e;
@@ -454,9 +455,9 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax, in
         const int row = e / ncol, col = e % ncol;
         const int q = col / 3, c = col % 3, x = row % 3;
         const double sq = L.sqa[(size_t)(row / 3) * nq + q];
-        const W4 t = rec[tri(row / 3, 0)];
+        const LrRec t = rec[tri(row / 3, 0)];
         const double tx = x == 0 ? t[0] : x == 1 ? t[1] : t[2], tc = c == 0 ? t[0] : c == 1 ? t[1] : t[2];
-        const double u = sq * (tx * tc + (x == c ? double(t[3]) : 0.0)) * L.sqa[q];
+        const double u = sq * (tx * tc + (x == c ? t[3] : 0.0)) * L.sqa[q];
         U1[e] = W(u);
         X[operand_at(row, col)] = W(sq * u);
     }
@@ -468,8 +469,8 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax, in
             Un[(size_t)r * ncol + col] = W(L.sqa[(size_t)(r / 3) * nq + col / 3]) * v;
         };
         // (two calls, so that the compiler knows which memory the operand is in)
-        if (vlds) product_tlr<true, W>(nK, ncol, T, Vl, ldx, ldp, st);
-        else product_tlr<false, W>(nK, ncol, T, V2, ldx, ldp, st);
+        if (vlds) product_tlr<true, W>(nK, ncol, rec, Vl, ldx, ldp, st);
+        else product_tlr<false, W>(nK, ncol, rec, V2, ldx, ldp, st);
         if (m + 1 < a.mmax) {
             for (int e = tid; e < nK * ncol; e += blockDim.x) {
                 const int i = e / ncol, col = e - i * ncol;
@@ -495,8 +496,8 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax, in
                 auto st = [&](int r, int q, W v) {
                     wv[(size_t)q * N3p + r] = W(L.sqa[(size_t)(r / 3) * nq + q]) * v;
                 };
-                if (vlds) product_tlr<true, W>(nK, nq, T, Vl, ldx, ldp, st);   // ends with a barrier
-                else product_tlr<false, W>(nK, nq, T, V2, ldx, ldp, st);
+                if (vlds) product_tlr<true, W>(nK, nq, rec, Vl, ldx, ldp, st);   // ends with a barrier
+                else product_tlr<false, W>(nK, nq, rec, V2, ldx, ldp, st);
             });
 
     // --- moments mu_n(q) = <u_a, u_b>, a + b = n: eight moments (consecutive in the
@@ -581,8 +582,8 @@ __global__ void __launch_bounds__(kMbdThreads, 1) k_mbd(MbdArgs a, int nkmax, in
                         if (t2pair(i, j, r, rh, t)) nrm = (t.A + t.B) * (t.A + t.B) + 2.0 * t.B * t.B;
                     } else {
                         // |T_ij|^2 = (A + B)^2 + 2 B^2, A = |s|^2
-                        const W4 t = rec[tri(i, j)];
-                        const double A = double(t[0]) * double(t[0]) + double(t[1]) * double(t[1]) + double(t[2]) * double(t[2]);
+                        const LrRec t = rec[tri(i, j)];
+                        const double A = t[0] * t[0] + t[1] * t[1] + t[2] * t[2];
                         const double B = t[3];
                         nrm = (A + B) * (A + B) + 2.0 * B * B;
                     }
