@@ -265,14 +265,15 @@ __global__ void __launch_bounds__(kRowsThreads, 4) k_rows_lists(MbdArgs a, int p
             const double rcut = (i == 0 || j == 0) ? SI.r_mbd1 : SI.r_mbd2;
             const LrPair<W> t = lr_pair<W>(W(r), W(a.beta * (L.Rt[i] + L.Rt[j])), W(a.damp_d), W(rcut), W(a.r_buf));
             const double sA = sqrt(fmax(double(t.A), 0.0)) / r;
-            const W4 rec = {W(sA * v[0]), W(sA * v[1]), W(sA * v[2]), t.B};
+            const double u[4] = {sA * v[0], sA * v[1], sA * v[2], double(t.B)};
+            const W4 rec = {W(u[0]), W(u[1]), W(u[2]), W(u[3])};
             if (e >= 0) {
                 R.rec[R.row0(i) + e] = rec;
                 R.pj[R.row0(i) + e] = j;
             }
             if (j == 0)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) first[x][c] = double(rec[c]);
+                for (int c = 0; c < 4; ++c) first[x][c] = u[c];   // (u_1 is rounded once, at its end)
         }
         head += cnt;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");

@@ -23,7 +23,8 @@ pytestmark = pytest.mark.gpu
 CUT = dict(r_scs=0.6, r_nbr=8.0, r_mbd1=8.0, r_mbd2=3.0)
 
 
-@pytest.mark.parametrize("form,order,limit", [("dense", 2, 4.0e-8), ("dense", 4, 1.0e-7)])
+@pytest.mark.parametrize("form,order,limit", [("dense", 2, 4.0e-8), ("dense", 4, 1.0e-7), ("sparse", 2, 4.0e-8),
+                                              ("sparse", 4, 1.6e-7)])
 def test_spread_over_rotations(form, order, limit):
     import torch
     from paper_2407_06409_amd import Context, compute_batch
