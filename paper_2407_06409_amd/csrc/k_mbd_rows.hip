@@ -43,14 +43,19 @@ static_assert(kMaxSites <= (1 << kSlotBits), "slots fit their field");
 template <typename W>
 struct RowsAtom {
     typedef W W4 __attribute__((ext_vector_type(4)));
+    typedef double T4 __attribute__((ext_vector_type(4)));
+    static constexpr bool kPacked = sizeof(W) < sizeof(double);   // pair terms side by side, see term0
     int k, nK, n1, nall, N3, N3p, nq, nwe, nw, ncol, na, ldq, stride, nbox;
     const StructInfo* SI;
     const Site* S;
     MbdLds L;             // site arrays, in the workspace
     int32_t* slot_site;   // site of each slot
     uint32_t* keys;       // curve keys per site (setup only)
+    int32_t* low;         // kPacked, in the place of the keys: places of the rows' first pair terms
     double* boxes;        // bounding boxes of kBox slots
     W4* rec;              // list entries: s = sqrt(A) rhat and B (T_LR = s s^T + B I; A >= 0)
+    T4* term;             // pair terms, in the place of rec after the products
+    size_t cap;           // entries that the lists have space for
     int32_t* pj;          // list entries: slot, ascending in each row
     int32_t* uni;         // per group, from its first row's place: the union of its rows' entries, ascending
     int32_t* len;         // entries per row
@@ -58,6 +63,15 @@ struct RowsAtom {
     W *P, *V, *Q;         // P: block m - 1 holds D u_m
     __device__ W* block(int m) const { return P + (size_t)(m - 1) * N3 * ncol; }
     __device__ size_t row0(int i) const { return i == 0 ? 0 : (size_t)nK + (size_t)(i - 1) * stride; }
+    // Place of row i's first pair term (a pair's term belongs to the higher of its slots, whose
+    // row has it among its first entries).  Terms are FP64 on both paths and take the space of
+    // the 4-vectors: entry by entry where those are FP64 too, side by side where those have
+    // half the size, as every pair has two entries and one term.  (Terms rounded to FP32 are
+    // what the sums' FP64 would be lost on: forces of frames with one atom per local SCS at
+    // 6 + 3 A were 0.7 % further from FP64 in rms.  FP64 terms cost the mixed path 0 .. 1 %:
+    // 256 C at 10 + 8 A 27.7 -> 28.0 ms.)
+    __device__ size_t term0(int i) const { return kPacked ? (size_t)low[i] : row0(i); }
+    __device__ size_t terms() const { return kPacked ? cap / 2 : cap; }
 };
 
 // The atom and part of workgroup b when every atom has `parts` workgroups: an atom's
@@ -93,13 +107,15 @@ __device__ inline RowsAtom<W> rows_atom(const MbdArgs& a, int k, double* small) 
     // slots, keys and boxes take the parts of L.rb beyond the first
     R.slot_site = reinterpret_cast<int32_t*>(R.L.rb + R.nK);
     R.keys = reinterpret_cast<uint32_t*>(R.slot_site + R.nK);
+    R.low = R.slot_site + R.nK;
     R.boxes = R.L.rb + 2 * (size_t)R.nK;
     R.nbox = (R.nK + kBox - 1) / kBox;
-    const int64_t cap = rows_cap(R.nK, R.SI->m2max);
+    R.cap = (size_t)rows_cap(R.nK, R.SI->m2max);
     R.rec = reinterpret_cast<typename RowsAtom<W>::W4*>(w + G.lists);
-    R.pj = reinterpret_cast<int32_t*>(R.rec + cap);
-    R.uni = R.pj + cap;
-    R.len = R.uni + cap;
+    R.term = reinterpret_cast<typename RowsAtom<W>::T4*>(w + G.lists);
+    R.pj = reinterpret_cast<int32_t*>(R.rec + R.cap);
+    R.uni = R.pj + R.cap;
+    R.len = R.uni + R.cap;
     R.ulen = R.len + R.nK;
     R.P = w + G.P;
     R.V = w + G.V;
@@ -602,6 +618,35 @@ __global__ void __launch_bounds__(kAtomThreads) k_rows_energy(MbdArgs a) {
     const bool fit = a.fit != 0;
     double* const cfn = L.cf + (size_t)(kMaxNmax + 1) * nq;
     auto cfq = [&](int n, int q) -> double { return fit ? cfn[n * nq + q] : a.coef[n]; };
+    if (R.kPacked && a.forces) {
+        // places of the rows' pair terms: partners below each row (none for a group that outgrew
+        // its lists), then their sum over the rows before, by one wavefront
+        for (int i = tid; i < nK; i += blockDim.x) {
+            const size_t e0 = R.row0(i);
+            int lo = 0, hi = R.ulen[(i + kTriple - 1) / kTriple] > 0 ? R.len[i] : 0;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (R.pj[e0 + mid] < i) lo = mid + 1;
+                else hi = mid;
+            }
+            R.low[i] = lo;
+        }
+        __syncthreads();
+    }
+    if (R.kPacked && a.forces && wave == nwave - 1) {
+        int carry = 0;
+        for (int i0 = 0; i0 < nK; i0 += 64) {
+            const int v = i0 + lane < nK ? R.low[i0 + lane] : 0;
+            int x = v;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_up(x, o);
+                if (lane >= o) x += t;
+            }
+            if (i0 + lane < nK) R.low[i0 + lane] = carry + x - v;
+            carry += __shfl(x, 63);
+        }
+    }
     if (a.lz_steps > 0)
         lanczos_fit<W>(
             a, k, R.N3, R.N3p, L, R.V,
@@ -748,8 +793,8 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_operands(MbdArgs a, int p
 // ---------------------------------------------------------------------------
 // Each unordered coupled pair once: from row i over its partners j < i, Tbar_ij = P_i Q_j^T
 // (and the u_0 terms for j = 0), C = Tbar_ij + Tbar_ij^T, and the pair's terms (its
-// gradient with respect to r_i and its R~ term) into the entry's slot of a buffer, in the
-// place of its T_LR coefficients (used for the last time by the products).  Three rows per
+// gradient with respect to r_i and its R~ term) in FP64 into a buffer in the place of the
+// lists' T_LR coefficients (used for the last time by the products; term0).  Three rows per
 // wavefront, over the union of their entries: eight entries at a time, eight lanes per
 // entry (16 bytes of a row each), the partner's Q loaded once for the three rows' P in LDS;
 // the pairs' C wait in LDS so that the evaluation of the radial parts, longer than a
@@ -778,9 +823,9 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_pairs(MbdArgs a, int part
     const int nr = min(kTriple, nK - i0);
     const int nu = R.ulen[grp];
     const size_t u0 = R.row0(i0);
-    size_t e0[kTriple];                                  // next entry of each row
+    size_t e0[kTriple];                                  // place of the next entry's term of each row
 #pragma unroll
-    for (int x = 0; x < kTriple; ++x) e0[x] = R.row0(min(i0 + x, nK - 1));
+    for (int x = 0; x < kTriple; ++x) e0[x] = R.term0(min(i0 + x, nK - 1));
     for (int e = VW * lane; e < 3 * nr * KK; e += VW * 64) {   // P of the rows: [row][b ncol + col]
         const int row = e / KK, kk = e - row * KK, b = kk / ncol;
         *reinterpret_cast<VV*>(pi + e) =
@@ -879,7 +924,8 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_pairs(MbdArgs a, int part
                 for (int z = 0; z < 3; ++z) rCr += rh[y] * C[3 * y + z] * rh[z];
             const double ct = (3.0 * rCr - (C[0] + C[4] + C[8])) / (r * r * r);
             const size_t e = (x == 0 ? e0[0] + k0 : x == 1 ? e0[1] + k1 : e0[2] + k2);
-            R.rec[e] = typename RowsAtom<W>::W4{W(gp[0]), W(gp[1]), W(gp[2]), W(a.beta * double(lp.fLR) * double(lp.dfS) * ct)};
+            if (e < R.terms())   // (always, but in a call that is refused for an outgrown list)
+                R.term[e] = typename RowsAtom<W>::T4{gp[0], gp[1], gp[2], a.beta * double(lp.fLR) * double(lp.dfS) * ct};
         }
 #pragma unroll
         for (int y = 0; y < kTriple; ++y) e0[y] += __popcll(__ballot((ent >> (kSlotBits + y)) & 1));
@@ -912,14 +958,14 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_sums(MbdArgs a, int parts
     double g[kTriple][9];
 #pragma unroll
     for (int x = 0; x < kTriple; ++x) {
-        e0[x] = R.row0(min(i0 + x, R.nK - 1));
+        e0[x] = R.term0(min(i0 + x, R.nK - 1));
 #pragma unroll
         for (int y = 0; y < 9; ++y) g[x][y] = 0.0;
     }
     for (int t0 = 0; t0 < nu; t0 += 64) {
         const int ent = t0 + lane < nu ? R.uni[u0 + t0 + lane] : 0;
         const int j = ent & ((1 << kSlotBits) - 1), bits = ent >> kSlotBits;
-        size_t up = 0;      // the slot of the first of the rows in j's row
+        size_t up = 0, ut = 0;   // the entry of the first of the rows in j's row, and its term
         int end = 0;
         if (bits != 0 && j > i0) {
             const size_t b = R.row0(j);
@@ -931,6 +977,7 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_sums(MbdArgs a, int parts
                 else hi = mid;
             }
             up = b + lo;
+            ut = R.term0(j) + lo;
             end = n - lo;
         }
 #pragma unroll
@@ -944,17 +991,18 @@ __global__ void __launch_bounds__(kRowsThreads) k_rows_sums(MbdArgs a, int parts
                 bool ok = true;
                 if (j > i) {
                     ok = end > 0 && R.pj[up] == i;
-                    src = up;
+                    src = ut;
                     sg = -1.0;
                     ++up;
+                    ++ut;
                     --end;
                 }
-                if (ok) {
-                    const typename RowsAtom<W>::W4 t = R.rec[src];
-                    g[x][0] += sg * double(t[0]);
-                    g[x][1] += sg * double(t[1]);
-                    g[x][2] += sg * double(t[2]);
-                    g[x][3] += double(t[3]);
+                if (ok && src < R.terms()) {
+                    const typename RowsAtom<W>::T4 t = R.term[src];
+                    g[x][0] += sg * t[0];
+                    g[x][1] += sg * t[1];
+                    g[x][2] += sg * t[2];
+                    g[x][3] += t[3];
                 } else {   // the coupling relation is symmetric: never taken
                     atomicOr(a.err, 32);
                     atomicMin(a.err_atom, R.k);
