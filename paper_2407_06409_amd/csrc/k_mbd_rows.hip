@@ -1116,37 +1116,49 @@ static size_t rows_pairs_lds(const MbdArgs& a, size_t wsz) {   // per wavefront
     return sizeof(double) * 64 * 7 + wsz * ((9 * KK + 3) / 4 * 4);
 }
 
+// Atoms of one set of launches of at most `threads` work-items per atom: a launch's work-items
+// are counted in 32 bits.  Every atom has the workgroups of the call's largest neighbourhood,
+// so one of 31,000 sites (a one-atom cell at 42 A) leaves room for 6,400 atoms.
+static int rows_atoms_per_launch(int n, long long threads) {
+    return (int)std::min<long long>(n, std::max<long long>(8, 0xffffffffll / threads / 8 * 8));
+}
+
 template <typename W, bool TB, int NM>
-static hipError_t launch_rows_t(hipStream_t st, const MbdArgs& a, int nkmax) {
+static hipError_t launch_rows_t(hipStream_t st, const MbdArgs& all, int nkmax) {
     constexpr int VW = 16 / sizeof(W);
-    const bool vec = a.ncol % VW == 0;
-    const unsigned atoms8 = 8u * (unsigned)((a.n + 7) / 8);
-    const dim3 per_atom(a.n);
+    const bool vec = all.ncol % VW == 0;
     auto parts_of = [](int items, int waves) { return (items + waves - 1) / waves; };
     const int groups = (nkmax + 1) / kTriple + 1;                  // three rows per wavefront
     const int rows = parts_of(groups, kRowsWaves);                 // workgroups per atom
-    const int nlt = a.ncol / (vec ? VW : 1);
+    const int nlt = all.ncol / (vec ? VW : 1);
     const int prod = parts_of(groups * ((nlt + 63) / 64), kRowsWaves);
-    const int wl = (int)((rows_product_lds<W>(a.ncol) + 15) / 16 * 16);
-    hipLaunchKernelGGL((k_rows_setup<W>), per_atom, dim3(kAtomThreads), 0, st, a);
-    hipLaunchKernelGGL((k_rows_lists<W, TB>), dim3(atoms8 * rows), dim3(kRowsThreads), 0, st, a, rows);
-    for (int m = 1; m < a.mmax; ++m) {
-        const dim3 grid(atoms8 * prod);
-        const size_t lds = (size_t)kRowsWaves * wl;
-        if (vec) hipLaunchKernelGGL((k_rows_product<W, VW>), grid, dim3(kRowsThreads), lds, st, a, prod, m, wl);
-        else hipLaunchKernelGGL((k_rows_product<W, 1>), grid, dim3(kRowsThreads), lds, st, a, prod, m, wl);
-    }
-    const bool operands = a.forces && (a.fit || TB);   // in k_rows_energy
-    hipLaunchKernelGGL((k_rows_energy<W, TB, NM>), per_atom, dim3(kAtomThreads), rows_energy_lds(a, operands), st, a);
-    if (a.forces) {
-        if (!operands) {
-            const int per = 2 * kRowsWaves * (64 / a.nq);   // sites of a workgroup: two rounds per wavefront
-            const int ops = parts_of(nkmax, per);
-            hipLaunchKernelGGL((k_rows_operands<W, NM>), dim3(atoms8 * ops), dim3(kRowsThreads), 0, st, a, ops);
+    const int wl = (int)((rows_product_lds<W>(all.ncol) + 15) / 16 * 16);
+    const bool operands = all.forces && (all.fit || TB);   // in k_rows_energy
+    const int per = 2 * kRowsWaves * (64 / all.nq);        // sites of an operands workgroup: two rounds per wavefront
+    const int ops = parts_of(nkmax, per);
+    // P of three rows in LDS per wavefront (10 KB at 12 nodes and n_max = 6): small workgroups
+    const size_t lw = rows_pairs_lds(all, sizeof(W));
+    const int pw = 2 * lw <= 64 * 1024 ? 2 : 1, pr = parts_of(groups, pw);
+    const int most = rows_atoms_per_launch(
+        all.n, std::max(std::max((long long)kAtomThreads, 64ll * pw * pr), (long long)kRowsThreads * std::max(std::max(rows, prod), ops)));
+    for (int first = 0; first < all.n; first += most) {
+        MbdArgs a = all;
+        a.n = std::min(most, all.n - first);
+        a.order = all.order + first;
+        const unsigned atoms8 = 8u * (unsigned)((a.n + 7) / 8);
+        const dim3 per_atom(a.n);
+        hipLaunchKernelGGL((k_rows_setup<W>), per_atom, dim3(kAtomThreads), 0, st, a);
+        hipLaunchKernelGGL((k_rows_lists<W, TB>), dim3(atoms8 * rows), dim3(kRowsThreads), 0, st, a, rows);
+        for (int m = 1; m < a.mmax; ++m) {
+            const dim3 grid(atoms8 * prod);
+            const size_t lds = (size_t)kRowsWaves * wl;
+            if (vec) hipLaunchKernelGGL((k_rows_product<W, VW>), grid, dim3(kRowsThreads), lds, st, a, prod, m, wl);
+            else hipLaunchKernelGGL((k_rows_product<W, 1>), grid, dim3(kRowsThreads), lds, st, a, prod, m, wl);
         }
-        // P of three rows in LDS per wavefront (10 KB at 12 nodes and n_max = 6): small workgroups
-        const size_t lw = rows_pairs_lds(a, sizeof(W));
-        const int pw = 2 * lw <= 64 * 1024 ? 2 : 1, pr = parts_of(groups, pw);
+        hipLaunchKernelGGL((k_rows_energy<W, TB, NM>), per_atom, dim3(kAtomThreads), rows_energy_lds(a, operands), st, a);
+        if (!a.forces) continue;
+        if (!operands)
+            hipLaunchKernelGGL((k_rows_operands<W, NM>), dim3(atoms8 * ops), dim3(kRowsThreads), 0, st, a, ops);
         if (vec) hipLaunchKernelGGL((k_rows_pairs<W, VW>), dim3(atoms8 * pr), dim3(64 * pw), pw * lw, st, a, pr);
         else hipLaunchKernelGGL((k_rows_pairs<W, 1>), dim3(atoms8 * pr), dim3(64 * pw), pw * lw, st, a, pr);
         hipLaunchKernelGGL((k_rows_sums<W>), dim3(atoms8 * rows), dim3(kRowsThreads), 0, st, a, rows);
