@@ -298,10 +298,13 @@ const char* lmbd_stage_name(int32_t i);
  * it and walks only the coupled pairs (for the two-radius regime of Sec. III.A,
  * where block rows other than the central atom's couple only up to r_mbd2);
  * LMBD_MBD_AUTO (the default) takes the sparse form for each structure of a call
- * with r_mbd2 <= 0.45 r_nbr and the dense form for the others (a structure's
- * results do not depend on the batch it is in).  Both forms compute the same
- * quantities (to rounding).  LMBD_E_INVALID_ARG for a NULL context or an
- * unknown mode. */
+ * with r_mbd2 <= 0.45 r_nbr and more than 24 sites in its largest neighbourhood,
+ * and the dense form for the others (a structure's results do not depend on the
+ * batch it is in).  Both forms compute the same quantities (to rounding), and
+ * neither choice is absolute: under LMBD_MBD_SPARSE the approximate forces, and
+ * structures whose neighbourhoods are too small for the lists to fit the space
+ * of the dense form (a few sites with few nodes), still take the dense form.
+ * LMBD_E_INVALID_ARG for a NULL context or an unknown mode. */
 enum { LMBD_MBD_AUTO = 0, LMBD_MBD_DENSE = 1, LMBD_MBD_SPARSE = 2 };
 lmbd_status lmbd_set_mbd_product(lmbd_context* ctx, int32_t mode);
 

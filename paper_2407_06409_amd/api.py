@@ -78,7 +78,8 @@ class Context:
             raise C.LmbdError(st)
 
     def set_mbd_product(self, mode: str = "auto"):
-        """'auto', 'dense' (T_LR stored, matrix-core products) or 'sparse' (coupled pairs only)."""
+        """'auto', 'dense' (T_LR stored, matrix-core products) or 'sparse' (coupled pairs only, where
+        the neighbourhoods are not too small for it)."""
         code = {"auto": C.LMBD_MBD_AUTO, "dense": C.LMBD_MBD_DENSE, "sparse": C.LMBD_MBD_SPARSE}[mode]
         st = self.lib.lmbd_set_mbd_product(self.handle, code)
         if st != 0:

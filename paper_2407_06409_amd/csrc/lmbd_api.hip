@@ -1122,14 +1122,17 @@ lmbd_status lmbd_compute_batch(lmbd_context* ctx, const lmbd_params* params, int
     // MBD kernel form per structure, not per call, so that a structure's results do not
     // depend on what it shares a call with: dense-form atoms first, then sparse-form atoms,
     // each part still largest first.  Neighbourhoods beyond the dense form's LDS are always
-    // sparse; others by their radii, as long as the sparse layout fits the space reserved
-    // (it does but for neighbourhoods of a few sites with few nodes, where the dense form is
-    // no slower)
+    // sparse; others by their radii and size (kSparseMbdRatio), as long as the sparse layout
+    // fits the space reserved (it does but for neighbourhoods of a few sites with few nodes,
+    // where the dense form is no slower)
     std::vector<int> form(n_structs);
     for (int s = 0; s < n_structs; ++s) {
+        int nk = 0;   // the structure's largest neighbourhood
+        for (int64_t k = sbegin[s]; k < sbegin[s + 1]; ++k) nk = std::max(nk, cnt[k].nK);
         const bool sparse = params->force_model == LMBD_FORCES_EXACT &&   // the approximate forces use dense products
                             (ctx->mbd_product == LMBD_MBD_SPARSE ||
-                             (ctx->mbd_product == LMBD_MBD_AUTO && structs[s].r_mbd2 <= kSparseMbdRatio * structs[s].r_nbr));
+                             (ctx->mbd_product == LMBD_MBD_AUTO && nk > kSparseMbdMinSites &&
+                              structs[s].r_mbd2 <= kSparseMbdRatio * structs[s].r_nbr));
         bool fits = true;
         for (int64_t k = sbegin[s]; k < sbegin[s + 1] && sparse; ++k) {   // (the tighter space of an energy call)
             const int me = std::max(1, (n_max + 1) / 2);

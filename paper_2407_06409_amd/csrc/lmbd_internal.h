@@ -19,7 +19,14 @@ constexpr double kSqrt2OverPi = 0.79788456080286535588;    // sqrt(2/pi)
 constexpr int kMaxFreq = 33;       // omega = 0 plus up to 32 quadrature nodes
 constexpr int kMaxNmax = 12;       // highest body order
 constexpr int kMaxN1 = 256;        // atoms in K1 (r < r_scs), central atom included
-constexpr double kSparseMbdRatio = 0.45;  // automatic sparse MBD products when r_mbd2 <= this * r_nbr
+// Automatic sparse MBD products when r_mbd2 <= kSparseMbdRatio r_nbr and the structure's largest
+// neighbourhood has more than kSparseMbdMinSites sites.  Below, the row form's launches (nine
+// with forces) are what a call waits for and the dense form's one is faster, energy and forces of
+// an open cluster of n sites at 6 + 3 A, FP64: n = 2 .. 24 rows 284, 291 (4), 299 (8), 320 (12),
+// 328 (16), 363 us (24), dense 257, 259, 272, 293, 300, 353; 40 sites 398 and 426.  24 sites is
+// also where they meet for 200 clusters in a call (15.4 ms both) and for 32 nodes (499 and 501 us).
+constexpr double kSparseMbdRatio = 0.45;
+constexpr int kSparseMbdMinSites = 24;
 constexpr int kMaxNK = 400;        // sites in K (r < r_nbr), central atom included; the MBD kernel's LDS,
                                    // 8 (3 nq + 15) bytes per site for nq >= 12 nodes, caps it lower for
                                    // long grids (the host checks that limit too)
