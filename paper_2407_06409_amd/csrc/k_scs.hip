@@ -336,8 +336,6 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, co
     const int li = lane & 15, lk = lane >> 4;
     const int Nr = N + 3;                           // rows: B~, then d^T
     const int ntr = (Nr + NB - 1) / NB;             // row tiles
-    const int ntc = (N + NB - 1) / NB;              // column tiles
-    constexpr int PW = kPack<R>;
     const int npan = (N + 2 * NB - 1) / (2 * NB);   // 32-column panels
     Acc zacc;
 #pragma unroll
@@ -387,11 +385,11 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, co
             }
         }
     };
-    // (1) the update of unit u (row tiles 2u, 2u + 1; both column tiles) of the panel
-    // at column c0p (mtp row tiles from its diagonal down, a second column tile if twop)
+    // (1) the update of unit u (row tiles 2u, 2u + 1; both column tiles, whether or not the
+    // panel has them) of the panel at column c0p
     // with the chunks cb, cb + st, .. below ce: m[x][h] = A(2u + x, h)^T - (L_h L_t^T)^T,
     // starting from the matrix (init 0), from zero (1) or from m as given (2)
-    auto update = [&](int c0p, int mtp, bool twop, int u, int cb, int st, int ce, int init, Acc(&m)[2][2]) {
+    auto update = [&](int c0p, int u, int cb, int st, int ce, int init, Acc(&m)[2][2]) {
         // (the lane's indices are made opaque here so that the offsets derived from
         // them are formed per call rather than held, or spilled, over the panel loop)
         int lio = li, lko = lk;
@@ -400,15 +398,9 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, co
         // conditional block is waited for at once): a row tile past the end repeats the last
         // one, a row past a tile's end its last row; their values reach only entries that
         // nothing reads
-        bool v[2][2];
         FacTile ti[2];
 #pragma unroll
-        for (int x = 0; x < 2; ++x) {
-            const int t = 2 * u + x;
-            ti[x] = fac_tile(Nr, min(c0p / NB + t, ntr - 1));
-#pragma unroll
-            for (int h = 0; h < 2; ++h) v[x][h] = t < mtp && (h == 0 || twop) && !(t == 0 && h == 1);
-        }
+        for (int x = 0; x < 2; ++x) ti[x] = fac_tile(Nr, min(c0p / NB + (2 * u + x), ntr - 1));
         // sums of products (less m as given for init 2, less d in its rows for init 0); the
         // matrix minus them at the end
 #pragma unroll
@@ -668,7 +660,7 @@ __device__ __forceinline__ void chol_factor(R* __restrict__ A, int N, int ld, co
                 }
             }
             const int ahead = kind == kPrepare ? 1 : 0;   // (its chunks: this panel's)
-            if (have) update(c0 + 2 * NB * ahead, mt - 2 * ahead, ahead ? N - c0 - 2 * NB > NB : two, u, cb, st, nch, init, m);
+            if (have) update(c0 + 2 * NB * ahead, u, cb, st, nch, init, m);
             if (split) {
                 if (have && cb > 0) {
 #pragma unroll
@@ -1028,7 +1020,6 @@ struct ScsLds {
     double *qx, *qy, *qz, *qab, *qsg, *qR;     // shell sites
     double *Y, *X;                             // adjoint: lambda and X, 3N x 3 each
     double* H;                                 // adjoint: pair terms of one chunk, 3 per thread
-    double* gk;                                // d: sums; B~: pair values
     int32_t* key;                              // adjoint: reduction key of each thread's pair
 };
 
@@ -1081,7 +1072,7 @@ size_t scs_assemble_lds_bytes(int n1max, int n2max) {
     return std::max(dvec_lds_bytes(n1max, n2max), matrix_lds_bytes(n1max));
 }
 
-__device__ inline ScsLds scs_assemble_lds(double* base, int n1max, int n2max, bool matrix) {
+__device__ inline ScsLds scs_assemble_lds(double* base, int n1max, int n2max) {
     ScsLds L = {};
     L.px = base;
     L.py = L.px + n1max;
@@ -1095,8 +1086,6 @@ __device__ inline ScsLds scs_assemble_lds(double* base, int n1max, int n2max, bo
     L.qab = L.qz + n2max;
     L.qsg = L.qab + n2max;
     L.qR = L.qsg + n2max;
-    L.gk = L.qR + n2max;          // d: sums
-    L.key = reinterpret_cast<int32_t*>(L.gk + (matrix ? 0 : 6 * n1max));
     return L;
 }
 
@@ -1166,7 +1155,7 @@ __global__ void __launch_bounds__(kChunk) k_scs_dvec(ScsArgs a, int n1max, int n
     const int n1 = cnt.n1, n12 = cnt.n12;
     const int N = 3 * n1;
     const double rc = a.sinfo[a.atom_struct[k]].r_scs;
-    ScsLds L = scs_assemble_lds(lds, n1max, n2max, false);
+    ScsLds L = scs_assemble_lds(lds, n1max, n2max);
     double* D = (mixed ? a.dvec : a.xsol) + a.x_off[k] + (size_t)w * N * 3;
     const int32_t* seg_i = pair_segs(a, k);
     const int32_t* li = a.pl_i + a.pl_off[k];
@@ -1707,7 +1696,7 @@ __global__ void __launch_bounds__(256) k_scs_nu(ScsArgs a, int n1max, int n2max)
     const int n1 = cnt.n1, n12 = cnt.n12, n2 = n12 - n1, nall = cnt.n_all;
     const int N = 3 * n1;
     const double rc = a.sinfo[a.atom_struct[k]].r_scs;
-    ScsLds L = scs_assemble_lds(lds, n1max, n2max, false);
+    ScsLds L = scs_assemble_lds(lds, n1max, n2max);
     const double* X = a.xsol + a.x_off[k] + (size_t)w * N * 3;
     const double* Y = a.lam + a.x_off[k] + (size_t)w * N * 3;
     const int32_t* seg = pair_segs(a, k);
