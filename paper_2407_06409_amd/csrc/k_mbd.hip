@@ -215,8 +215,8 @@ __device__ __forceinline__ void mfma_syrk_nt(int M, int K, const W* __restrict__
 // conditions: a load in a conditional block is waited for at once) on their way during
 // the matrix work of this one.  Strips of 16 rows also spread evenly over the SIMDs (18
 // strips at 91 sites: 5, 5, 4, 4), where six 48-row items kept two of eight wavefronts
-// idle.  1,728 C at 6 A, per atom: four products 551k -> 396k cycles (FP32 325k -> 257k),
-// the Lanczos iteration's eleven 2,427k -> 1,596k.
+// idle.  1,728 C at 6 A, per atom: four products 551k -> 396k cycles (FP32, then with FP32
+// 4-vectors, 325k -> 257k), the Lanczos iteration's eleven 2,427k -> 1,596k.
 constexpr int kDeep = 4;
 typedef double LrRec __attribute__((ext_vector_type(4)));
 __device__ inline int tri(int i, int j) {

@@ -9,7 +9,7 @@
 //   k_rows_energy    spectrum bounds, moments, energy                 one workgroup per atom
 //   k_rows_operands  polarisability adjoints, operands of Tbar        a (site, node) per lane
 //   k_rows_pairs     Tbar and gradient of every coupled pair          three rows per wavefront
-//   k_rows_sums      pair terms summed per site                       a row per wavefront
+//   k_rows_sums      pair terms summed per site                       three rows per wavefront
 //   k_rows_final     blend adjoint, outputs                           one workgroup per atom
 // All of it is bound by gathers of the partners' rows.  What makes them cheap is where they
 // hit: the sites are ordered along a space-filling curve, so that the rows at work share

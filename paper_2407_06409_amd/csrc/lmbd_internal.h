@@ -253,8 +253,10 @@ struct MbdArgs {
     int* err_atom;             // lowest atom whose frame raised an error
     const double* e_weight;    // [n] or null
     double* e_atom;            // [n]
-    void* work;                // per atom T (N3^2), U (mmax N3 ncol), V (N3 ncol), with forces P^T and
-                               // Q^T (n_max ncol x N3 each): double or float
+    void* work;                // per atom, double or float.  Dense form: T_LR's FP64 4-vectors in the space
+                               // of N3 x N3 elements, which Tbar takes later, U (mmax N3 ncol), V and V2
+                               // (N3 ncol each), with forces P and Q (N3 x (n_max - 2) ncol each, in the
+                               // space of n_max ncol columns).  Sparse form: RowsLayout.
     const int64_t* work_off;
     int forces;
     double* abar_loc;          // per atom n1 * nw (aloc_off)
@@ -337,7 +339,8 @@ __host__ __device__ inline int64_t mbd_dense_elements(int nK, int nq, int n_max,
 // The sparse form's workspace in the same space, offsets in elements of the workspace type
 // (size wsz), each part on a 16-byte boundary: site arrays (double); the lists, row i >= 1
 // with space for `stride` entries (every site within r_mbd2 of the structure's fullest atom,
-// the central atom, slack) and the central row for nK, as 4-vectors, int32 slots, int32
+// the central atom, slack) and the central row for nK, as 4-vectors (whose space the pair terms
+// of the adjoint take after the products), int32 slots, int32
 // unions over three rows, and lengths; the Krylov blocks P; V (Lanczos vectors, central terms of Tbar); with forces Q.
 __host__ __device__ inline int rows_stride(int nK, int m2max) { return nK < m2max + 2 ? nK : m2max + 2; }
 __host__ __device__ inline int64_t rows_cap(int nK, int m2max) {
