@@ -218,7 +218,7 @@ __device__ __forceinline__ void mfma_syrk_nt(int M, int K, const W* __restrict__
 // idle.  1,728 C at 6 A, per atom: four products 551k -> 396k cycles (FP32, then with FP32
 // 4-vectors, 325k -> 257k), the Lanczos iteration's eleven 2,427k -> 1,596k.
 constexpr int kDeep = 4;
-typedef double LrRec __attribute__((ext_vector_type(4)));
+typedef double LrRec __attribute__((ext_vector_type(4), aligned(16)));   // (as the workspace is)
 __device__ inline int tri(int i, int j) {
     const int hi = max(i, j), lo = min(i, j);
     return ((hi * (hi + 1)) >> 1) + lo;

@@ -42,8 +42,8 @@ static_assert(kMaxSites <= (1 << kSlotBits), "slots fit their field");
 // What every kernel of this file derives from its atom.
 template <typename W>
 struct RowsAtom {
-    typedef W W4 __attribute__((ext_vector_type(4)));
-    typedef double T4 __attribute__((ext_vector_type(4)));
+    typedef W W4 __attribute__((ext_vector_type(4), aligned(16)));   // (as the workspace is)
+    typedef double T4 __attribute__((ext_vector_type(4), aligned(16)));
     static constexpr bool kPacked = sizeof(W) < sizeof(double);   // pair terms side by side, see term0
     int k, nK, n1, nall, N3, N3p, nq, nwe, nw, ncol, na, ldq, stride, nbox;
     const StructInfo* SI;
