@@ -185,7 +185,7 @@ __device__ __forceinline__ float bcast(float x, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
 
-// 1/sqrt(x) of a pivot.  FP64: the hardware estimate y (relative error up to 7e-8) and the series
+// 1/sqrt(x) of a pivot.  FP64: the hardware estimate y (relative error up to 5e-8) and the series
 // of (1 - e)^(-1/2) to e^2 with e = 1 - x y^2, one dependent operation more than a Newton step:
 // the solves use a pivot's value squared, and after a Newton step (error up to 3.5e-15) the
 // polarisability of an atom alone in its system was up to 7.3e-15 off (rms 7.4e-16).
